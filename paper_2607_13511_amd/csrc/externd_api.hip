@@ -441,9 +441,9 @@ static int factorize_impl(const float* A, int64_t m, int64_t n, double mu, doubl
       const int64_t c0 = blk * b_eff;
       const int bb = (int)((k - c0) < b_eff ? (k - c0) : b_eff);
       HIP_TRY(launch_select(w, (int)blk, bb, s));
+      HIP_TRY(launch_init(w, bb, tau, s));
       if (bb > BBP) {
         // a wide block: its quarters coupled through the Gram inverses
-        HIP_TRY(launch_init_wide(w, bb, tau, s));
         for (int it = 0; it < iters; ++it) {
           HIP_TRY(launch_vstep_wide(w, (int)blk, bb, tau, s, tm, weighted));
           HIP_TRY(launch_ustep_wide(w, (int)blk, bb, tau, weighted, it == iters - 1, s, tm));
@@ -451,7 +451,6 @@ static int factorize_impl(const float* A, int64_t m, int64_t n, double mu, doubl
         HIP_TRY(launch_block_out_wide(w, c0, bb, k, B_packed, C_packed, D, s));
         HIP_TRY(launch_deflate_wide(w, (int)blk, bb, false, s, tm));
       } else {
-        HIP_TRY(launch_init(w, bb, tau, s));
         for (int it = 0; it < iters; ++it) {
           HIP_TRY(launch_vstep(w, (int)blk, bb, tau, s, tm, weighted));
           HIP_TRY(launch_ustep(w, (int)blk, bb, tau, weighted, it == iters - 1, s, tm));
@@ -609,7 +608,7 @@ int externd_step_init(const float* R, int64_t m, int64_t n, const float* h, int3
   HIP_TRY(launch_prep(w, h, s));
   HIP_TRY(launch_stage(w, R, n, s));
   HIP_TRY(launch_select(w, 0, bb, s));
-  HIP_TRY(bb > BBP ? launch_init_wide(w, bb, tau, s) : launch_init(w, bb, tau, s));
+  HIP_TRY(launch_init(w, bb, tau, s));
   HIP_TRY(launch_store_factor(U_out, w.Ut, m, w.m_pad, bb, s));
   HIP_TRY(hipMemcpyAsync(J_out, w.J, sizeof(int32_t) * bb, hipMemcpyDeviceToDevice, s));
   return EXTERND_OK;

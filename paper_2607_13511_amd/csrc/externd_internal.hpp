@@ -183,6 +183,7 @@ hipError_t launch_prep(const Ws& w, const float* h, hipStream_t s, double lam = 
 hipError_t launch_stage(const Ws& w, const float* A, int64_t lda, hipStream_t s, bool track = false);
 hipError_t launch_select(const Ws& w, int blk, int bb, hipStream_t s);
 hipError_t launch_finish(const Ws& w, int blk, hipStream_t s);
+// bb up to BMAX: every quarter in the same launches.
 hipError_t launch_init(const Ws& w, int bb, double tau, hipStream_t s);
 // The contraction launches build the Gram of their factor themselves (side
 // workgroups; weighted U-step: V^T diag(H) V from the weights' digit
@@ -200,7 +201,6 @@ hipError_t launch_ustep(const Ws& w, int blk, int bb, double tau, bool weighted,
 hipError_t launch_scale(const Ws& w, int bb, hipStream_t s);
 // Wide blocks (64 < bb <= BMAX): the same steps over the quarters of the
 // block, coupled through the BMAX x BMAX Gram inverses and joint solve.
-hipError_t launch_init_wide(const Ws& w, int bb, double tau, hipStream_t s);
 hipError_t launch_vstep_wide(const Ws& w, int blk, int bb, double tau, hipStream_t s, Timer* t = nullptr,
                              bool weighted = false);
 hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weighted, bool final, hipStream_t s,

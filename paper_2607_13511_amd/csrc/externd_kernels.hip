@@ -1189,76 +1189,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   tile_stats(y, wave, j0, n, (int)(n_pad / TILE), ct, ps, pm, pi);
 }
 
-// V-step target Y = G_U^{-1} P (Eq. (3) first half) and its T_tau
-// statistics, after the contraction launch: P is the sum of the gv row
-// groups' exact partials, G_U^{-1} comes from the contraction's side path.
-// grid: n_pad / 16 tiles of 16 columns (statistics per 16-column tile).
-template <int GV>
-__device__ __forceinline__ void vtarget_sum16(const long long* __restrict__ Pp, int s, int64_t n_pad, int64_t j0,
-                                              double* Ps) {
-  long long v[GV][4];
-#pragma unroll
-  for (int g = 0; g < GV; ++g)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = threadIdx.x + q * NT, c = e >> 4, jj = e & 15;
-      v[g][q] = Pp[((int64_t)g * BBP + c) * n_pad + j0 + jj];
-    }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    long long acc = 0;
-#pragma unroll
-    for (int g = 0; g < GV; ++g) acc += v[g][q];
-    const int e = threadIdx.x + q * NT;
-    Ps[(e >> 4) * 17 + (e & 15)] = ldexp((double)acc, -s);  // column j0 + (e & 15) = j0 + (tid & 15)
-  }
-}
-
-// WIDE (a block of nq > 1 quarters, Sec. 2.4 with b up to BMAX): the
-// quarter's targets Y_q = sum_q' G^{-1}[q][q'] P_q', with ginvU the block
-// row q of the nq x nq blocks (block q' at ginvU + 4096 q') and Pp the
-// partials of quarter 0 (quarter q' at Pp + q' pq_stride); Y, ps, pm, pi are
-// the quarter's.
-template <bool WIDE>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_vtarget(const long long* __restrict__ Pp, const int* __restrict__ cshift,
-                                                int64_t n_pad, int gv, const double* __restrict__ ginvU,
-                                                double* __restrict__ Y, int64_t n, double* ps, double* pm, int* pi,
-                                                int nq, int64_t pq_stride) {
-  __shared__ double Ps[64 * 17];
-  const int tile = blockIdx.x;
-  const int ntile = (int)(n_pad / 16);
-  const int64_t j0 = (int64_t)tile * 16;
-  const int lane = lane_id(), w = wave_id();
-  const int li = lane & 15, lk = lane >> 4;
-  // the contraction's exponent of the one column this thread sums
-  const int s = cshift[j0 + (threadIdx.x & 15)];
-  double a[16];
-  v4d y[2] = {v4d{}, v4d{}};
-  static_assert(GV_MAX == 8, "one case per group count");
-  for (int q2 = 0; q2 < (WIDE ? nq : 1); ++q2) {
-    load_ginv(ginvU + (WIDE ? (int64_t)q2 * 4096 : 0), a);
-    const long long* Pq = Pp + (WIDE ? q2 * pq_stride : 0);
-    if (WIDE && q2 > 0) __syncthreads();  // Ps of the previous quarter consumed
-    switch (gv) {
-      case 1: vtarget_sum16<1>(Pq, s, n_pad, j0, Ps); break;
-      case 2: vtarget_sum16<2>(Pq, s, n_pad, j0, Ps); break;
-      case 3: vtarget_sum16<3>(Pq, s, n_pad, j0, Ps); break;
-      case 4: vtarget_sum16<4>(Pq, s, n_pad, j0, Ps); break;
-      case 5: vtarget_sum16<5>(Pq, s, n_pad, j0, Ps); break;
-      case 6: vtarget_sum16<6>(Pq, s, n_pad, j0, Ps); break;
-      case 7: vtarget_sum16<7>(Pq, s, n_pad, j0, Ps); break;
-      default: vtarget_sum16<8>(Pq, s, n_pad, j0, Ps); break;
-    }
-    __syncthreads();
-    // A = G^{-1}[16 w + li][4 ks + lk] (a), B = P[4 ks + lk][li] (LDS)
-#pragma unroll
-    for (int ks = 0; ks < 16; ++ks) y[0] = mfma_f64(a[ks], Ps[(4 * ks + lk) * 17 + li], y[0]);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) Y[(int64_t)(16 * w + lk + 4 * r) * n_pad + j0 + li] = y[0][r];
-  // the second half of the 32-wide statistics tile lies past the limit
-  tile_stats(y, w, j0, (j0 + 16 < n ? j0 + 16 : n), ntile, tile, ps, pm, pi);
-}
 // ---------------------------------------------------------------------------
 // U-step Q = R diag(h~) V  (Eq. (3) second half, Sec. 2.5); the target
 // Z = Q G_V^{-1} follows in k_utarget
@@ -1498,51 +1428,78 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   tile_stats(z, wave, i0, iend, (int)gridDim.x - 2 * nside, rt, ps, pm, pi);
 }
 
-// U-step target rows Z = Q G_V^{-1} (Eq. (3) second half) and their T_tau
-// statistics, after the contraction launch (G_V^{-1} from its side path).
-// grid: m_pad / 32 row tiles (statistics per tile).  Rows past m hold
-// Q = 0 (zero residual padding), so their targets are zero.
-// WIDE: Z_q^T = sum_q' G^{-1}[q][q'] Q_q'^T, with ginvV the block row q
-// (block q' at + 4096 q') and Q the contraction of quarter 0 (quarter q' at
-// Q + q' 64 m_pad); Z, ps, pm, pi are the quarter's.
-template <bool WIDE>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_utarget(const double* __restrict__ Q, const double* __restrict__ ginvV,
-                                                double* __restrict__ Z, int64_t m, int64_t m_pad, double* ps,
-                                                double* pm, int* pi, int nq) {
-  const int nrt = (int)(m_pad / TILE);
+// Targets of a wide block (nq > 1 quarters, Eq. (3)) and their T_tau
+// statistics, after the contraction and inverse launches:
+//   Y_q = sum_q' G^{-1}[q][q'] X_q'
+// for X = P (V-step; ginv of U^T U, tiles of 16 NH = 16 columns) or X = Q^T
+// (U-step; ginv of V^T diag(h~) V, tiles of 32 rows).  X and Y are component-
+// major with leading dimension Lp, by quarters (X's xq entries apart); ginv holds the nq x nq blocks
+// (block (q, q') at (q NQMAX + q') 4096).  Indices past L hold X = 0, so
+// their targets are zero.
+// grid: (Lp / (16 NH) tiles, nq): workgroup (tile, q), wave w its components
+// 16 w .. 16 w + 15.  Bound by the fp64 MFMA rate (2 L (64 nq)^2 flops, 62
+// cycles per 16x16x4).  X goes through LDS a quarter at a time (loads of the
+// next one in flight during the products): straight from memory, every wave
+// of the workgroup read it again, and the vector memory path, not the MFMA,
+// set the time.  9728x2560, block 256: V 51 -> 15 us,
+// U 65 -> 33 us for the four quarters (one launch per quarter before).
+template <int NH>
+__global__ __launch_bounds__(NT) void k_target_wide(const double* __restrict__ X, int64_t xq,
+                                                    const double* __restrict__ ginv, double* __restrict__ Y, int64_t L, int64_t Lp, double* ps,
+                                                    double* pm, int* pi, int nq, int64_t ntmax) {
+  // X_q' of the tile as [half][component][16]: the 32 lanes of a read phase
+  // (two components) cover all 64 banks
+  __shared__ __attribute__((aligned(16))) double Xs[2][NH][BBP][16];
   const int lane = lane_id(), w = wave_id();
   const int li = lane & 15, lk = lane >> 4;
+  const int tile = (int)blockIdx.x, ntile = (int)gridDim.x, q = (int)blockIdx.y;
+  const int64_t i0 = (int64_t)tile * 16 * NH, q0 = (int64_t)BBP * q;
+  // staging: 16-byte pairs, 8 NH per component
+  constexpr int PER = BBP * 8 * NH / NT;
+  v2d xs[PER];
+  auto fetch = [&](int q2) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = threadIdx.x + NT * u, c = e / (8 * NH), p = e % (8 * NH);
+      xs[u] = *(const v2d*)(X + q2 * xq + (int64_t)c * Lp + i0 + 2 * p);
+    }
+  };
+  auto put = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = threadIdx.x + NT * u, c = e / (8 * NH), p = e % (8 * NH);
+      *(v2d*)&Xs[buf][p >> 3][c][2 * (p & 7)] = xs[u];
+    }
+  };
   double a[16];
-  {
-    const int rt = (int)blockIdx.x;
-    const int64_t i0 = (int64_t)rt * TILE;
-    v4d z[2] = {v4d{}, v4d{}};
-    for (int q2 = 0; q2 < (WIDE ? nq : 1); ++q2) {
-      load_ginv(ginvV + (WIDE ? (int64_t)q2 * 4096 : 0), a);
-      // B = Q[4 ks + lk][i0 + li (+16)], straight from memory
-      const double* Qq = Q + (WIDE ? (int64_t)q2 * BBP * m_pad : 0);
-      double b0[16], b1[16];
+  fetch(0);
+  load_ginv(ginv + (int64_t)q * NQMAX * 4096, a);
+  put(0);
+  v4d y[2] = {v4d{}, v4d{}};
+  for (int q2 = 0; q2 < nq; ++q2) {
+    const bool more = q2 + 1 < nq;
+    if (more) fetch(q2 + 1);
+    __syncthreads();
 #pragma unroll
-      for (int ks = 0; ks < 16; ++ks) {
-        const double* qr = Qq + (int64_t)(4 * ks + lk) * m_pad + i0 + li;
-        b0[ks] = qr[0];
-        b1[ks] = qr[16];
-      }
+    for (int ks = 0; ks < 16; ++ks)
 #pragma unroll
-      for (int ks = 0; ks < 16; ++ks) {
-        z[0] = mfma_f64(a[ks], b0[ks], z[0]);
-        z[1] = mfma_f64(a[ks], b1[ks], z[1]);
-      }
+      for (int hf = 0; hf < NH; ++hf) y[hf] = mfma_f64(a[ks], Xs[q2 & 1][hf][4 * ks + lk][li], y[hf]);
+    if (more) {
+      load_ginv(ginv + ((int64_t)q * NQMAX + q2 + 1) * 4096, a);
+      put((q2 + 1) & 1);
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double* row = Z + (int64_t)(16 * w + lk + 4 * r) * m_pad + i0;
-      row[li] = z[0][r];
-      row[16 + li] = z[1][r];
-    }
-    tile_stats(z, w, i0, m, nrt, rt, ps, pm, pi);
   }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    double* row = Y + (q0 + 16 * w + lk + 4 * r) * Lp + i0 + li;
+#pragma unroll
+    for (int hf = 0; hf < NH; ++hf) row[16 * hf] = y[hf][r];
+  }
+  // NH = 1: the second half of the 32-wide statistics tile lies past the limit
+  const int64_t end = NH == 2 || i0 + 16 > L ? L : i0 + 16;
+  tile_stats(y, w, i0, end, ntile, tile, ps + q0 * ntmax, pm + q0 * ntmax, pi + q0 * ntmax);
 }
+
 // ---------------------------------------------------------------------------
 // T_tau of target components from their per-tile statistics (Eq. (2)):
 // theta = tau * (sum |x|) / L, strict ">", and when no entry exceeds theta
@@ -1672,13 +1629,26 @@ __device__ __forceinline__ void tern_range(int64_t L_pad, int sp, int ns, int64_
 // V <- T_tau(Y[c, :]) for c < bb; zero components beyond bb.  Weighted
 // (Wmf given): also the digit-scaled planes of V for the weighted Gram,
 // Wmf[d * wstride + mf_offset(c, j)] = dig_d(j) v_jc.
-// grid: BBP x ns (component c = blockIdx.x / ns, split blockIdx.x % ns).
+// grid: (BBP x ns, quarters): component c = blockIdx.x / ns of quarter
+// blockIdx.y, split blockIdx.x % ns.  The quarters of a wide block share the
+// launch: each alone is 4.7 us of latency on a few hundred workgroups.
 __global__ __launch_bounds__(NT) void k_tern_v(const double* __restrict__ Y, int64_t n, int64_t n_pad, int bb, double tau,
                                                const double* __restrict__ ps, const double* __restrict__ pm,
                                                const int* __restrict__ pi, int ntile, int ns, int8_t* __restrict__ Vt,
                                                int8_t* __restrict__ Vmf, const int8_t* __restrict__ hdig,
-                                               int8_t* __restrict__ Wmf, int64_t wstride, unsigned* ready) {
+                                               int8_t* __restrict__ Wmf, int64_t wstride, unsigned* ready,
+                                               int64_t ntmax) {
   const int c = blockIdx.x / ns, sp = blockIdx.x % ns;
+  // quarter blockIdx.y of a wide block
+  const int64_t q0 = (int64_t)BBP * blockIdx.y;
+  Y += q0 * n_pad;
+  Vt += q0 * n_pad;
+  Vmf += q0 * n_pad;
+  if (Wmf) Wmf += q0 * n_pad;
+  ps += q0 * ntmax;
+  pm += q0 * ntmax;
+  pi += q0 * ntmax;
+  bb -= (int)q0;
   if (ready && blockIdx.x == 0 && threadIdx.x == 0) *ready = 0u;  // the V-step's G_U^{-1} flag
   int64_t i0, i1;
   tern_range(n_pad, sp, ns, i0, i1);
@@ -1709,13 +1679,24 @@ __global__ __launch_bounds__(NT) void k_tern_v(const double* __restrict__ Y, int
 // split's share of g_c = sum_i U_ic Q_ic = diag(U^T R H V)_c for the joint
 // scale solve (Eq. (4)): gpart[c * TERN_SPLIT_MAX + sp], unused slots 0.
 // ps/pm/pi: statistics of ntile row groups (the U-step's groups, or 32-row
-// tiles after the initial gather).  grid: BBP x ns as k_tern_v.
+// tiles after the initial gather).  grid: (BBP x ns, quarters) as k_tern_v.
 __global__ __launch_bounds__(NT) void k_tern_u(const double* __restrict__ Z, const double* __restrict__ Q, int64_t m,
                                                int64_t m_pad, int bb, double tau, const double* __restrict__ ps,
                                                const double* __restrict__ pm, const int* __restrict__ pi, int ntile,
                                                int ns, int8_t* __restrict__ Ut, int8_t* __restrict__ Umf,
-                                               double* __restrict__ gpart, unsigned* ready) {
+                                               double* __restrict__ gpart, unsigned* ready, int64_t ntmax) {
   const int c = blockIdx.x / ns, sp = blockIdx.x % ns;
+  // quarter blockIdx.y of a wide block
+  const int64_t q0 = (int64_t)BBP * blockIdx.y;
+  Z += q0 * m_pad;
+  if (Q) Q += q0 * m_pad;
+  Ut += q0 * m_pad;
+  Umf += q0 * m_pad;
+  ps += q0 * ntmax;
+  pm += q0 * ntmax;
+  pi += q0 * ntmax;
+  gpart += q0 * TERN_SPLIT_MAX;
+  bb -= (int)q0;
   if (ready && blockIdx.x == 0 && threadIdx.x == 0) *ready = 0u;  // the U-step's G_V^{-1} flag
   int64_t i0, i1;
   tern_range(m_pad, sp, ns, i0, i1);
@@ -1743,15 +1724,23 @@ __global__ __launch_bounds__(NT) void k_tern_u(const double* __restrict__ Z, con
 // Gathers the bb selected residual columns into X (component-major fp64,
 // 64 x m_pad; zero for c >= bb) with the per-32-row-tile statistics of
 // |x| that T_tau needs; k_tern_u then thresholds them like a U target.
-// grid: m_pad/32 row tiles; thread (c = tid % 64, g = tid / 64) takes rows
+// grid: (m_pad/32 row tiles, quarters); thread (c = tid % 64, g = tid / 64) takes rows
 // 8 g .. 8 g + 7 of the tile for component c.
 __global__ __launch_bounds__(NT) void k_init_gather(const float* __restrict__ R, const int* __restrict__ J, int64_t m,
                                                     int64_t m_pad, int64_t n_pad, int bb, double* __restrict__ X,
                                                     double* __restrict__ ps, double* __restrict__ pm,
-                                                    int* __restrict__ pi) {
+                                                    int* __restrict__ pi, int64_t ntmax) {
   __shared__ double s_sum[4][BBP], s_max[4][BBP];
   __shared__ int s_idx[4][BBP];
   const int rt = blockIdx.x, ntile = (int)gridDim.x;
+  // quarter blockIdx.y of a wide block
+  const int64_t q0 = (int64_t)BBP * blockIdx.y;
+  J += q0;
+  X += q0 * m_pad;
+  ps += q0 * ntmax;
+  pm += q0 * ntmax;
+  pi += q0 * ntmax;
+  bb -= (int)q0;
   const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
   const int64_t i0 = (int64_t)rt * TILE + 8 * g;
   int jc = c < bb ? J[c] : 0;
@@ -3018,10 +3007,47 @@ __host__ __device__ __forceinline__ int pair_index(int q, int q2, int nq) {
 // added into gaccW[pair] with integer atomics (exact, order-free); the
 // sweep's first pivot launch clears gaccW again.
 // grid: npairs x nslice workgroups, workgroup (pair, slice) takes a slice of
-// the K steps.
+// the K steps; after them, in a V-step (Pp given), n_pad / 64 workgroups per
+// 16 components that replace row group 0's int64 partials of the contraction
+// by P (fp64, the sum of the gv partials scaled by 2^-cshift; each thread
+// reads and writes its own entries only).  The sum needs no inverse, so it
+// runs beside the Gram, once for all quarters.
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_gram_pairs(
-    const v4i* __restrict__ Xmf, int64_t L_pad, int nq, int nslice, int* __restrict__ gaccW) {
+    const v4i* __restrict__ Xmf, int64_t L_pad, int nq, int nslice, int* __restrict__ gaccW,
+    long long* Pp, const int* __restrict__ cshift, int64_t n_pad, int gv) {
   __shared__ int red[4 * 4096];
+  const int ngram = nq * (nq + 1) / 2 * nslice;
+  if ((int)blockIdx.x >= ngram) {
+    // columns j, j + 1 of components cc + 4 u: the partials of a pair in
+    // flight at once, from clamped row groups (masked in the sum)
+    const int b = (int)blockIdx.x - ngram;
+    const int ncol = (int)((n_pad + 63) / 64);
+    const int64_t j = (int64_t)(b % ncol) * 64 + 2 * (threadIdx.x & 31);
+    if (j >= n_pad) return;
+    const int sh0 = cshift[j], sh1 = cshift[j + 1];
+    const int c0 = 16 * (b / ncol) + (threadIdx.x >> 5);
+    v2l v[2][GV_MAX];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int c = c0 + 8 * u, q = c / BBP;
+#pragma unroll
+      for (int g = 0; g < GV_MAX; ++g)
+        v[u][g] = *(const v2l*)(Pp + (((int64_t)q * gv + (g < gv ? g : 0)) * BBP + c % BBP) * n_pad + j);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      long long s0 = 0, s1 = 0;
+#pragma unroll
+      for (int g = 0; g < GV_MAX; ++g) {
+        s0 += g < gv ? v[u][g].x : 0ll;
+        s1 += g < gv ? v[u][g].y : 0ll;
+      }
+      const int c = c0 + 8 * u;
+      *(v2d*)((double*)Pp + ((int64_t)(c / BBP) * gv * BBP + c % BBP) * n_pad + j) =
+          v2d{ldexp((double)s0, -sh0), ldexp((double)s1, -sh1)};
+    }
+    return;
+  }
   const int p = blockIdx.x / nslice, sl = blockIdx.x % nslice;
   int q, q2;
   pair_of(p, nq, q, q2);
@@ -3400,12 +3426,14 @@ hipError_t launch_colnorms(const Ws& w, int blk, double* colnorm2, double* fro2,
 }
 
 hipError_t launch_init(const Ws& w, int bb, double tau, hipStream_t s) {
-  hipLaunchKernelGGL(k_init_gather, dim3((unsigned)(w.m_pad / TILE)), dim3(NT), 0, s, w.R, w.J, w.m, w.m_pad, w.n_pad,
-                     bb, w.Z, w.tps, w.tpm, w.tpi);
+  const unsigned nq = (unsigned)((bb + BBP - 1) / BBP);
+  hipLaunchKernelGGL(k_init_gather, dim3((unsigned)(w.m_pad / TILE), nq), dim3(NT), 0, s, w.R, w.J, w.m, w.m_pad,
+                     w.n_pad, bb, w.Z, w.tps, w.tpm, w.tpi, w.ntmax);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_tern_u, dim3(BBP * w.nsu), dim3(NT), 0, s, w.Z, (const double*)nullptr, w.m, w.m_pad, bb, tau,
-                     w.tps, w.tpm, w.tpi, (int)(w.m_pad / TILE), w.nsu, w.Ut, w.Umf, w.gvec, (unsigned*)nullptr);
+  hipLaunchKernelGGL(k_tern_u, dim3(BBP * w.nsu, nq), dim3(NT), 0, s, w.Z, (const double*)nullptr, w.m, w.m_pad, bb,
+                     tau, w.tps, w.tpm, w.tpi, (int)(w.m_pad / TILE), w.nsu, w.Ut, w.Umf, w.gvec, (unsigned*)nullptr,
+                     w.ntmax);
   return hipGetLastError();
 }
 
@@ -3424,7 +3452,7 @@ hipError_t launch_vstep(const Ws& w, int blk, int bb, double tau, hipStream_t s,
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_TERNV, k_tern_v, dim3(BBP * w.nsv), dim3(NT), 0, s, (const double*)w.Y, w.n,
                        w.n_pad, bb, tau, (const double*)w.tps, (const double*)w.tpm, (const int*)w.tpi,
                        (int)(w.n_pad / TILE), w.nsv, w.Vt, w.Vmf, (const int8_t*)w.hdig, weighted ? w.Wmf : nullptr,
-                       (int64_t)BMAX * w.n_pad, ready);
+                       (int64_t)BMAX * w.n_pad, ready, w.ntmax);
   return hipGetLastError();
 }
 
@@ -3457,7 +3485,7 @@ hipError_t launch_ustep(const Ws& w, int blk, int bb, double tau, bool weighted,
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_TERNU, k_tern_u, dim3(BBP * w.nsu), dim3(NT), 0, s, (const double*)w.Z,
                        final ? (const double*)w.Q : nullptr, w.m, w.m_pad, bb, tau, (const double*)w.tps,
                        (const double*)w.tpm, (const int*)w.tpi, w.ntu - (int)NSIDE_MAX, w.nsu, w.Ut, w.Umf, w.gvec,
-                       ready);
+                       ready, w.ntmax);
   return hipGetLastError();
 }
 
@@ -3505,8 +3533,10 @@ static hipError_t wide_gram_inverse(const Ws& w, int which, bool weighted, int b
                        (const double*)w.hwmax, w.gramVW, bb, nq, EXTERND_RIDGE_REL, w.wA0, w.wflag);
   } else {
     const v4i* X = (const v4i*)(which ? w.Vmf : w.Umf);
-    hipLaunchKernelGGL(k_gram_pairs, dim3((unsigned)(npairs * GRAM_PAIR_SLICES)), dim3(NT), 0, s, X,
-                       which ? w.n_pad : w.m_pad, nq, GRAM_PAIR_SLICES, w.gaccW);
+    const unsigned nsum = which ? 0u : (unsigned)((w.n_pad + 63) / 64 * (nq * BBP / 16));
+    hipLaunchKernelGGL(k_gram_pairs, dim3((unsigned)(npairs * GRAM_PAIR_SLICES) + nsum), dim3(NT), 0, s, X,
+                       which ? w.n_pad : w.m_pad, nq, GRAM_PAIR_SLICES, w.gaccW, w.Pp, (const int*)w.cshift,
+                       w.n_pad, w.gv);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_wide_prep, dim3((unsigned)npairs), dim3(NT), 0, s, 0, (const int*)w.gaccW,
@@ -3521,14 +3551,6 @@ static hipError_t wide_gram_inverse(const Ws& w, int which, bool weighted, int b
   hipLaunchKernelGGL(k_wide_ginv, dim3((unsigned)(nq * nq)), dim3(NT), 0, s, S, nq, bb, (const int*)w.wflag,
                      which ? w.ginvVW : w.ginvUW);
   return hipGetLastError();
-}
-
-hipError_t launch_init_wide(const Ws& w, int bb, double tau, hipStream_t s) {
-  for (int q = 0; q < nq_of(bb); ++q) {
-    const hipError_t e = launch_init(quarter_view(w, q), bb_of_quarter(bb, q), tau, s);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
 }
 
 hipError_t launch_vstep_wide(const Ws& w, int blk, int bb, double tau, hipStream_t s, Timer* tm, bool weighted) {
@@ -3547,22 +3569,16 @@ hipError_t launch_vstep_wide(const Ws& w, int blk, int bb, double tau, hipStream
   }
   e = wide_gram_inverse(w, 0, false, bb, s);
   if (e != hipSuccess) return e;
-  for (int q = 0; q < nq; ++q) {
-    const Ws v = quarter_view(w, q);
-    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_VTARGET, k_vtarget<true>, dim3((unsigned)(w.n_pad / 16)), dim3(NT), 0, s,
-                         (const long long*)w.Pp, (const int*)w.cshift, w.n_pad, w.gv,
-                         (const double*)(w.ginvUW + (int64_t)q * NQMAX * 4096), v.Y, w.n, v.tps, v.tpm, v.tpi, nq,
-                         (int64_t)BBP * w.gv * w.n_pad);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_TERNV, k_tern_v, dim3(BBP * w.nsv), dim3(NT), 0, s, (const double*)v.Y,
-                         w.n, w.n_pad, bb_of_quarter(bb, q), tau, (const double*)v.tps, (const double*)v.tpm,
-                         (const int*)v.tpi, (int)(w.n_pad / 16), w.nsv, v.Vt, v.Vmf, (const int8_t*)w.hdig,
-                         weighted ? v.Wmf : nullptr, (int64_t)BMAX * w.n_pad, (unsigned*)nullptr);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_VTARGET, k_target_wide<1>, dim3((unsigned)(w.n_pad / 16), (unsigned)nq),
+                       dim3(NT), 0, s, (const double*)w.Pp, (int64_t)BBP * w.gv * w.n_pad, (const double*)w.ginvUW, w.Y, w.n, w.n_pad, w.tps, w.tpm,
+                       w.tpi, nq, w.ntmax);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_TERNV, k_tern_v, dim3(BBP * w.nsv, (unsigned)nq), dim3(NT), 0, s,
+                       (const double*)w.Y, w.n, w.n_pad, bb, tau, (const double*)w.tps, (const double*)w.tpm,
+                       (const int*)w.tpi, (int)(w.n_pad / 16), w.nsv, w.Vt, w.Vmf, (const int8_t*)w.hdig,
+                       weighted ? w.Wmf : nullptr, (int64_t)BMAX * w.n_pad, (unsigned*)nullptr, w.ntmax);
+  return hipGetLastError();
 }
 
 hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weighted, bool final, hipStream_t s,
@@ -3590,21 +3606,16 @@ hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weig
   }
   e = wide_gram_inverse(w, 1, weighted, bb, s);
   if (e != hipSuccess) return e;
-  for (int q = 0; q < nq; ++q) {
-    const Ws v = quarter_view(w, q);
-    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_UTARGET, k_utarget<true>, dim3((unsigned)(w.m_pad / TILE)), dim3(NT), 0,
-                         s, (const double*)w.Q, (const double*)(w.ginvVW + (int64_t)q * NQMAX * 4096), v.Z, w.m,
-                         w.m_pad, v.tps, v.tpm, v.tpi, nq);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_TERNU, k_tern_u, dim3(BBP * w.nsu), dim3(NT), 0, s, (const double*)v.Z,
-                         final ? (const double*)v.Q : nullptr, w.m, w.m_pad, bb_of_quarter(bb, q), tau,
-                         (const double*)v.tps, (const double*)v.tpm, (const int*)v.tpi, (int)(w.m_pad / TILE), w.nsu,
-                         v.Ut, v.Umf, v.gvec, (unsigned*)nullptr);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_UTARGET, k_target_wide<2>, dim3((unsigned)(w.m_pad / TILE), (unsigned)nq),
+                       dim3(NT), 0, s, (const double*)w.Q, (int64_t)BBP * w.m_pad, (const double*)w.ginvVW, w.Z, w.m, w.m_pad, w.tps, w.tpm,
+                       w.tpi, nq, w.ntmax);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_TERNU, k_tern_u, dim3(BBP * w.nsu, (unsigned)nq), dim3(NT), 0, s,
+                       (const double*)w.Z, final ? (const double*)w.Q : nullptr, w.m, w.m_pad, bb, tau,
+                       (const double*)w.tps, (const double*)w.tpm, (const int*)w.tpi, (int)(w.m_pad / TILE), w.nsu,
+                       w.Ut, w.Umf, w.gvec, (unsigned*)nullptr, w.ntmax);
+  return hipGetLastError();
 }
 
 // The raw V^T H V of a wide block into gramVW (the step entry point of the
@@ -3618,7 +3629,8 @@ hipError_t launch_gram_wide_raw(const Ws& w, int bb, bool weighted, hipStream_t 
 hipError_t launch_scale_wide(const Ws& w, int bb, float* D_block, hipStream_t s) {
   const int nq = nq_of(bb), npairs = nq * (nq + 1) / 2;
   hipLaunchKernelGGL(k_gram_pairs, dim3((unsigned)(npairs * GRAM_PAIR_SLICES)), dim3(NT), 0, s, (const v4i*)w.Umf,
-                     w.m_pad, nq, GRAM_PAIR_SLICES, w.gaccW);
+                     w.m_pad, nq, GRAM_PAIR_SLICES, w.gaccW, (long long*)nullptr, (const int*)nullptr,
+                     (int64_t)0, 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_wide_prep, dim3((unsigned)npairs), dim3(NT), 0, s, 2, (const int*)w.gaccW,
