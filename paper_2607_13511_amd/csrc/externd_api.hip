@@ -446,7 +446,7 @@ static int factorize_impl(const float* A, int64_t m, int64_t n, double mu, doubl
         // a wide block: its quarters coupled through the Gram inverses
         for (int it = 0; it < iters; ++it) {
           HIP_TRY(launch_vstep_wide(w, (int)blk, bb, tau, s, tm, weighted));
-          HIP_TRY(launch_ustep_wide(w, (int)blk, bb, tau, weighted, it == iters - 1, s, tm));
+          HIP_TRY(launch_ustep_wide(w, (int)blk, bb, tau, weighted, it == 0, it == iters - 1, s, tm));
         }
         HIP_TRY(launch_block_out_wide(w, c0, bb, k, B_packed, C_packed, D, s));
         HIP_TRY(launch_deflate_wide(w, (int)blk, bb, false, s, tm));
@@ -647,7 +647,7 @@ int externd_step_ustep(const float* R, int64_t m, int64_t n, const int8_t* V, in
   HIP_TRY(launch_stage(w, R, n, s));
   HIP_TRY(load_factor_quarters(w, 1, V, n, bb, s));
   if (h) HIP_TRY(launch_vweight(w, bb, s));
-  HIP_TRY(bb > BBP ? launch_ustep_wide(w, 0, bb, tau, h != nullptr, false, s)
+  HIP_TRY(bb > BBP ? launch_ustep_wide(w, 0, bb, tau, h != nullptr, true, false, s)
                    : launch_ustep(w, 0, bb, tau, h != nullptr, false, s, nullptr, true));
   HIP_TRY(launch_store_factor(U_out, w.Ut, m, w.m_pad, bb, s));
   if (Q_out_or_null) HIP_TRY(launch_store_cm(Q_out_or_null, w.Q, m, w.m_pad, bb, s));

@@ -203,8 +203,9 @@ hipError_t launch_scale(const Ws& w, int bb, hipStream_t s);
 // block, coupled through the BMAX x BMAX Gram inverses and joint solve.
 hipError_t launch_vstep_wide(const Ws& w, int blk, int bb, double tau, hipStream_t s, Timer* t = nullptr,
                              bool weighted = false);
-hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weighted, bool final, hipStream_t s,
-                             Timer* t = nullptr);
+// first: the first U-step on this residual (the rows' bounds not measured yet).
+hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weighted, bool first, bool final,
+                             hipStream_t s, Timer* t = nullptr);
 hipError_t launch_scale_wide(const Ws& w, int bb, float* D_block, hipStream_t s);
 hipError_t launch_gram_wide_raw(const Ws& w, int bb, bool weighted, hipStream_t s);
 hipError_t launch_block_out_wide(const Ws& w, int64_t c0, int bb, int64_t k, uint8_t* Bp, uint8_t* Cp, float* D,

@@ -1428,6 +1428,257 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   tile_stats(z, wave, i0, iend, (int)gridDim.x - 2 * nside, rt, ps, pm, pi);
 }
 
+// ---------------------------------------------------------------------------
+// Contractions of a wide block (nq = 2 .. 4 quarters of 64 components): one
+// pass over R for all of them.  A workgroup's four waves convert four K
+// steps of its 32 x 32 residual tiles to digit planes at a time, share them
+// through LDS (double-buffered, one barrier per round), and wave q multiplies
+// all four by its quarter's trits, so each residual entry is read and
+// converted once and no cross-wave sum is left (waves nq .. 3 only convert).
+// Per K step a wave issues 8 MFMAs (256 cycles) against 4 LDS reads and two
+// trit loads; at nq = 4 the matrix cores need 10 us of a 9728 x 2560 pass,
+// the residual's read 16.  One launch per quarter, each reading R, took
+// 4 x 20.2 us (V) and 4 x 21.8 us (U); this takes 33 and 44 us.
+// ---------------------------------------------------------------------------
+constexpr int WIDE_KB = NT / 64;  // K steps per round
+struct WidePlanes { v4i p[2][WIDE_KB][4][64]; };
+
+// The MFMAs of K step u of a round: x = the wave's trit operands, reloaded
+// from `next` (the same K step of the next round) once used.  ROWS: the planes
+// are the A operand (output rows = residual rows), else the B operand (output
+// columns = residual columns).
+template <bool ROWS>
+__device__ __forceinline__ void wide_products(const WidePlanes& sp, int buf, int u, v4i (&x)[2], const v4i* next,
+                                              v16i (&acc)[2][4]) {
+  const int lane = lane_id();
+  v4i P[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) P[p] = sp.p[buf][u][p][lane];
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      acc[t][p] = ROWS ? mfma_i8(P[p], x[t], acc[t][p]) : mfma_i8(x[t], P[p], acc[t][p]);
+  x[0] = next[0];
+  x[1] = next[64];
+}
+
+// P = U^T R of a wide block, row-group partials as k_vstep's: quarter q at
+// Pp + q gv 64 n_pad.  grid: (n_pad/32 column tiles) x gv.
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_vstep_wide(
+    const float* __restrict__ R, const v4i* __restrict__ Umf, long long* __restrict__ Pp,
+    const int* __restrict__ cshift, int64_t m_pad, int64_t n_pad, int gv, int nq) {
+  __shared__ WidePlanes sp;
+  const int nct = (int)(n_pad / TILE);
+  const int ct = blockIdx.x % nct, g = blockIdx.x / nct;
+  const int nks = (int)(m_pad / TILE);
+  const int ks0 = (int)((long long)g * nks / gv), ks1 = (int)((long long)(g + 1) * nks / gv);
+  const int lane = lane_id(), wave = wave_id();
+  const int h = lane >> 5, l32 = lane & 31;
+  const int s = cshift[(int64_t)ct * TILE + l32];
+  const float* Rc = R + (int64_t)ct * TILE + l32;
+  const v4i* Uq = Umf + (int64_t)(wave < nq ? wave : 0) * 4 * m_pad + lane;
+  v16i acc[2][4];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int p = 0; p < 4; ++p) acc[t][p] = v16i{};
+  // K steps past the row group load its last one again and convert to zero
+  float xn[16];
+  auto load_r = [&](int ks) {
+    const int64_t i0 = (int64_t)(ks < ks1 ? ks : ks1 - 1) * TILE + 16 * h;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) xn[q] = Rc[(i0 + q) * n_pad];
+  };
+  auto convert = [&](int ks, int buf) {
+    const int sk = ks < ks1 ? s : -1000;
+    unsigned y[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) y[q] = fx_biased(xn[q], sk);
+    v4i P[4];
+    make_planes(y, P);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) sp.p[buf][wave][p][lane] = P[p];
+  };
+  auto trits = [&](int ks) { return Uq + (int64_t)(ks < ks1 ? ks : ks1 - 1) * 128; };
+  if (ks0 < ks1) {
+    v4i a[WIDE_KB][2];
+    load_r(ks0 + wave);
+#pragma unroll
+    for (int u = 0; u < WIDE_KB; ++u) {
+      a[u][0] = trits(ks0 + u)[0];
+      a[u][1] = trits(ks0 + u)[64];
+    }
+    convert(ks0 + wave, 0);
+    load_r(ks0 + WIDE_KB + wave);
+    // round r: its products, with the conversion of round r + 1 and the loads
+    // of round r + 2 in the same straight line for the scheduler to mix
+    int buf = 0;
+    for (int base = ks0; base < ks1; base += WIDE_KB, buf ^= 1) {
+      __syncthreads();
+      const int nb = base + WIDE_KB;
+      wide_products<false>(sp, buf, 0, a[0], trits(nb), acc);
+      wide_products<false>(sp, buf, 1, a[1], trits(nb + 1), acc);
+      convert(nb + wave, buf ^ 1);
+      load_r(nb + WIDE_KB + wave);
+      __builtin_amdgcn_sched_barrier(0);  // the loads stay here, a round ahead of their use
+      wide_products<false>(sp, buf, 2, a[2], trits(nb + 2), acc);
+      wide_products<false>(sp, buf, 3, a[3], trits(nb + 3), acc);
+    }
+  }
+  if (wave >= nq) return;
+  long long* Pg = Pp + ((int64_t)(wave * gv + g) * BBP) * n_pad + (int64_t)ct * TILE;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      Pg[(int64_t)(32 * t + 8 * (r >> 2) + 4 * h + (r & 3)) * n_pad + l32] = combine_acc(acc, t, r);
+}
+
+// Q = R diag(h~) V of a wide block, component-major fp64 by quarters, and
+// the rows' measured bounds, as k_ustep.  grid: row groups of `rows` <= 32
+// rows.  Lane l loads 4 consecutive columns of rows 8 q + l / 8 (whole
+// 128-byte row segments per instruction), converts them with their rows'
+// exponents and writes each plane's 4 digits as one word of the operand.
+template <bool WEIGHTED>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_ustep_wide(
+    const float* __restrict__ R, const v4i* __restrict__ Vmf, const double* __restrict__ hw, double* __restrict__ Q,
+    float* __restrict__ rowb, int64_t m_pad, int64_t n_pad, int rows, int nq) {
+  constexpr int QLD = 34;  // doubles per component row of the output transpose
+  __shared__ union {
+    WidePlanes sp;
+    double tq[4][32 * QLD];
+  } sm;
+  __shared__ int s_row[TILE];
+  __shared__ int s_rmax[4][TILE];
+  const int64_t i0 = (int64_t)blockIdx.x * rows;
+  if (i0 >= m_pad) return;
+  const int valid = (int)(m_pad - i0 < rows ? m_pad - i0 : rows);
+  const int lane = lane_id(), wave = wave_id();
+  const int h = lane >> 5, l32 = lane & 31;
+  const int nks = (int)(n_pad / TILE);
+  const int lrow = lane >> 3, lch = lane & 7;
+  // rows past `valid` read the last valid row; their results are discarded
+  const float* Rr[4];
+  float p2s[4];
+  double cw[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = 8 * q + lrow < valid ? 8 * q + lrow : valid - 1;
+    Rr[q] = R + (i0 + r) * n_pad + 4 * lch;
+    const int s = fx_shift(rowb[i0 + r]);
+    p2s[q] = __builtin_amdgcn_ldexpf(1.0f, s);  // x 2^s = x * p2s exactly
+    cw[q] = weighted_round_const(s);
+    if (wave == 0 && lch == 0) s_row[8 * q + lrow] = s;
+  }
+  // the largest |x h~_j| of each row seen by this lane (k_ustep)
+  float rmax[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  constexpr int BIAS = 0x00808080;
+  int ymin[4] = {BIAS, BIAS, BIAS, BIAS}, ymax[4] = {BIAS, BIAS, BIAS, BIAS};
+  const v4i* Vq = Vmf + (int64_t)(wave < nq ? wave : 0) * 4 * n_pad + lane;
+  v16i acc[2][4];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int p = 0; p < 4; ++p) acc[t][p] = v16i{};
+  v4f xn[4];
+  v2d wn[2];
+  auto load_r = [&](int ks) {
+    const int64_t j = (int64_t)(ks < nks ? ks : nks - 1) * TILE;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) xn[q] = *(const v4f*)(Rr[q] + j);
+    if (WEIGHTED) {
+      wn[0] = *(const v2d*)(hw + j + 4 * lch);
+      wn[1] = *(const v2d*)(hw + j + 4 * lch + 2);
+    }
+  };
+  // plane word of (row, chunk): operand lane row + 32 (chunk / 4), word chunk % 4
+  const int wofs = (lrow + 32 * (lch >> 2)) * 4 + (lch & 3);
+  // K steps past the last load it again and convert to zero
+  auto convert = [&](int ks, int buf) {
+    const bool in = ks < nks;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      unsigned y[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (WEIGHTED) {
+          y[e] = fx_biased_w(xn[q][e], in ? wn[e >> 1][e & 1] : 0.0, cw[q]);
+          ymin[q] = min(ymin[q], (int)y[e]);
+          ymax[q] = max(ymax[q], (int)y[e]);
+        } else {
+          y[e] = fx_biased_m(xn[q][e], in ? p2s[q] : 0.0f);
+          rmax[q] = fmaxf(rmax[q], fabsf(xn[q][e]));
+        }
+      }
+      int w4[4];
+      planes4(y[0], y[1], y[2], y[3], w4[0], w4[1], w4[2], w4[3]);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) ((int*)sm.sp.p[buf][wave][p])[wofs + 32 * q] = w4[p];
+    }
+  };
+  auto trits = [&](int ks) { return Vq + (int64_t)(ks < nks ? ks : nks - 1) * 128; };
+  {
+    v4i b[WIDE_KB][2];
+    load_r(wave);
+#pragma unroll
+    for (int u = 0; u < WIDE_KB; ++u) {
+      b[u][0] = trits(u)[0];
+      b[u][1] = trits(u)[64];
+    }
+    convert(wave, 0);
+    load_r(WIDE_KB + wave);
+    int buf = 0;
+    for (int base = 0; base < nks; base += WIDE_KB, buf ^= 1) {
+      __syncthreads();
+      const int nb = base + WIDE_KB;
+      wide_products<true>(sm.sp, buf, 0, b[0], trits(nb), acc);
+      wide_products<true>(sm.sp, buf, 1, b[1], trits(nb + 1), acc);
+      convert(nb + wave, buf ^ 1);
+      load_r(nb + WIDE_KB + wave);
+      __builtin_amdgcn_sched_barrier(0);
+      wide_products<true>(sm.sp, buf, 2, b[2], trits(nb + 2), acc);
+      wide_products<true>(sm.sp, buf, 3, b[3], trits(nb + 3), acc);
+    }
+  }
+  // measured row bounds: over the 8 lanes of a row, then the waves
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    int v = WEIGHTED ? max(ymax[q] - BIAS, BIAS - ymin[q]) : __float_as_int(rmax[q]);  // non-negative floats order like ints
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
+    if (lch == 0) s_rmax[wave][8 * q + lrow] = v;
+  }
+  __syncthreads();  // the planes have been read, too
+  if (threadIdx.x < valid) {
+    const int i = threadIdx.x;
+    int r = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r = max(r, s_rmax[q][i]);
+    rowb[i0 + i] = WEIGHTED ? __int2float_ru(r + 1) * __builtin_amdgcn_ldexpf(1.0f, -s_row[i]) : __int_as_float(r);
+  }
+  if (wave >= nq) return;
+  // out[t][M = row][N = component] -> Q[64 wave + 32 t + N][row] through this
+  // wave's own transposed LDS tile
+  double* tq = sm.tq[wave];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      const int M = 8 * (r >> 2) + 4 * h + (r & 3);
+      *(v2d*)(tq + l32 * QLD + M) = v2d{ldexp((double)combine_acc(acc, t, r), -s_row[M]),
+                                        ldexp((double)combine_acc(acc, t, r + 1), -s_row[M + 1])};
+    }
+    double* Qt = Q + (int64_t)(BBP * wave + 32 * t) * m_pad + i0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int N = 2 * k + h;
+      const double v = tq[N * QLD + l32];
+      if (l32 < valid) Qt[(int64_t)N * m_pad + l32] = v;
+    }
+  }
+}
+
 // Targets of a wide block (nq > 1 quarters, Eq. (3)) and their T_tau
 // statistics, after the contraction and inverse launches:
 //   Y_q = sum_q' G^{-1}[q][q'] X_q'
@@ -3556,17 +3807,10 @@ static hipError_t wide_gram_inverse(const Ws& w, int which, bool weighted, int b
 hipError_t launch_vstep_wide(const Ws& w, int blk, int bb, double tau, hipStream_t s, Timer* tm, bool weighted) {
   const int nq = nq_of(bb);
   hipError_t e;
-  // P_q = U_q^T R per quarter (contraction launches without a side path)
-  for (int q = 0; q < nq; ++q) {
-    const Ws v = quarter_view(w, q);
-    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_VSTEP, k_vstep, dim3((unsigned)((w.n_pad / TILE) * w.gv)), dim3(NT), 0,
-                         s, w.R, (const v4i*)v.Umf, v.Pp, (const int*)w.cshift, w.m_pad, w.n_pad, w.gv,
-                         bb_of_quarter(bb, q), w.gacc, w.counters + CNT_GRAM_U, w.ginvU, 0, (double*)nullptr,
-                         (double*)nullptr, (double*)nullptr, (int*)nullptr, w.n, (unsigned*)nullptr,
-                         (unsigned*)nullptr, (int*)nullptr);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_VSTEP, k_vstep_wide, dim3((unsigned)((w.n_pad / TILE) * w.gv)), dim3(NT), 0,
+                       s, w.R, (const v4i*)w.Umf, w.Pp, (const int*)w.cshift, w.m_pad, w.n_pad, w.gv, nq);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
   e = wide_gram_inverse(w, 0, false, bb, s);
   if (e != hipSuccess) return e;
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_VTARGET, k_target_wide<1>, dim3((unsigned)(w.n_pad / 16), (unsigned)nq),
@@ -3581,29 +3825,42 @@ hipError_t launch_vstep_wide(const Ws& w, int blk, int bb, double tau, hipStream
   return hipGetLastError();
 }
 
-hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weighted, bool final, hipStream_t s,
-                             Timer* tm) {
+hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weighted, bool first, bool final,
+                             hipStream_t s, Timer* tm) {
   const int nq = nq_of(bb);
   hipError_t e;
-  // Q_q = R diag(h~) V_q per quarter (contraction launches without a side path)
-  for (int q = 0; q < nq; ++q) {
-    const Ws v = quarter_view(w, q);
-    const int bq = bb_of_quarter(bb, q);
+  const unsigned nrow = (unsigned)((w.m_pad + w.urows - 1) / w.urows);
+  int q0 = 0;
+  if (first) {
+    // The rows' bounds are those that the deflation raised.  Quarter 0's pass
+    // measures them, and the other quarters convert at the measured bounds'
+    // exponents (two to four bits finer after a wide block's deflation).
     if (weighted)
-      EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (k_ustep<true>), dim3((unsigned)w.ntu), dim3(NT), 0, s, w.R,
-                           (const v4i*)v.Vmf, v.Vr, w.hw, v.Q, w.rowb, w.m_pad, w.n_pad, bq, w.gacc + 4096,
+      EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (k_ustep<true>), dim3(nrow), dim3(NT), 0, s, w.R,
+                           (const v4i*)w.Vmf, w.Vr, w.hw, w.Q, w.rowb, w.m_pad, w.n_pad, BBP, w.gacc + 4096,
                            w.counters + CNT_GRAM_V, w.ginvV, w.gramV, 0, w.urows, (const int8_t*)nullptr,
                            (long long*)nullptr, (const double*)nullptr, (double*)nullptr, (double*)nullptr,
                            (double*)nullptr, (int*)nullptr, w.m, (unsigned*)nullptr, (int*)nullptr, 1);
     else
-      EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (k_ustep<false>), dim3((unsigned)w.ntu), dim3(NT), 0, s, w.R,
-                           (const v4i*)v.Vmf, v.Vr, w.hw, v.Q, w.rowb, w.m_pad, w.n_pad, bq, w.gacc + 4096,
+      EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (k_ustep<false>), dim3(nrow), dim3(NT), 0, s, w.R,
+                           (const v4i*)w.Vmf, w.Vr, w.hw, w.Q, w.rowb, w.m_pad, w.n_pad, BBP, w.gacc + 4096,
                            w.counters + CNT_GRAM_V, w.ginvV, w.gramV, 0, w.urows, (const int8_t*)nullptr,
                            (long long*)nullptr, (const double*)nullptr, (double*)nullptr, (double*)nullptr,
                            (double*)nullptr, (int*)nullptr, w.m, (unsigned*)nullptr, (int*)nullptr, 1);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
+    q0 = 1;
   }
+  const v4i* Vq = (const v4i*)(w.Vmf + (int64_t)BBP * q0 * w.n_pad);
+  double* Qq = w.Q + (int64_t)BBP * q0 * w.m_pad;
+  if (weighted)
+    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, k_ustep_wide<true>, dim3(nrow), dim3(NT), 0, s, w.R, Vq,
+                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows, nq - q0);
+  else
+    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, k_ustep_wide<false>, dim3(nrow), dim3(NT), 0, s, w.R, Vq,
+                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows, nq - q0);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
   e = wide_gram_inverse(w, 1, weighted, bb, s);
   if (e != hipSuccess) return e;
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_UTARGET, k_target_wide<2>, dim3((unsigned)(w.m_pad / TILE), (unsigned)nq),
