@@ -314,70 +314,167 @@ __device__ __forceinline__ void block_argmax(double& v, long long& i, double* sh
 }
 
 // ---------------------------------------------------------------------------
-// 64x64 SPD inverse: block sweep operator (block Gauss-Jordan without
-// pivoting, stable for SPD) with 4x4 pivot blocks and fp64 MFMA updates.
-// A: LDS 64x64 row-major, in: matrix, out: inverse.  pbuf: LDS 1024 doubles.
-// Requires blockDim.x == 256.
+// 64x64 SPD inverse: sweep operator (Gauss-Jordan without pivoting, stable
+// for SPD) by 16x16 blocks on fp64 MFMA, pivots in pairs inside a block.
+// blockDim.x == 256.
 //
 // The matrix is first scaled exactly by powers of two, A~ = S A S with
 // S = diag(2^-e_i), so that every diagonal entry lies in [0.5, 2); then
-// A^{-1} = S A~^{-1} S.  Sweeping the pivot block K (4 indices) with
-// P = A~_KK maps A_ij -> A_ij - A_iK P^{-1} A_Kj (i, j outside K),
-// A_iK -> A_iK P^{-1}, A_Kj -> P^{-1} A_Kj, A_KK -> -P^{-1}; after all 16
-// blocks the matrix is -A~^{-1}.  With C = A~[:, K] - E_K all four cases
-// are the single rank-4 update A -= (C P^{-1}) C^T, except the diagonal of
-// the pivot block, which needs a further -2.
+// A^{-1} = S A~^{-1} S.  Sweeping block K with P = A~_KK maps
+// A_ij -> A_ij - A_iK P^{-1} A_Kj (i, j outside K), A_iK -> A_iK P^{-1},
+// A_Kj -> P^{-1} A_Kj, A_KK -> -P^{-1}; after all blocks the matrix is
+// -A~^{-1}.
 //
-// Wave w holds tile row w of A in v_mfma_f64_16x16x4f64 accumulators
-// (lane l, register r, tile nt <-> A[16 w + l/16 + 4 r][16 nt + l%16]);
-// the sweep keeps A symmetric, so C^T is the pivot rows minus E_K^T, held
-// by one wave: it publishes them through LDS, every lane forms P^{-1}
-// (closed form by 2x2 Schur blocks) and its entry of W = -C P^{-1}, and
-// each wave applies W C^T to its four tiles with four MFMAs.  One barrier
-// per step (the published rows are double-buffered).
+// A 16x16 tile is kept as v_mfma_f64_16x16x4f64 leaves it: lane l, register
+// r <-> row l / 16 + 4 r, column l % 16.  As the B operand of K step r that
+// register is the tile itself, as the A operand it is the tile's transpose,
+// and the swept matrix stays symmetric, so every product below takes its
+// operands from tiles as they are.  Wave w owns tile column w (in LDS, at
+// 4 i + w).  The wave of the pivot block sweeps it in registers (sweep16)
+// and publishes N = -P^{-1}; every other wave forms T = N A_Kw, updates
+// tile (K + 1, w) first, and the wave of block K + 1 goes straight on to
+// its pivot block while the others finish: the chain is four sweep16 and,
+// between them, 8 MFMAs and one barrier.
+//
+// Bound by latency: a 16x16x4 takes 62 cycles (not pipelined), an LDS round
+// trip 130, a dependent fp64 operation 8, an issue 5; sweep16 takes 2000
+// cycles, a step 3700.  17.7 K cycles in all, 10.3 K for 32 components; the
+// sweep by 4x4 pivot blocks that every wave inverted for itself (16 steps of
+// 1200) took 22.7 K and 13.3 K.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ v4d mfma_f64(double a, double b, v4d c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// 1 / x for the pivots of the sweep below: the hardware estimate refined by
-// two Newton steps r <- r (2 - x r) (error ~ 1 ulp).  The sweep works on a
-// matrix scaled to a unit-order diagonal, so x is far from the denormal and
+// 1 / x for the pivots: the hardware estimate (24 bits) refined by one cubic
+// step, r (1 + e + e^2) with e = 1 - x r.  The sweep works on a matrix
+// scaled to a unit-order diagonal, so x is far from the denormal and
 // overflow ranges that the full IEEE division sequence guards against.
 __device__ __forceinline__ double recip_nr(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = r * fma(-x, r, 2.0);
-  r = r * fma(-x, r, 2.0);
-  return r;
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 
-// Inverse of the symmetric 4x4 block [[A, B], [B^T, D]] (2x2 blocks) by the
-// Schur complement S = D - B^T A^{-1} B; uses the upper triangle of P.
-__device__ __forceinline__ void spd_inverse4(const double (&P)[4][4], double (&Pi)[4][4]) {
-  const double ra = recip_nr(P[0][0] * P[1][1] - P[0][1] * P[0][1]);
-  const double a00 = P[1][1] * ra, a01 = -P[0][1] * ra, a11 = P[0][0] * ra;
-  // X = A^{-1} B
-  const double x00 = a00 * P[0][2] + a01 * P[1][2], x01 = a00 * P[0][3] + a01 * P[1][3];
-  const double x10 = a01 * P[0][2] + a11 * P[1][2], x11 = a01 * P[0][3] + a11 * P[1][3];
-  // S = D - B^T X
-  const double s00 = P[2][2] - (P[0][2] * x00 + P[1][2] * x10);
-  const double s01 = P[2][3] - (P[0][2] * x01 + P[1][2] * x11);
-  const double s11 = P[3][3] - (P[0][3] * x01 + P[1][3] * x11);
-  const double rs = recip_nr(s00 * s11 - s01 * s01);
-  const double t00 = s11 * rs, t01 = -s01 * rs, t11 = s00 * rs;
-  // Y = X S^{-1}
-  const double y00 = x00 * t00 + x01 * t01, y01 = x00 * t01 + x01 * t11;
-  const double y10 = x10 * t00 + x11 * t01, y11 = x10 * t01 + x11 * t11;
-  Pi[0][0] = a00 + (y00 * x00 + y01 * x01);
-  Pi[0][1] = a01 + (y00 * x10 + y01 * x11);
-  Pi[1][0] = Pi[0][1];
-  Pi[1][1] = a11 + (y10 * x10 + y11 * x11);
-  Pi[0][2] = -y00; Pi[0][3] = -y01;
-  Pi[1][2] = -y10; Pi[1][3] = -y11;
-  Pi[2][0] = -y00; Pi[3][0] = -y01;
-  Pi[2][1] = -y10; Pi[3][1] = -y11;
-  Pi[2][2] = t00; Pi[2][3] = t01;
-  Pi[3][2] = t01; Pi[3][3] = t11;
+// Lane L of each row of 16 lanes, in every lane of the row.
+template <int L>
+__device__ __forceinline__ double row_bcast(double v) {
+  const long long b = __double_as_longlong(v);
+  return __longlong_as_double(__builtin_amdgcn_update_dpp(b, b, 0x150 + L, 0xF, 0xF, false));
+}
+// The values of the even and the odd row of each pair of 16-lane rows, in
+// both rows.
+__device__ __forceinline__ void pair_rows(double x, double& even, double& odd) {
+  const int lo = __double2loint(x), hi = __double2hiint(x);
+  const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  even = __hiloint2double(h[0], l[0]);
+  odd = __hiloint2double(h[1], l[1]);
+}
+// Sweeps pivots P, P + 1 (P even) of the 16x16 tile d: with C the two pivot
+// rows minus the identity's and Pi the inverse of their 2x2 block, all cases
+// of the sweep are d -= (C^T Pi) C, except that the pivots' diagonal
+// entries keep 2 too much (no later step reads them; taken off at the end).
+// The rows lie in one pair of lane rows, which is the K slots of the MFMA
+// that holds them; the other two slots get zero.
+template <int P>
+__device__ __forceinline__ void sweep_pair(v4d& d, int lr, int lc) {
+  constexpr int q = P >> 2, gp = (P >> 1) & 1;
+  double r0, r1;
+  pair_rows(d[q], r0, r1);
+  const double a = row_bcast<P>(r0), b = row_bcast<P + 1>(r0), c = row_bcast<P + 1>(r1);
+  const double det = fma(a, c, -(b * b));
+  const bool odd = lr & 1;
+  const double c0 = r0 - (lc == P ? 1.0 : 0.0), c1 = r1 - (lc == P + 1 ? 1.0 : 0.0);
+  // this lane row's row of det Pi C
+  const double t = fma(c0, odd ? -b : c, c1 * (odd ? a : -b));
+  const double wv = -(t * recip_nr(det));
+  d = mfma_f64((lr >> 1) == gp ? wv : 0.0, odd ? c1 : c0, d);
+}
+// d -> -d^{-1}
+__device__ __forceinline__ void sweep16(v4d& d, int lr, int lc) {
+  sweep_pair<0>(d, lr, lc);
+  sweep_pair<2>(d, lr, lc);
+  sweep_pair<4>(d, lr, lc);
+  sweep_pair<6>(d, lr, lc);
+  sweep_pair<8>(d, lr, lc);
+  sweep_pair<10>(d, lr, lc);
+  sweep_pair<12>(d, lr, lc);
+  sweep_pair<14>(d, lr, lc);
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (lr + 4 * r == lc) d[r] -= 2.0;
+}
+// Tiles in LDS or memory: registers of a lane in pairs.
+__device__ __forceinline__ void put_tile(v2d* p, const v4d& x) {
+  p[lane_id()] = v2d{x[0], x[1]};
+  p[64 + lane_id()] = v2d{x[2], x[3]};
+}
+__device__ __forceinline__ v4d get_tile(const v2d* p) {
+  const v2d a = p[lane_id()], b = p[64 + lane_id()];
+  return v4d{a.x, a.y, b.x, b.y};
+}
+// c += X^T y (X symmetric: X y)
+__device__ __forceinline__ void mul_tile(const v4d& x, const v4d& y, v4d& c) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) c = mfma_f64(x[r], y[r], c);
+}
+// Sweeps blocks 0 .. nb - 1 of the symmetric 4x4 tiles (tile (i, j) at
+// tile + 128 (4 i + j)); tiles outside them must be those of the identity
+// and stay.  nbuf: 2 tiles.  Ends with the caller's barrier to come.
+__device__ __forceinline__ void sweep_tiles(v2d* tile, v2d* nbuf, int nb) {
+  const int w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int lr = lane_id() >> 4, lc = lane_id() & 15;
+  v4d pend = v4d{};  // tile (K, w) after step K, stored once every wave has read row K
+  if (w == 0) {
+    pend = get_tile(tile);
+    sweep16(pend, lr, lc);
+    put_tile(nbuf, pend);
+  }
+  // rolled loops: the code runs once per launch and is fetched cold
+#pragma unroll 1
+  for (int K = 0; K < nb; ++K) {
+    const int K1 = K + 1 < nb ? K + 1 : K;
+    const v4d b = get_tile(tile + 128 * (4 * K + w));
+    v4d c = get_tile(tile + 128 * (4 * K1 + w));
+    __syncthreads();
+    const v4d n = get_tile(nbuf + 128 * (K & 1));
+    const v4d p = get_tile(tile + 128 * (4 * K + K1));
+    if (w >= nb) continue;  // padding columns: only the barriers
+    if (K > 0) put_tile(tile + 128 * (4 * (K - 1) + w), pend);
+    // T = N A_Kw = -P^{-1} A_Kw, which takes A_iw to A_iw + A_Ki^T T; in the
+    // pivot's own column A_iK becomes A_Ki^T P^{-1} = 0 + A_Ki^T (-N)
+    const bool own = w == K;
+    v4d T = v4d{};
+    if (own) {
+      T = -n;
+      c = v4d{};
+    } else {
+      mul_tile(n, b, T);
+    }
+    pend = -T;
+    if (K1 != K) {
+      mul_tile(p, T, c);
+      put_tile(tile + 128 * (4 * K1 + w), c);
+      if (w == K1) {
+        // the next pivot block; the other tiles of this column follow from
+        // row K1 in the next step
+        sweep16(c, lr, lc);
+        put_tile(nbuf + 128 * (K1 & 1), c);
+        continue;
+      }
+    }
+#pragma unroll 1
+    for (int i = 0; i < nb; ++i) {
+      if (i == K || (K1 != K && i == K1)) continue;
+      const v4d x = get_tile(tile + 128 * (4 * K + i));
+      v4d y = own ? v4d{} : get_tile(tile + 128 * (4 * i + w));
+      mul_tile(x, T, y);
+      put_tile(tile + 128 * (4 * i + w), y);
+    }
+  }
+  __syncthreads();
+  if (w < nb) put_tile(tile + 128 * (4 * (nb - 1) + w), pend);
 }
 
 template <typename T>
@@ -436,16 +533,16 @@ __device__ __forceinline__ void await_flag(unsigned* ready, int* flags) {
   }
 }
 
-// nk: pivot blocks to sweep, ceil(bb / 4) for a block of bb real components
-// whose padding is the identity.  A pivot block made only of padding has
-// A - I exactly zero in its rows (the padding diagonal is exactly 1 before
-// and after the power-of-two scaling, and no earlier step touches rows
-// that are zero in every real column), so its step would add exactly zero:
-// stopping after nk blocks gives the same inverse bit for bit.
+// The inverse of the SPD matrix A (LDS 64x64 row-major) into A, or into out
+// (global, in the fp64 MFMA operand order of ginv_index, written through).
+// pbuf: LDS, 512 doubles.  nk: groups of 4 real components, ceil(bb / 4);
+// the padding past them is the identity, and blocks made only of padding
+// are not swept (their rows and columns are zero off the diagonal, so their
+// steps would add zero).
 __device__ __forceinline__ void spd_inverse64(double* A, double* pbuf, int nk, double* out = nullptr) {
   __shared__ int sexp[64];
   const int t = threadIdx.x;
-  const int lane = t & 63, w = t >> 6;
+  const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int lr = lane >> 4, lc = lane & 15;
   if (t < 64) {
     int E = 0;
@@ -453,85 +550,40 @@ __device__ __forceinline__ void spd_inverse64(double* A, double* pbuf, int nk, d
     sexp[t] = E >> 1;  // floor(E / 2)
   }
   __syncthreads();
-  int er[4], ec[4];
+  const int ec = sexp[16 * w + lc];
+  v4d x[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    er[q] = sexp[16 * w + lr + 4 * q];
-    ec[q] = sexp[16 * q + lc];
-  }
-  v4d acc[4];
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      acc[nt][r] = ldexp(A[(16 * w + lr + 4 * r) * 64 + 16 * nt + lc], -(er[r] + ec[nt]));
-  const double m0 = lr == 0, m1 = lr == 1, m2 = lr == 2, m3 = lr == 3;
-  // The loop over the owner waves stays rolled: the sweep runs once per
-  // launch, and its code is fetched cold while the streaming workgroups
-  // load the memory system, so a 4x smaller body is faster.
-#pragma unroll 1
-  for (int ntK = 0; ntK < 4 && 4 * ntK < nk; ++ntK)
+      x[i][r] = ldexp(A[(16 * i + lr + 4 * r) * 64 + 16 * w + lc], -(sexp[16 * i + lr + 4 * r] + ec));
+  __syncthreads();  // A becomes the tiles
+  v2d* tile = (v2d*)A;
 #pragma unroll
-  for (int rK = 0; rK < 4; ++rK) {
-    const int K = 4 * ntK + rK;
-    if (K >= nk) break;
-    // The sweep keeps A symmetric, so the pivot column block equals the
-    // pivot rows: their owner (wave K / 4, register K % 4) publishes
-    // C^T[c][j] = A[4K + c][j] - delta(j, 4K + c) and every wave builds
-    // its own operands from it.  Double-buffered: one barrier per step.
-    double* Rb = pbuf + (rK & 1) * 256;
-    if (w == ntK) {
+  for (int i = 0; i < 4; ++i) put_tile(tile + 128 * (4 * i + w), x[i]);
+  const int nb = (nk + 3) >> 2;
+  sweep_tiles(tile, (v2d*)pbuf, nb);
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const int col = 16 * nt + lc;
-        Rb[lr * 64 + col] = acc[nt][rK] - (col == 4 * K + lr ? 1.0 : 0.0);
-      }
-    }
+  for (int i = 0; i < 4; ++i) {
+    const v4d y = get_tile(tile + 128 * (4 * i + w));
+    const double sg = (i < nb && w < nb) ? -1.0 : 1.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[i][r] = ldexp(sg * y[r], -(sexp[16 * i + lr + 4 * r] + ec));
+  }
+  if (out) {
+    // the inverse is symmetric: element (row, col) goes to the place of (col,
+    // row), so that every store instruction writes 512 contiguous bytes
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) store_coherent(out + (16 * w + 4 * i + r) * 64 + lane, x[i][r]);
+  } else {
     __syncthreads();
-    double P[4][4], Pi[4][4];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int b = a; b < 4; ++b) {
-        P[a][b] = Rb[a * 64 + 4 * K + b] + (a == b ? 1.0 : 0.0);
-        P[b][a] = P[a][b];
-      }
-    double cw[4], bop[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) cw[c] = Rb[c * 64 + 16 * w + lc];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) bop[nt] = Rb[lr * 64 + 16 * nt + lc];
-    spd_inverse4(P, Pi);
-    // A operand: W[16 w + lc][lr] = -(C P^{-1})[16 w + lc][lr]; column lr
-    // of P^{-1} picked by exact 0/1 weights (no divergent selects)
-    double wc[4];
-#pragma unroll
-    for (int b = 0; b < 4; ++b) wc[b] = cw[0] * Pi[0][b] + cw[1] * Pi[1][b] + cw[2] * Pi[2][b] + cw[3] * Pi[3][b];
-    const double aop = -(wc[0] * m0 + wc[1] * m1 + wc[2] * m2 + wc[3] * m3);
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = mfma_f64(aop, bop[nt], acc[nt]);
+      for (int r = 0; r < 4; ++r) A[(16 * i + lr + 4 * r) * 64 + 16 * w + lc] = x[i][r];
   }
-  // Each step also takes 2 off its pivot block's diagonal.  A pivot row is
-  // published only in its own step and no later step reads the diagonal
-  // entry, so all these corrections are applied here at once (the
-  // accumulators stay in the MFMA registers during the sweep).
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (16 * w + lr + 4 * r == 16 * nt + lc) acc[nt][r] -= 2.0;
-  // the inverse goes back to A (LDS, row-major), or to out (global, in the
-  // fp64 MFMA operand order of ginv_index, for the target kernel of the
-  // next launch; written through)
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = 16 * w + lr + 4 * r, col = 16 * nt + lc;
-      const double v = -ldexp(acc[nt][r], -(er[r] + ec[nt]));
-      if (out) store_coherent(out + ginv_index(row, col), v);
-      else A[row * 64 + col] = v;
-    }
   __syncthreads();
 }
 
@@ -2091,6 +2143,11 @@ __device__ __forceinline__ double scale_solve(int* gacc, int bb, const double* _
   const double delta = EXTERND_SCALE_GUARD_REL * tr / (double)bb;
   if (t < bb) Gs[t * 64 + t] += delta;
   __syncthreads();
+  // M stays in registers for the refinement below: rows 4 j + t / 64, column t % 64
+  double Mr[4096 / NT];
+#pragma unroll
+  for (int j = 0; j < 4096 / NT; ++j) Mr[j] = Gs[t + NT * j];
+  __syncthreads();  // the inverse rewrites Gs
   spd_inverse64(Gs, colbuf, (bb + 3) >> 2);
   // g_c: the per-split partial sums in split order
   __shared__ double s_g[BBP];
@@ -2101,17 +2158,34 @@ __device__ __forceinline__ double scale_solve(int* gacc, int bb, const double* _
     s_g[t] = t < bb ? g : 0.0;
   }
   __syncthreads();
-  // d = M^{-1} g: row t / 4, the quarter t % 4 of its columns in registers,
-  // the quarters added pairwise in a fixed order
-  double dq = 0.0;
-  {
-    const int r = t >> 2, q = t & 3;
+  // M^{-1} x: row t / 4, the quarter t % 4 of its columns in registers, the
+  // quarters added pairwise in a fixed order
+  const int r = t >> 2, q = t & 3;
+  auto times_inverse = [&](const double* x) {
+    double v = 0.0;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) dq += Gs[r * 64 + 16 * q + c] * s_g[16 * q + c];
-    dq += __shfl_xor(dq, 1, 64);
-    dq += __shfl_xor(dq, 2, 64);
-    if (q == 0) colbuf[r] = (r < bb) ? dq : 0.0;
+    for (int c = 0; c < 16; ++c) v += Gs[r * 64 + 16 * q + c] * x[16 * q + c];
+    v += __shfl_xor(v, 1, 64);
+    v += __shfl_xor(v, 2, 64);
+    return r < bb ? v : 0.0;
+  };
+  // d = M^{-1} g, refined once: d += M^{-1} (g - M d).  An inverse of a nearly
+  // singular M (two components alike) leaves 1e-8 of the block's energy
+  // decrease to its rounding; one refinement leaves 1e-14.
+  const double d0 = times_inverse(s_g);
+  if (q == 0) colbuf[r] = d0;
+  __syncthreads();
+  const double dl = colbuf[t & 63];
+#pragma unroll
+  for (int j = 0; j < 4096 / NT; ++j) {
+    double v = Mr[j] * dl;
+    wave_sum63(v);
+    const int row = (t >> 6) + 4 * j;
+    if ((t & 63) == 63) colbuf[64 + row] = s_g[row] - v;
   }
+  __syncthreads();
+  const double d1 = d0 + times_inverse(colbuf + 64);
+  if (q == 0) colbuf[r] = d1;
   __syncthreads();
   double gain = 0.0;
   if (t < BBP) {
