@@ -22,14 +22,58 @@ static inline int clampi(int64_t v, int64_t lo, int64_t hi) { return (int)(v < l
 struct Layout {
   int64_t m_pad, n_pad;
   int gv, gd, nblk_cap;
-  int urows, ntu, nsu, nsv;
+  int urows, ntr, gu, urows_wide, nsu, nsv;
   size_t off[48];
   size_t total;
 };
 
+// Streaming workgroups of a contraction launch: USTEP_SLOTS less the side
+// workgroups and the slots left empty beside them.
+static const int64_t USTEP_FREE = USTEP_SLOTS - 2 * NSIDE_MAX;
+
+// Capacity for the U-step's row tiles: those of one column group.
+static int64_t ntmax_rows(int64_t m_pad) {
+  const int64_t rows = clampi((m_pad + USTEP_FREE - 1) / USTEP_FREE, 1, TILE);
+  return (m_pad + rows - 1) / rows + NSIDE_MAX;
+}
 static int64_t stat_tiles(int64_t nrt, int64_t nct, int64_t ntu) {
   const int64_t a = nrt > 2 * nct ? nrt : 2 * nct;
   return a > ntu ? a : ntu;
+}
+
+// U-step: equal row tiles of at most 32 rows x gu column groups, together as
+// many as fit in one pass of the resident workgroups, so that every CU
+// streams the same share of R.  A wave takes ~0.55 us per K step whatever the
+// rows below 20 (conversion and MFMAs run on the whole 32-row tile), then
+// grows with them (memory); a split adds ~3 us (partials, arrival, sum).
+// Without it, few rows meant tiles of few rows and the work of 32: 2560 x
+// 9728 weighted ran 427 tiles of 6 rows in 64.7 us a step, with 80 tiles of
+// 32 rows x 6 groups in 29.3 us; 2048 x 2048 (5 rows) 20.5 -> 17.1; at 9728 x
+// 2560 (21 rows) there is nothing to split.  The partials take the place of
+// the V-step's (2048 entries per tile and group), their row maxima
+// that of the staging's (32 per tile and group).
+static void ustep_split(int64_t m_pad, int64_t n_pad, int gv, int* urows, int* ntr, int* gu) {
+  const int64_t nks = n_pad / TILE;
+  int64_t best = -1;
+  for (int g = 1; g <= GU_MAX && g <= nks; ++g) {
+    const int64_t tiles = USTEP_FREE / g;
+    int64_t rows = (m_pad + tiles - 1) / tiles;
+    if (rows > TILE) {
+      if (g > 1) break;
+      rows = TILE;  // more tiles than slots: several passes
+    }
+    if (g > 1 && rows < 16) rows = 16;  // fewer rows would not be faster
+    const int64_t nt = (m_pad + rows - 1) / rows;
+    if (g > 1 && (nt * g * 8 > gv * n_pad || nt * g * TILE > nks * m_pad)) break;
+    const int64_t rounds = ((nks + g - 1) / g + 3) / 4;
+    const int64_t cost = rounds * (rows > 20 ? rows : 20) + (g > 1 ? 110 : 0);
+    if (best < 0 || cost < best) {
+      best = cost;
+      *urows = (int)rows;
+      *ntr = (int)nt;
+      *gu = g;
+    }
+  }
 }
 
 static Layout make_layout(int64_t m, int64_t n, int64_t k) {
@@ -43,19 +87,14 @@ static Layout make_layout(int64_t m, int64_t n, int64_t k) {
   // the residual while the others idle).
   L.gv = clampi((480 + nct - 1) / nct, 1, nrt < GV_MAX ? nrt : GV_MAX);
   L.gd = clampi(DEFLATE_SLOTS / nct, 1, nrt < 64 ? nrt : 64);
-  // U-step: equal row groups of at most 32 rows, as many as fit beside the
-  // side workgroups in one pass of USTEP_SLOTS resident workgroups, so
-  // that every CU streams the same share of R.  NSIDE_MAX more slots stay
-  // empty: those that the dispatcher places beside the side workgroups
-  // (ntu counts them; the launch maps them out).
-  L.urows = clampi((L.m_pad + (USTEP_SLOTS - 2 * NSIDE_MAX) - 1) / (USTEP_SLOTS - 2 * NSIDE_MAX), 1, TILE);
-  L.ntu = (int)((L.m_pad + L.urows - 1) / L.urows) + NSIDE_MAX;
+  ustep_split(L.m_pad, L.n_pad, L.gv, &L.urows, &L.ntr, &L.gu);
+  L.urows_wide = clampi((L.m_pad + USTEP_FREE - 1) / USTEP_FREE, 1, TILE);
   L.nsu = clampi((L.m_pad + TERN_CHUNK - 1) / TERN_CHUNK, 1, TERN_SPLIT_MAX);
   L.nsv = clampi((L.n_pad + TERN_CHUNK - 1) / TERN_CHUNK, 1, TERN_SPLIT_MAX);
   L.nblk_cap = (int)(k + 2);  // fro2 before every block and after the last; one spare
   // statistics tiles: 32-row tiles (initial gather, wide U-steps) or the
   // U-step's row groups on the U side, 16-column tiles on the V side
-  const int64_t ntmax = stat_tiles(nrt, nct, L.ntu);
+  const int64_t ntmax = stat_tiles(nrt, nct, ntmax_rows(L.m_pad));
   const size_t sizes[] = {
       sizeof(float) * (size_t)(L.m_pad * L.n_pad),     // 0 R
       (size_t)(BMAX * L.m_pad),                        // 1 Ut
@@ -127,7 +166,9 @@ bool carve(Ws& w, void* base, size_t bytes, int64_t m, int64_t n, int64_t k) {
   w.gv = L.gv;
   w.gd = L.gd;
   w.urows = L.urows;
-  w.ntu = L.ntu;
+  w.ntr = L.ntr;
+  w.gu = L.gu;
+  w.urows_wide = L.urows_wide;
   w.nsu = L.nsu;
   w.nsv = L.nsv;
   w.R = (float*)(b + L.off[0]);
@@ -142,7 +183,11 @@ bool carve(Ws& w, void* base, size_t bytes, int64_t m, int64_t n, int64_t k) {
   w.ginvU = (double*)(b + L.off[9]);
   w.ginvV = (double*)(b + L.off[10]);
   w.gramV = (double*)(b + L.off[11]);
+  // the partial Grams take the first NSIDE_INT of the buffer's NSIDE_MAX matrices
+  static_assert((NSIDE_MAX - NSIDE_INT) * 4096 >= USTEP_SLOTS + 2 * FLAG_COPIES * FLAG_STRIDE, "room for counters and flags");
   w.gparti = (int*)(b + L.off[13]);
+  w.utcnt = (unsigned*)(w.gparti + NSIDE_INT * 4096);
+  w.gflag = w.utcnt + USTEP_SLOTS;
   w.colE_part = (double*)(b + L.off[14]);
   w.hw = (double*)(b + L.off[15]);
   w.gvec = (double*)(b + L.off[16]);
@@ -177,7 +222,7 @@ bool carve(Ws& w, void* base, size_t bytes, int64_t m, int64_t n, int64_t k) {
   w.wflag = (int*)(b + L.off[45]);
   w.vtcnt = (unsigned*)(b + L.off[44]);
   const int64_t nrt = L.m_pad / TILE, nct = L.n_pad / TILE;
-  w.ntmax = stat_tiles(nrt, nct, L.ntu);
+  w.ntmax = stat_tiles(nrt, nct, ntmax_rows(L.m_pad));
   return true;
 }
 

@@ -30,11 +30,15 @@ constexpr int NSIDE_INT = 8;   // integer-Gram workgroups of the scale solve
 constexpr int NSIDE_GRAM = 16; // workgroups of the integer Gram launch
 constexpr int NSIDE_MAX = 16;
 constexpr int GV_MAX = 8;      // row groups of the V-step contraction
+constexpr int GU_MAX = 8;      // column groups of the U-step contraction
 // Workgroups of the contraction kernels resident at once: two per CU on
 // 256 CUs (LDS and register budgets of k_vstep / k_ustep).
 constexpr int USTEP_SLOTS = 512;
 // The same for the deflation kernel (240 VGPRs: two workgroups per CU).
 constexpr int DEFLATE_SLOTS = 512;
+// Copies of an in-launch flag, each on a line of its own (words apart).
+constexpr int FLAG_COPIES = 16;
+constexpr int FLAG_STRIDE = 32;
 // Threads per workgroup for all kernels except the selection kernel.
 constexpr int NT = 256;
 // Weighted Grams on int8 MFMA: the weights h~_j / max h~ as integers of at
@@ -55,14 +59,10 @@ constexpr int TERN_CHUNK = 640;
 // CNT_SAFEGUARD: blocks replaced by the single-entry step; CNT_SG_*: the
 // last block's single-entry decision (fired, row, column, negative sign);
 // CNT_SEQ_USED: components extracted by the persistent sequential path.
-// CNT_GINV_V: set to 1 by the U-step's side path once G_V^{-1} is stored
-// (the row groups of the same launch wait for it); cleared by k_tern_u.
-// CNT_GINV_U: the same for the V-step's G_U^{-1}; cleared by k_tern_v.
 enum Counter {
   CNT_GRAM_U = 0, CNT_GRAM_V = 1, CNT_SCALE = 2,
   CNT_DECISION = 5, CNT_ACCEPTED = 6, CNT_SAFEGUARD = 7,
-  CNT_SG_FIRE = 8, CNT_SG_ROW = 9, CNT_SG_COL = 10, CNT_SG_NEG = 11, CNT_SEQ_USED = 12, CNT_GINV_V = 13,
-  CNT_GINV_U = 14, CNT_COUNT = 16
+  CNT_SG_FIRE = 8, CNT_SG_ROW = 9, CNT_SG_COL = 10, CNT_SG_NEG = 11, CNT_SEQ_USED = 12, CNT_COUNT = 16
 };
 // Flags written by the device, read by the host.
 enum Flag { FLAG_NONFINITE = 0, FLAG_BADWEIGHT = 1, FLAG_SYNC = 2, FLAG_COUNT = 4 };
@@ -73,7 +73,8 @@ struct Ws {
   int nblk_cap;          // capacity of the per-block arrays (k + 2)
   int gv;                // row groups of the V-step contraction
   int gd;                // row groups of the deflation / staging passes
-  int urows, ntu;        // U-step: rows per workgroup (<= 32) and number of row groups
+  int urows, ntr, gu;    // U-step: rows per workgroup (<= 32), row tiles, column groups per row tile
+  int urows_wide;        // U-step of wide blocks: rows per workgroup (<= 32)
   int nsu, nsv;          // ternarization workgroups per U / V component
   int64_t ntmax;         // statistics tiles per component (the larger of the U and V sides)
 
@@ -96,7 +97,10 @@ struct Ws {
   double* ginvU;         // BBP x BBP
   double* ginvV;         // BBP x BBP
   double* gramV;         // BBP x BBP raw V^T H V (no ridge)
-  int* gparti;           // NSIDE_MAX x BBP x BBP partial integer Grams
+  int* gparti;           // NSIDE_INT x BBP x BBP partial integer Grams (scale step entry point)
+  unsigned* utcnt;       // USTEP_SLOTS arrival counters of the U-step's row tiles (zero between launches)
+  unsigned* gflag;       // 2 x FLAG_COPIES flags, FLAG_STRIDE apart: set by the V-step's (then the U-step's)
+                         // side path once its inverse Gram is stored, cleared by k_tern_v (k_tern_u)
   double* colE_part;     // gd x n_pad partial column energies
   double* hw;            // n_pad: h~ (fp64), 1 when unweighted
   double* gvec;          // BBP x TERN_SPLIT_MAX: diag(U^T Q) in per-split partial sums

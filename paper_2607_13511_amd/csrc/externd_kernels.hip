@@ -515,14 +515,18 @@ __device__ __forceinline__ void load_ginv(const double* ginv, double (&a)[16]) {
 // polls it with coherent loads for at most SYNC_TICKS of the 100 MHz wall
 // clock (20 ms, against a few microseconds expected); past that it raises
 // FLAG_SYNC, which the host reports as EXTERND_ESYNC, and goes on.
+// The flag is kept in FLAG_COPIES copies on lines of their own, and workgroup
+// b polls copy b % FLAG_COPIES: hundreds of workgroups asking for one line
+// delay its store.
 constexpr unsigned long long SYNC_TICKS = 2000000ull;
 __device__ __forceinline__ void ginv_ready(unsigned* ready) {
   if (!ready) return;
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (threadIdx.x == 0) store_coherent(ready, 1u);
+  if (threadIdx.x < FLAG_COPIES) store_coherent(ready + FLAG_STRIDE * threadIdx.x, 1u);
 }
 __device__ __forceinline__ void await_flag(unsigned* ready, int* flags) {
+  ready += FLAG_STRIDE * (blockIdx.x % FLAG_COPIES);
   const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
   while (load_coherent(ready) == 0u) {
     if (__builtin_amdgcn_s_memrealtime() - t0 > SYNC_TICKS) {
@@ -1247,12 +1251,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // grid: nside side WGs (V^T V on int8 MFMA over K slices, weighted
 //       V^T diag(H) V from the weights' digit planes; the last of them adds
 //       the ridge and inverts; the raw Gram is kept for the scale solve)
-//       followed by ntile row groups of `rows` <= 32 rows, sized so
-//       that the whole grid is resident at two workgroups per CU and every
-//       CU streams the same share of R; each row group stores Q, waits for
-//       G_V^{-1} and writes its Z rows and T_tau statistics.
-// Each WG owns `rows` full rows (one 32-row MFMA tile; rows past `rows`
-// are neither loaded nor stored); its 4 waves interleave 32-column K steps.
+//       followed by ntr row tiles of `rows` <= 32 rows x gu column groups,
+//       sized so that the whole grid is resident at two workgroups per CU
+//       and every CU streams the same share of R (ustep_split); each row
+//       tile stores Q, waits for G_V^{-1} and writes its Z rows and T_tau
+//       statistics.
+// Each WG owns `rows` rows (one 32-row MFMA tile; rows past `rows` are
+// neither loaded nor stored) and, with gu > 1, one of gu ranges of the K
+// steps: the groups' exact int64 partials (Qp) and row maxima (mx) go out
+// written through, and the last of a tile's groups to arrive (utcnt) sums
+// them and goes on alone (SPLIT: gu > 1).  Its 4 waves interleave 32-column
+// K steps.
 // A = R digit planes (rows x columns), B = V (MFMA-ready layout).  Each
 // wave streams its 32 x 32 residual tiles into LDS with direct loads
 // (8 lanes per 128-byte row segment, 16-byte chunks XOR-swizzled by row)
@@ -1266,7 +1275,7 @@ constexpr int USTAGE_B = 4096 + 256;  // bytes per staged K step: tile + weights
 // 64 KB wave reduction reuses afterwards
 constexpr int USTEP_SMEM_LL = (4 * NST_U * USTAGE_B + 7) / 8 > 8192 ? (4 * NST_U * USTAGE_B + 7) / 8 : 8192;
 
-template <bool WEIGHTED>
+template <bool WEIGHTED, bool SPLIT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_ustep(const float* __restrict__ R, const v4i* __restrict__ Vmf,
                                               const int8_t* __restrict__ Vr, const double* __restrict__ hw,
                                               double* __restrict__ Q, float* __restrict__ rowb,
@@ -1275,7 +1284,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
                                               const int8_t* __restrict__ Wmf, long long* gacc64,
                                               const double* __restrict__ hwmax, double* __restrict__ Z, double* ps,
                                               double* pm, int* pi, int64_t m, unsigned* ready, int* flags,
-                                              int storeQ) {
+                                              int storeQ, int ntr, int gu, long long* Qp, int* mx, unsigned* utcnt) {
   // side path: ired 16 KB | G 32 KB | inverse scratch 8 KB; contraction:
   // 4 waves x NST_U staged K steps (52 KB), then the 64 KB wave reduction
   __shared__ __attribute__((aligned(16))) long long smem[USTEP_SMEM_LL];
@@ -1311,11 +1320,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   // grid) are left empty so that the inverse sweep has its CU to itself,
   // and the row groups after them shift down.  Were the placement
   // different, those slots would only cost their share of the stream.
-  const int rt0 = blockIdx.x - nside;
-  if (nside && rt0 >= 256 - nside && rt0 < 256) return;
-  const int rt = (nside && rt0 >= 256) ? rt0 - nside : rt0;
+  const int b0 = blockIdx.x - nside;
+  if (nside && b0 >= 256 - nside && b0 < 256) return;
+  const int b = (nside && b0 >= 256) ? b0 - nside : b0;
+  if (b >= (SPLIT ? ntr * gu : ntr)) return;  // the slots counted for the empty ones
+  const int rt = SPLIT ? b % ntr : b, cg = SPLIT ? b / ntr : 0;
   const int64_t i0 = (int64_t)rt * rows;
-  if (i0 >= m_pad) return;  // the slots counted for the empty ones, past the last row group
   const int valid = (int)(m_pad - i0 < rows ? m_pad - i0 : rows);
   const int lane = lane_id(), wave = wave_id();
   const int h = lane >> 5, l32 = lane & 31;
@@ -1335,6 +1345,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
     for (int p = 0; p < 4; ++p) acc[t][p] = v16i{};
   const int nks = (int)(n_pad / TILE);
+  const int ks0 = SPLIT ? (int)((long long)cg * nks / gu) : 0;
+  const int ks1 = SPLIT ? (int)((long long)(cg + 1) * nks / gu) : nks;
   char* wst = (char*)smem + wave * (NST_U * USTAGE_B);
   // loader mapping: lane -> row 8 q + lane / 8, 16-byte chunk lane % 8,
   // stored at chunk position (lane % 8) ^ (row % 8); rows >= valid are
@@ -1349,7 +1361,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   const float* Rld = R + (i0 + lrow) * n_pad + (((lane & 7) ^ lrow) * 4);
   constexpr int NLD = WEIGHTED ? 5 : 4;  // direct loads per staged K step
   v4i bn[NST_U][2];
-  // stage st <- K step kk (< nks); nothing is loaded past the last K step
+  // stage st <- K step kk (< ks1); nothing is loaded past the last K step
   auto issue = [&](int kk, int st) {
     char* dst = wst + st * USTAGE_B;
 #pragma unroll
@@ -1371,11 +1383,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   __builtin_amdgcn_global_load_lds(rowb + i0 + (l32 < valid ? l32 : valid - 1), (lds_void*)&s_rbw[wave][0], 4, 0, 0);
 #pragma unroll
   for (int d = 0; d < NST_U - 1; ++d)
-    if (wave + 4 * d < nks) issue(wave + 4 * d, d);
-  // with both first stages issued (nks >= 8) at least 2 x 3 loads follow
+    if (ks0 + wave + 4 * d < ks1) issue(ks0 + wave + 4 * d, d);
+  // with both first stages issued (8 K steps or more) at least 2 x 3 loads follow
   // the bound's (one direct residual load and two factor loads per stage)
   const unsigned rba = lds_addr(&s_rbw[wave][lane]);
-  const float rbound = nks >= 4 * (NST_U - 1) ? lds_read1_after<2 * 3>(rba) : lds_read1_after<0>(rba);
+  const float rbound = ks1 - ks0 >= 4 * (NST_U - 1) ? lds_read1_after<2 * 3>(rba) : lds_read1_after<0>(rba);
   const int s = fx_shift(rbound);
   const float p2s = __builtin_amdgcn_ldexpf(1.0f, s);  // x 2^s = x * p2s exactly
   const double cw = weighted_round_const(s);
@@ -1384,17 +1396,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   const unsigned o0 = l32 * 128 + ((4 * h + 0) ^ sw) * 16, o1 = l32 * 128 + ((4 * h + 1) ^ sw) * 16;
   const unsigned o2 = l32 * 128 + ((4 * h + 2) ^ sw) * 16, o3 = l32 * 128 + ((4 * h + 3) ^ sw) * 16;
   const unsigned wbase = lds_addr(wst);
-  for (int ks = wave; ks < nks; ks += 4 * NST_U) {
+  for (int ks = ks0 + wave; ks < ks1; ks += 4 * NST_U) {
 #pragma unroll
     for (int u = 0; u < NST_U; ++u) {
       const int kk = ks + 4 * u, kn = kk + 4 * (NST_U - 1);
-      if (kn < nks) issue(kn, (u + NST_U - 1) % NST_U);
-      if (kk < nks) {
+      if (kn < ks1) issue(kn, (u + NST_U - 1) % NST_U);
+      if (kk < ks1) {
         const unsigned b = wbase + u * USTAGE_B;
         v4f x[4];
         // with the following stages issued, at least NLD * (NST_U - 1)
         // loads follow this stage's; near the end the wait drains
-        if (kn < nks) lds_read4_after<NLD * (NST_U - 1)>(b + o0, b + o1, b + o2, b + o3, x[0], x[1], x[2], x[3]);
+        if (kn < ks1) lds_read4_after<NLD * (NST_U - 1)>(b + o0, b + o1, b + o2, b + o3, x[0], x[1], x[2], x[3]);
         else lds_read4_after<0>(b + o0, b + o1, b + o2, b + o3, x[0], x[1], x[2], x[3]);
         unsigned y[16];
         if (WEIGHTED) {
@@ -1439,22 +1451,78 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   // every direct load has landed before the staging area is reused
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
+  int rm = 0;  // thread i < valid: the largest of row i in this workgroup
   if (threadIdx.x < valid) {
     const int i = threadIdx.x;
-    int r = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) r = max(r, max(s_rmax[q][i], s_rmax[q][i + 32]));
-    rowb[i0 + i] = WEIGHTED ? __int2float_ru(r + 1) * __builtin_amdgcn_ldexpf(1.0f, -s_row[i]) : __int_as_float(r);
+    for (int q = 0; q < 4; ++q) rm = max(rm, max(s_rmax[q][i], s_rmax[q][i + 32]));
   }
-  // out[t][M = row][N = component] -> Q[32 t + N][row], via a transposed
-  // LDS tile for coalesced stores
+  // out[t][M = row][N = component] -> entry (32 t + N, row) of a transposed
+  // LDS tile, rows permuted by the component: the 32 lanes of a store (32
+  // components, one row) then fall into different banks
+  auto tqi = [](int c, int M) { return c * 32 + (M ^ (c & 31)); };
   double* tq = (double*)smem;
-  reduce_waves(smem, acc, nks <= FOLD_KMAX,
-               [&](int t, int M, int N, long long v) { tq[(32 * t + N) * 32 + M] = ldexp((double)v, -s_row[M]); });
+  const bool fold = ks1 - ks0 <= FOLD_KMAX;
+  if (!SPLIT) {
+    reduce_waves(smem, acc, fold,
+                 [&](int t, int M, int N, long long v) { tq[tqi(32 * t + N, M)] = ldexp((double)v, -s_row[M]); });
+  } else {
+    reduce_waves(smem, acc, fold, [&](int t, int M, int N, long long v) { smem[tqi(32 * t + N, M)] = v; });
+    __syncthreads();
+    long long* mine = Qp + (int64_t)(rt * gu + cg) * 2048;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int e = threadIdx.x + NT * k;
+      store_coherent(mine + e, smem[tqi(e >> 5, e & 31)]);
+    }
+    if (threadIdx.x < TILE) store_coherent(mx + (int64_t)(rt * gu + cg) * TILE + threadIdx.x, rm);
+    __builtin_amdgcn_s_waitcnt(0);
+    __shared__ int s_last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const unsigned old = __hip_atomic_fetch_add(utcnt + rt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_last = old == (unsigned)(gu - 1);
+    }
+    __syncthreads();
+    if (!s_last) return;
+    if (threadIdx.x == 0) store_coherent(utcnt + rt, 0u);
+    // all partials in flight at once, as plain 16-byte loads from clamped
+    // groups (masked in the sum; see k_vstep for why plain loads see them)
+    const long long* all = Qp + (int64_t)rt * gu * 2048 + 2 * threadIdx.x;
+    int mv[GU_MAX];
+#pragma unroll
+    for (int g = 0; g < GU_MAX; ++g) mv[g] = mx[(int64_t)(rt * gu + (g < gu ? g : 0)) * TILE + (threadIdx.x & 31)];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      v2l v[2][GU_MAX];
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int g = 0; g < GU_MAX; ++g) v[k][g] = *(const v2l*)(all + (g < gu ? g : 0) * 2048 + 2 * NT * (2 * half + k));
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int e = 2 * (threadIdx.x + NT * (2 * half + k)), c = e >> 5, M = e & 31;
+        long long s0 = 0, s1 = 0;
+#pragma unroll
+        for (int g = 0; g < GU_MAX; ++g) {
+          s0 += g < gu ? v[k][g].x : 0ll;
+          s1 += g < gu ? v[k][g].y : 0ll;
+        }
+        tq[tqi(c, M)] = ldexp((double)s0, -s_row[M]);
+        tq[tqi(c, M + 1)] = ldexp((double)s1, -s_row[M + 1]);
+      }
+    }
+    rm = 0;
+#pragma unroll
+    for (int g = 0; g < GU_MAX; ++g) rm = max(rm, mv[g]);
+  }
+  if (threadIdx.x < valid)
+    rowb[i0 + threadIdx.x] = WEIGHTED ? __int2float_ru(rm + 1) * __builtin_amdgcn_ldexpf(1.0f, -s_row[threadIdx.x])
+                                      : __int_as_float(rm);
   __syncthreads();
   if (storeQ)
     for (int e = threadIdx.x; e < 2048; e += NT)
-      if ((e & 31) < valid) Q[(int64_t)(e >> 5) * m_pad + i0 + (e & 31)] = tq[e];
+      if ((e & 31) < valid) Q[(int64_t)(e >> 5) * m_pad + i0 + (e & 31)] = tq[tqi(e >> 5, e & 31)];
   if (!Z) return;
   // The target rows Z = Q G_V^{-1} of this row group (Eq. (3) second half)
   // and their T_tau statistics, once the side path has stored G_V^{-1}.
@@ -1467,8 +1535,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   // A = G^{-1}[16 w + li][4 ks + lk], B = Q^T[4 ks + lk][li (+16)] (LDS)
 #pragma unroll
   for (int ks = 0; ks < 16; ++ks) {
-    z[0] = mfma_f64(a[ks], tq[(4 * ks + lk) * 32 + li], z[0]);
-    z[1] = mfma_f64(a[ks], tq[(4 * ks + lk) * 32 + 16 + li], z[1]);
+    z[0] = mfma_f64(a[ks], tq[tqi(4 * ks + lk, li)], z[0]);
+    z[1] = mfma_f64(a[ks], tq[tqi(4 * ks + lk, 16 + li)], z[1]);
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -1477,7 +1545,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     if (16 + li < valid) row[16 + li] = z[1][r];
   }
   const int64_t iend = i0 + valid < m ? i0 + valid : m;
-  tile_stats(z, wave, i0, iend, (int)gridDim.x - 2 * nside, rt, ps, pm, pi);
+  tile_stats(z, wave, i0, iend, ntr, rt, ps, pm, pi);
 }
 
 // ---------------------------------------------------------------------------
@@ -1952,7 +2020,7 @@ __global__ __launch_bounds__(NT) void k_tern_v(const double* __restrict__ Y, int
   pm += q0 * ntmax;
   pi += q0 * ntmax;
   bb -= (int)q0;
-  if (ready && blockIdx.x == 0 && threadIdx.x == 0) *ready = 0u;  // the V-step's G_U^{-1} flag
+  if (ready && blockIdx.x == 0 && threadIdx.x < FLAG_COPIES) ready[FLAG_STRIDE * threadIdx.x] = 0u;  // the V-step's G_U^{-1} flag
   int64_t i0, i1;
   tern_range(n_pad, sp, ns, i0, i1);
   int8_t* dst = Vt + (int64_t)c * n_pad;
@@ -2000,7 +2068,7 @@ __global__ __launch_bounds__(NT) void k_tern_u(const double* __restrict__ Z, con
   pi += q0 * ntmax;
   gpart += q0 * TERN_SPLIT_MAX;
   bb -= (int)q0;
-  if (ready && blockIdx.x == 0 && threadIdx.x == 0) *ready = 0u;  // the U-step's G_V^{-1} flag
+  if (ready && blockIdx.x == 0 && threadIdx.x < FLAG_COPIES) ready[FLAG_STRIDE * threadIdx.x] = 0u;  // the U-step's G_V^{-1} flag
   int64_t i0, i1;
   tern_range(m_pad, sp, ns, i0, i1);
   int8_t* dst = Ut + (int64_t)c * m_pad;
@@ -2503,10 +2571,12 @@ __global__ __launch_bounds__(NT) void k_prep(const float* __restrict__ h, int64_
                                              double* fro2_hist, double* fro2w_hist, int nblk_cap,
                                              unsigned* counters, int* flags, int* gacc, double lam,
                                              unsigned long long* argkey, int* gaccW, long long* gacc64,
-                                             int8_t* __restrict__ hdig, unsigned* vtcnt) {
+                                             int8_t* __restrict__ hdig, unsigned* vtcnt, unsigned* utcnt, unsigned* gflag) {
   __shared__ float smax[NT / 64];
   __shared__ int sbad[NT / 64];
   for (int64_t e = threadIdx.x; e < n_pad / TILE; e += NT) vtcnt[e] = 0u;
+  for (int e = threadIdx.x; e < USTEP_SLOTS; e += NT) utcnt[e] = 0u;
+  for (int e = threadIdx.x; e < 2 * FLAG_COPIES * FLAG_STRIDE; e += NT) gflag[e] = 0u;
   for (int e = threadIdx.x; e < nblk_cap; e += NT) {
     fro2_hist[e] = 0.0;
     fro2w_hist[e] = 0.0;
@@ -3708,7 +3778,7 @@ static inline unsigned grid_for(int64_t total) {
 hipError_t launch_prep(const Ws& w, const float* h, hipStream_t s, double lam) {
   hipLaunchKernelGGL(k_prep, dim3(1), dim3(NT), 0, s, h, w.n, w.n_pad, w.hw, w.hwmax, w.fro2_hist,
                      w.fro2w_hist, w.nblk_cap, w.counters, w.flags, w.gacc, lam, w.argkey, w.gaccW, w.gacc64,
-                     w.hdig, w.vtcnt);
+                     w.hdig, w.vtcnt, w.utcnt, w.gflag);
   return hipGetLastError();
 }
 
@@ -3768,7 +3838,7 @@ hipError_t launch_init(const Ws& w, int bb, double tau, hipStream_t s) {
 hipError_t launch_vstep(const Ws& w, int blk, int bb, double tau, hipStream_t s, Timer* tm, bool weighted) {
   const int nsb = (int)((w.n_pad / TILE) * w.gv);  // streaming workgroups, plus the empty slots past 256
   const unsigned grid = (unsigned)(NSIDE_GRAM + nsb + (nsb > 256 - NSIDE_GRAM ? NSIDE_GRAM : 0));
-  unsigned* ready = w.counters + CNT_GINV_U;
+  unsigned* ready = w.gflag;
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_VSTEP, k_vstep, dim3(grid), dim3(NT), 0, s, w.R, (const v4i*)w.Umf, w.Pp, (const int*)w.cshift, w.m_pad,
                                    w.n_pad, w.gv, bb, w.gacc, w.counters + CNT_GRAM_U, w.ginvU, NSIDE_GRAM, w.Y,
                                    w.tps, w.tpm, w.tpi, w.n, w.vtcnt, ready, w.flags);
@@ -3788,28 +3858,28 @@ hipError_t launch_vstep(const Ws& w, int blk, int bb, double tau, hipStream_t s,
 hipError_t launch_ustep(const Ws& w, int blk, int bb, double tau, bool weighted, bool final, hipStream_t s,
                         Timer* tm, bool keep_q) {
   hipError_t e;
-  static_assert(NSIDE_GRAM == NSIDE_MAX, "the empty row-group slots match the side workgroups");
   const unsigned nside = NSIDE_GRAM;
-  const unsigned grid = (unsigned)(nside + w.ntu);
-  unsigned* ready = w.counters + CNT_GINV_V;
+  const unsigned nst = (unsigned)(w.ntr * w.gu);  // streaming workgroups, plus the empty slots past 256
+  const unsigned grid = nside + nst + (nst > 256 - nside ? nside : 0);
+  unsigned* ready = w.gflag + FLAG_COPIES * FLAG_STRIDE;
   const int storeQ = (final || keep_q) ? 1 : 0;
   if (weighted)
-    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (k_ustep<true>), dim3(grid), dim3(NT), 0, s, w.R, (const v4i*)w.Vmf, w.Vr, w.hw, w.Q,
+    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (w.gu > 1 ? k_ustep<true, true> : k_ustep<true, false>), dim3(grid), dim3(NT), 0, s, w.R, (const v4i*)w.Vmf, w.Vr, w.hw, w.Q,
                                      w.rowb, w.m_pad, w.n_pad, bb, w.gacc + 4096,
                                      w.counters + CNT_GRAM_V, w.ginvV, w.gramV, (int)nside, w.urows,
                                      (const int8_t*)w.Wmf, w.gacc64, (const double*)w.hwmax, w.Z, w.tps, w.tpm,
-                                     w.tpi, w.m, ready, w.flags, storeQ);
+                                     w.tpi, w.m, ready, w.flags, storeQ, w.ntr, w.gu, w.Pp, (int*)w.rowb_part, w.utcnt);
   else
-    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (k_ustep<false>), dim3(grid), dim3(NT), 0, s, w.R, (const v4i*)w.Vmf, w.Vr, w.hw, w.Q,
+    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (w.gu > 1 ? k_ustep<false, true> : k_ustep<false, false>), dim3(grid), dim3(NT), 0, s, w.R, (const v4i*)w.Vmf, w.Vr, w.hw, w.Q,
                                      w.rowb, w.m_pad, w.n_pad, bb, w.gacc + 4096,
                                      w.counters + CNT_GRAM_V, w.ginvV, w.gramV, (int)nside, w.urows,
                                      (const int8_t*)nullptr, (long long*)nullptr, (const double*)nullptr, w.Z,
-                                     w.tps, w.tpm, w.tpi, w.m, ready, w.flags, storeQ);
+                                     w.tps, w.tpm, w.tpi, w.m, ready, w.flags, storeQ, w.ntr, w.gu, w.Pp, (int*)w.rowb_part, w.utcnt);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_TERNU, k_tern_u, dim3(BBP * w.nsu), dim3(NT), 0, s, (const double*)w.Z,
                        final ? (const double*)w.Q : nullptr, w.m, w.m_pad, bb, tau, (const double*)w.tps,
-                       (const double*)w.tpm, (const int*)w.tpi, w.ntu - (int)NSIDE_MAX, w.nsu, w.Ut, w.Umf, w.gvec,
+                       (const double*)w.tpm, (const int*)w.tpi, w.ntr, w.nsu, w.Ut, w.Umf, w.gvec,
                        ready, w.ntmax);
   return hipGetLastError();
 }
@@ -3903,24 +3973,27 @@ hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weig
                              hipStream_t s, Timer* tm) {
   const int nq = nq_of(bb);
   hipError_t e;
-  const unsigned nrow = (unsigned)((w.m_pad + w.urows - 1) / w.urows);
+  const unsigned nrow = (unsigned)((w.m_pad + w.urows_wide - 1) / w.urows_wide);
+  const unsigned nst = (unsigned)(w.ntr * w.gu);
   int q0 = 0;
   if (first) {
     // The rows' bounds are those that the deflation raised.  Quarter 0's pass
     // measures them, and the other quarters convert at the measured bounds'
     // exponents (two to four bits finer after a wide block's deflation).
     if (weighted)
-      EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (k_ustep<true>), dim3(nrow), dim3(NT), 0, s, w.R,
+      EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (w.gu > 1 ? k_ustep<true, true> : k_ustep<true, false>), dim3(nst), dim3(NT), 0, s, w.R,
                            (const v4i*)w.Vmf, w.Vr, w.hw, w.Q, w.rowb, w.m_pad, w.n_pad, BBP, w.gacc + 4096,
                            w.counters + CNT_GRAM_V, w.ginvV, w.gramV, 0, w.urows, (const int8_t*)nullptr,
                            (long long*)nullptr, (const double*)nullptr, (double*)nullptr, (double*)nullptr,
-                           (double*)nullptr, (int*)nullptr, w.m, (unsigned*)nullptr, (int*)nullptr, 1);
+                           (double*)nullptr, (int*)nullptr, w.m, (unsigned*)nullptr, (int*)nullptr, 1, w.ntr, w.gu, w.Pp,
+                           (int*)w.rowb_part, w.utcnt);
     else
-      EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (k_ustep<false>), dim3(nrow), dim3(NT), 0, s, w.R,
+      EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, (w.gu > 1 ? k_ustep<false, true> : k_ustep<false, false>), dim3(nst), dim3(NT), 0, s, w.R,
                            (const v4i*)w.Vmf, w.Vr, w.hw, w.Q, w.rowb, w.m_pad, w.n_pad, BBP, w.gacc + 4096,
                            w.counters + CNT_GRAM_V, w.ginvV, w.gramV, 0, w.urows, (const int8_t*)nullptr,
                            (long long*)nullptr, (const double*)nullptr, (double*)nullptr, (double*)nullptr,
-                           (double*)nullptr, (int*)nullptr, w.m, (unsigned*)nullptr, (int*)nullptr, 1);
+                           (double*)nullptr, (int*)nullptr, w.m, (unsigned*)nullptr, (int*)nullptr, 1, w.ntr, w.gu, w.Pp,
+                           (int*)w.rowb_part, w.utcnt);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     q0 = 1;
@@ -3929,10 +4002,10 @@ hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weig
   double* Qq = w.Q + (int64_t)BBP * q0 * w.m_pad;
   if (weighted)
     EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, k_ustep_wide<true>, dim3(nrow), dim3(NT), 0, s, w.R, Vq,
-                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows, nq - q0);
+                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows_wide, nq - q0);
   else
     EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, k_ustep_wide<false>, dim3(nrow), dim3(NT), 0, s, w.R, Vq,
-                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows, nq - q0);
+                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows_wide, nq - q0);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = wide_gram_inverse(w, 1, weighted, bb, s);
