@@ -232,7 +232,7 @@ int externd_factorize_refined(const float* A, int64_t m, int64_t n, double mu, d
  * Inference with a factorization (Sec. 2.6 cost model): for each of nb
  * input vectors x (rows of X), y = B (diag(D) (C x)), computed on the packed
  * trits in a fixed order (deterministic).
- *  - One vector with n, k <= 10240: integer matrix cores.  x and the
+ *  - One vector with n, k <= 65536: integer matrix cores.  x and the
  *    intermediate t = diag(D) C x enter as 48-bit fixed-point vectors (one
  *    power-of-two scale each: x's from max |x|, t's from the bound
  *    max |D| sum_j |x_j|), so every product and sum is exact; the error is
@@ -249,16 +249,16 @@ int externd_factorize_refined(const float* A, int64_t m, int64_t n, double mu, d
  *  B_packed   device, m rows of ceil(k/4) bytes; C_packed device, k rows of
  *             ceil(n/4) bytes; D device fp32[k] -- as written by
  *             externd_factorize (or _to_energy, whose zero components
- *             contribute nothing).  On the matrix-core path, rows of a
- *             multiple of 8 bytes (nb <= 5) or 16 bytes (nb >= 6) at an
- *             aligned base take whole-word loads.
+ *             contribute nothing).  On the matrix-core path, rows of
+ *             any length at any byte address take whole-word loads.
  *  X          device fp32, nb x n row-major.  Y device fp32, nb x m
  *             row-major (out).
  *  nb         1 <= nb <= EXTERND_APPLY_MAX_BATCH.
  *  workspace  device, >= externd_apply_workspace_bytes(m, n, k, nb) bytes,
  *             256-byte aligned.  nb = 1: the intermediate diag(D) C x
  *             (n, k <= 10240: its six 8-bit digit planes, 1536 bytes per
- *             256 entries, and an exponent word; else 4 k bytes).  nb >= 2: its bf16 parts (6 nb k bytes) and
+ *             256 entries, and an exponent word; n, k <= 65536: those of x
+ *             too; else 4 k bytes).  nb >= 2: its bf16 parts (6 nb k bytes) and
  *             partial sums over slices of the contracted dimensions (at
  *             most nb max(n, m) k / 32 bytes, rounded up to whole row
  *             groups).

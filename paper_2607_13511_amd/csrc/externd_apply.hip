@@ -5,9 +5,12 @@
 // Trit code (include/externd.h): 00 -> 0, 01 -> +1, 11 -> -1, element j of a
 // row in byte j >> 2 at bits 2 (j & 3).
 //
-// Two paths, chosen by the batch size nb.
+// Paths, chosen by the batch size nb and the vectors' lengths.
 //
-// One vector (a matrix-vector product), k_apply_vec_c then k_apply_vec_b:
+// One vector (a matrix-vector product): integer matrix cores, with the
+// vector's digit planes in LDS (k_gemv_c, k_gemv_b) or, beyond 10240
+// entries, brought there by segments (k_gemv_x, k_gemv_long).  Beyond 65536
+// entries k_apply_vec_c then k_apply_vec_b:
 // fp32 FMA on the vector ALUs.  The signed 2-bit field extract (v_bfe_i32)
 // of a code is the trit itself (01 -> 1, 11 -> -1, 00 -> 0).  A workgroup
 // takes VEC_RPW consecutive rows; lane l of wave w takes byte
@@ -131,6 +134,48 @@ struct ProdArgs {
   float* Y;
 };
 
+// N bytes at P + o, o < total = the matrix's bytes, of any alignment, as one
+// load (global loads take any byte address).  Where fewer than N bytes are
+// left, the load starts earlier and is shifted down when it is used
+// (window_fix), zeros above.  Bytes past the row's own are the next row's:
+// they meet zero vector entries.  A matrix of fewer than N bytes is read byte
+// by byte.
+template <int N>
+__device__ __forceinline__ void window_load(const uint8_t* __restrict__ P, int64_t o, int64_t total,
+                                            unsigned (&w)[N / 4]) {
+  if (total < N) {  // uniform
+#pragma unroll
+    for (int q = 0; q < N / 4; ++q) {
+      w[q] = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[q] |= (o + 4 * q + e < total ? (unsigned)P[o + 4 * q + e] : 0u) << (8 * e);
+    }
+    return;
+  }
+  __builtin_memcpy(w, P + (o < total - N ? o : total - N), N);
+}
+template <int N>
+__device__ __forceinline__ void window_fix(int64_t o, int64_t total, unsigned (&w)[N / 4]) {
+  const int cut = total >= N && o > total - N ? (int)(o - (total - N)) : 0;  // bytes to drop
+  if (cut) {
+    unsigned v[N / 4 + 1];
+#pragma unroll
+    for (int q = 0; q < N / 4; ++q) v[q] = w[q];
+    v[N / 4] = 0u;
+    const int ws = cut >> 2, bs = 8 * (cut & 3);
+#pragma unroll
+    for (int q = 0; q < N / 4; ++q) {
+      unsigned lo = 0u, hi = 0u;
+#pragma unroll
+      for (int z = 0; z <= N / 4; ++z) {
+        lo = z == q + ws ? v[z] : lo;
+        hi = z == q + ws + 1 ? v[z] : hi;
+      }
+      w[q] = (unsigned)((((uint64_t)hi << 32) | lo) >> bs);
+    }
+  }
+}
+
 // The parts of T_c = D_c v (zero past the real rows).
 __device__ __forceinline__ void store_t(const float* D, unsigned short* TS, int64_t tstride, int64_t rows, int64_t c,
                                         int b, float v) {
@@ -205,14 +250,10 @@ __global__ __launch_bounds__(NT_AP) void k_apply_prod(ProdArgs a) {
         // out of range: the row's first bytes, against zero vector parts
         wd[j][t] = *(const typename S::word*)(a.P + row * a.rb + (ok ? b0 : 0));
       } else {
-        unsigned u[4] = {0u, 0u, 0u, 0u};
-        if (ok)
-          for (int q = 0; q < S::bytes; ++q)
-            if (b0 + q < a.rb) u[q >> 2] |= (unsigned)a.P[row * a.rb + b0 + q] << (8 * (q & 3));
-        typename S::word v;
+        unsigned u[S::bytes / 4];
+        window_load<S::bytes>(a.P, row * a.rb + (ok ? b0 : 0), a.rows * a.rb, u);
 #pragma unroll
-        for (int q = 0; q < S::bytes / 4; ++q) v[q] = u[q];
-        wd[j][t] = v;
+        for (int q = 0; q < S::bytes / 4; ++q) wd[j][t][q] = u[q];
       }
     }
   }
@@ -243,6 +284,27 @@ __global__ __launch_bounds__(NT_AP) void k_apply_prod(ProdArgs a) {
     }
   }
   __syncthreads();
+  // uniform: only windows from the wave's last rows that reach the matrix's
+  // last bytes can be cut (with short rows, those of many rows before the end)
+  if (!AL && (row0 + AP_WROWS) * a.rb + S::bytes > a.rows * a.rb) {
+#pragma unroll
+    for (int j = 0; j < SL; ++j) {
+      const int64_t ch = ch0 + j;
+      const int64_t b0 = (ch < a.nch ? ch : 0) * (AP_CHUNK / 4) + S::bytes * g;
+      const bool ok = ch < a.nch && b0 < a.rb;
+#pragma unroll
+      for (int t = 0; t < S::tiles; ++t) {
+        int64_t row = row0 + TM * t + lr;
+        row = row < a.rows ? row : a.rows - 1;
+        unsigned u[S::bytes / 4];
+#pragma unroll
+        for (int q = 0; q < S::bytes / 4; ++q) u[q] = wd[j][t][q];
+        window_fix<S::bytes>(row * a.rb + (ok ? b0 : 0), a.rows * a.rb, u);
+#pragma unroll
+        for (int q = 0; q < S::bytes / 4; ++q) wd[j][t][q] = u[q];
+      }
+    }
+  }
 
   // 4. The products.
   typename S::accum acc[S::tiles];
@@ -540,42 +602,42 @@ __device__ __forceinline__ void gv_sum_max2(double& sum, double& m1, double& m2,
   }
 }
 
-// The 16 packed bytes of lane (rr, g) for super-step ss of row `row` (rb
-// bytes per row).  ALIGNED: rb and the base are multiples of 16, so a chunk
-// lies wholly inside or wholly past the row; a chunk past it is loaded from
-// the row's start and zeroed where it is used (gv_tile: masking it here
-// would wait for the load).  Else byte loads, zero past the row.
+// The 16 packed bytes of lane (rr, g) for super-step ss of the row at byte
+// offset `row` of P (rb bytes per row, `total` in all).  ALIGNED: rb and the
+// base are multiples of 16, so a chunk lies wholly inside or wholly past the
+// row; a chunk past it is loaded from the row's start and zeroed where it is
+// used (gv_tile: masking it here would wait for the load).  Else a window of
+// any alignment, whose bytes past the row meet zero digits.
 template <bool ALIGNED>
-__device__ __forceinline__ v4i_g gv_load(const uint8_t* __restrict__ row, int64_t rb, int64_t ss, int g) {
-  const int64_t o = ss * 64 + 16 * g;
-  if (ALIGNED) return *(const v4i_g*)(row + (o < rb ? o : 0));
-  uint8_t b[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) b[e] = row[o + e < rb ? o + e : 0];
+__device__ __forceinline__ v4i_g gv_load(const uint8_t* __restrict__ P, int64_t row, int64_t rb, int64_t total,
+                                         int64_t ss, int g) {
+  int64_t o = ss * 64 + 16 * g;
+  o = row + (o < rb ? o : 0);
+  if (ALIGNED) return *(const v4i_g*)(P + o);
   unsigned w[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    w[q] = 0u;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) w[q] |= (o + 4 * q + e < rb ? (unsigned)b[4 * q + e] : 0u) << (8 * e);
-  }
+  window_load<16>(P, o, total, w);
   return v4i_g{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
 }
 
-// The wave's share of a tile: super-steps [s0, s1) of row `row` (rows past
+// The wave's share of a tile: super-steps base + [s0, s1) of row `row` (rows past
 // the matrix read its last row; their results are discarded).
 struct GvWave {
-  const uint8_t* row;
+  const uint8_t* P;
+  int64_t row, total;
+  int base;  // first super-step of the segment in LDS
   int s0, s1;
 };
 __device__ __forceinline__ GvWave gv_wave(const uint8_t* __restrict__ P, int64_t rows, int64_t rb, int nss,
-                                          int64_t r0) {
+                                          int64_t r0, int base = 0) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tile = w / GV_KSPLIT, kh = w % GV_KSPLIT;
   const int half = (nss + GV_KSPLIT - 1) / GV_KSPLIT;
   const int64_t rr = r0 + 16 * tile + (lane & 15);
   GvWave v;
-  v.row = P + (rr < rows ? rr : rows - 1) * rb;
+  v.P = P;
+  v.row = (rr < rows ? rr : rows - 1) * rb;
+  v.total = rows * rb;
+  v.base = base;
   v.s0 = kh * half < nss ? kh * half : nss;
   v.s1 = (kh + 1) * half < nss ? (kh + 1) * half : nss;
   return v;
@@ -591,7 +653,8 @@ constexpr int GV_PF = 6;
 template <bool ALIGNED>
 __device__ __forceinline__ v4i_g gv_step_load(const GvWave& v, int64_t rb, int j) {
   const int g = (threadIdx.x & 63) >> 4;
-  return gv_load<ALIGNED>(v.row, rb, v.s0 + j < v.s1 ? v.s0 + j : v.s0, g);
+  return gv_load<ALIGNED>(v.P, v.row, rb, v.total,
+                          v.base + (v.s0 + j < v.s1 ? v.s0 + j : v.s0), g);
 }
 
 // The first GV_PF steps' trit loads (issued before the vector is staged, so
@@ -629,11 +692,18 @@ __device__ __forceinline__ void gv_tile(const GvWave& v, int64_t rb, v4i_g (&buf
     // no branch: a step past the wave's share (or a chunk past the row)
     // multiplies zero trits, its B operands read at a clamped address
     const int cur = v.s0 + j;
-    const bool live = cur < v.s1 && (!ALIGNED || (int64_t)cur * 64 + 16 * g < rb);
+    const bool live = cur < v.s1 && (int64_t)(v.base + cur) * 64 + 16 * g < rb;
     const int jb = cur < v.s1 ? j : 0;
     v4i_g bo[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) bo[i] = *(const v4i_g*)(bsrc + jb * bstep + i * (4 * GV_PLANES * 16));
+    if (!ALIGNED && __any(v.row + rb + 64 > v.total)) {
+      // the end of the matrix: a window may have started early
+      unsigned u[4] = {(unsigned)buf[j][0], (unsigned)buf[j][1], (unsigned)buf[j][2], (unsigned)buf[j][3]};
+      const int64_t o = (int64_t)(v.base + (cur < v.s1 ? cur : v.s0)) * 64 + 16 * g;
+      window_fix<16>(v.row + (o < rb ? o : 0), v.total, u);
+      buf[j] = v4i_g{(int)u[0], (int)u[1], (int)u[2], (int)u[3]};
+    }
     const v4i_g w = live ? buf[j] : v4i_g{0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -804,6 +874,145 @@ __global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void
   }
 }
 
+// ---- one vector, n or k beyond GV_MAX_LEN (both at most GV_LONG_MAX) ----
+//
+// The same arithmetic, with the vector's digit planes in memory and brought
+// into LDS a segment of GV_MAX_SS super-steps at a time.  x is converted
+// once, by a launch of its own (k_gemv_x), as the planes no longer fit a
+// workgroup; then the two sides are the same kernel.  Bound by the memory's
+// read of the trits: 8192 x 28672, k = 20480 (189 MB) takes 66 us; fp32
+// FMA on decoded trits, one byte a lane, was bound by the decode at 112 us.
+constexpr int64_t GV_LONG_MAX = 65536;  // int64 sums of 48-bit entries stay below 2^63
+
+// X's digit planes XT (256 nss components, zero past n) and the exponents
+// sX[0] = x's, sX[1] = t's (GV_NONFINITE for a non-finite x or D).  Every
+// workgroup forms the statistics of all of x and D with the same arithmetic
+// and converts GV_NT components.  grid: ceil(256 nss / GV_NT).
+__global__ __launch_bounds__(GV_NT) void k_gemv_x(const float* __restrict__ X, const float* __restrict__ D, int64_t n,
+                                                  int64_t k, int nss, uint8_t* __restrict__ XT,
+                                                  int* __restrict__ sX) {
+  __shared__ double sh[3 * (GV_NT / 64)];
+  const int tid = threadIdx.x;
+  double sx = 0.0, mx = 0.0, md = 0.0;
+  bool bad = false;
+  // four entries a load (any alignment), eight loads of either vector in
+  // flight: the latency of a few rounds is the launch's time
+  constexpr int U = 8;
+  const int64_t n4 = n >> 2, k4 = k >> 2;
+  for (int64_t c0 = tid; c0 < (n4 > k4 ? n4 : k4); c0 += U * GV_NT) {
+    float v[U][4], d[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t cx = c0 + u * GV_NT, cd = c0 + u * GV_NT;
+      if (n4 > 0) __builtin_memcpy(v[u], X + 4 * (cx < n4 ? cx : 0), 16);
+      if (k4 > 0) __builtin_memcpy(d[u], D + 4 * (cd < k4 ? cd : 0), 16);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double a = c0 + u * GV_NT < n4 ? fabs((double)v[u][e]) : 0.0;
+        const double b = c0 + u * GV_NT < k4 ? fabs((double)d[u][e]) : 0.0;
+        bad |= !(a <= 1.0e300) || !(b <= 1.0e300);
+        sx += a;
+        mx = fmax(mx, a);
+        md = fmax(md, b);
+      }
+  }
+  if (tid < 3) {  // the entries past the last whole four
+    const double a = 4 * n4 + tid < n ? fabs((double)X[4 * n4 + tid]) : 0.0;
+    const double b = 4 * k4 + tid < k ? fabs((double)D[4 * k4 + tid]) : 0.0;
+    bad |= !(a <= 1.0e300) || !(b <= 1.0e300);
+    sx += a;
+    mx = fmax(mx, a);
+    md = fmax(md, b);
+  }
+  if (bad) mx = INFINITY;
+  gv_sum_max2(sx, mx, md, sh);
+  const bool finite = mx < INFINITY;
+  const int s_x = gv_shift(mx);
+  const int64_t c = (int64_t)blockIdx.x * GV_NT + tid;
+  if (c < (int64_t)nss * GV_SS) {
+    const float x = (c < n && finite) ? X[c] : 0.0f;
+    int8_t d[GV_PLANES];
+    gv_digits((long long)rint(ldexp((double)x, s_x)), d);
+#pragma unroll
+    for (int p = 0; p < GV_PLANES; ++p) XT[gv_digit_offset(c, p)] = (uint8_t)d[p];
+  }
+  if (blockIdx.x == 0 && tid == 0) {
+    sX[0] = s_x;
+    sX[1] = finite ? gv_shift(md * sx) : GV_NONFINITE;
+  }
+}
+
+// CSIDE: T = the digit planes of diag(D) (P v) (256 nss_t components, zero
+// past the rows), exponent s[1]; else Y = P v.  v: the digit planes V of len
+// components, exponent s[CSIDE ? 0 : 1].  grid: ceil(rows / GV_ROWS).
+template <bool ALIGNED, bool CSIDE>
+__global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void k_gemv_long(
+    const uint8_t* __restrict__ P, int64_t rows, int64_t len, const uint8_t* __restrict__ V,
+    const int* __restrict__ s, const float* __restrict__ D, int nss_t, uint8_t* __restrict__ T,
+    float* __restrict__ Y) {
+  __shared__ __attribute__((aligned(16))) uint8_t dig[GV_MAX_SS * GV_SSB];
+  __shared__ __attribute__((aligned(16))) uint8_t zero16[16];
+  __shared__ int xch[GV_NT / 64][64][4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int nss = (int)((len + GV_SS - 1) / GV_SS);
+  const int64_t rb = (len + 3) >> 2;
+  const int64_t r0 = (int64_t)blockIdx.x * GV_ROWS;
+  const int s_v = s[CSIDE ? 0 : 1], s_t = s[1];
+  if (tid < 4) ((int*)zero16)[tid] = 0;
+  int out[4] = {0, 0, 0, 0};
+  for (int base = 0; base < nss; base += GV_MAX_SS) {
+    const int ns = nss - base < GV_MAX_SS ? nss - base : GV_MAX_SS;
+    constexpr int NCP = (GV_MAX_SS * GV_SSB / 16 + GV_NT - 1) / GV_NT;
+    const int ncp = ns * GV_SSB / 16;
+    v4i_g cp[NCP];
+#pragma unroll
+    for (int j = 0; j < NCP; ++j) {
+      const int e = tid + GV_NT * j;
+      cp[j] = ((const v4i_g*)(V + (int64_t)base * GV_SSB))[e < ncp ? e : 0];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const GvWave v = gv_wave(P, rows, rb, ns, r0, base);
+    v4i_g buf[GV_NSTEP];
+    gv_prefetch<ALIGNED>(v, rb, buf);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();  // the previous segment has been read
+#pragma unroll
+    for (int j = 0; j < NCP; ++j) {
+      const int e = tid + GV_NT * j;
+      if (e < ncp) ((v4i_g*)dig)[e] = cp[j];
+    }
+    __syncthreads();
+    int o[4];
+    gv_tile<ALIGNED>(v, rb, buf, dig, zero16, o);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[r] += o[r];
+  }
+  const long long y = gv_combine(out, xch);
+  if (wv % GV_KSPLIT == 0 && lane < 16) {
+    const int64_t i = r0 + 16 * (wv / GV_KSPLIT) + lane;
+    if (CSIDE) {
+      if (i < (int64_t)nss_t * GV_SS) {
+        long long q = 0;
+        if (i < rows && s_t != GV_NONFINITE) q = (long long)rint(ldexp((double)y, s_t - s_v) * (double)D[i]);
+        int8_t d[GV_PLANES];
+        gv_digits(q, d);
+#pragma unroll
+        for (int p = 0; p < GV_PLANES; ++p) T[gv_digit_offset(i, p)] = (uint8_t)d[p];
+      }
+    } else if (i < rows) {
+      Y[i] = s_t == GV_NONFINITE ? NAN : (float)ldexp((double)y, -s_v);
+    }
+  }
+  if (CSIDE && blockIdx.x == gridDim.x - 1) {
+    for (int64_t c = (int64_t)gridDim.x * GV_ROWS + tid; c < (int64_t)nss_t * GV_SS; c += GV_NT)
+#pragma unroll
+      for (int p = 0; p < GV_PLANES; ++p) T[gv_digit_offset(c, p)] = 0;
+  }
+}
+
 // ---- matrix-core path ----
 
 // Chunks per slice for nch chunks over nrg row groups: the most (a power of
@@ -829,12 +1038,23 @@ static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 // fit in LDS: the integer matrix-core path (k_gemv_c, k_gemv_b).
 static bool gemv_fits(int64_t n, int64_t k, int nb) { return nb == 1 && n <= GV_MAX_LEN && k <= GV_MAX_LEN; }
 
+static bool gemv_long(int64_t n, int64_t k, int nb) {
+  return nb == 1 && !gemv_fits(n, k, nb) && n <= GV_LONG_MAX && k <= GV_LONG_MAX;
+}
+
 static ApplyLayout apply_layout(int64_t m, int64_t n, int64_t k, int nb) {
   ApplyLayout L{};
   if (gemv_fits(n, k, nb)) {
     // the digit planes of t (256-component super-steps) and the exponent word
     L.ts = al256((size_t)((k + GV_SS - 1) / GV_SS) * GV_SSB);
     L.total = L.ts + 256;
+    return L;
+  }
+  if (gemv_long(n, k, nb)) {
+    // the digit planes of t and x and the exponent words
+    L.ts = al256((size_t)((k + GV_SS - 1) / GV_SS) * GV_SSB);
+    L.part = L.ts + al256((size_t)((n + GV_SS - 1) / GV_SS) * GV_SSB);
+    L.total = L.part + 256;
     return L;
   }
   if (nb <= AP_VEC_MAX) {
@@ -924,9 +1144,37 @@ static hipError_t run_gemv(const uint8_t* Bp, const uint8_t* Cp, const float* D,
   return hipGetLastError();
 }
 
+template <bool CSIDE>
+static hipError_t launch_gemv_long(const uint8_t* P, int64_t rows, int64_t len, const uint8_t* V, const int* sx,
+                                   const float* D, int nss_t, uint8_t* T, float* Y, hipStream_t s) {
+  const dim3 grid((unsigned)((rows + GV_ROWS - 1) / GV_ROWS));
+  if (((len + 3) / 4) % 16 == 0 && ((uintptr_t)P % 16) == 0)
+    hipLaunchKernelGGL((k_gemv_long<true, CSIDE>), grid, dim3(GV_NT), 0, s, P, rows, len, V, sx, D, nss_t, T, Y);
+  else
+    hipLaunchKernelGGL((k_gemv_long<false, CSIDE>), grid, dim3(GV_NT), 0, s, P, rows, len, V, sx, D, nss_t, T, Y);
+  return hipGetLastError();
+}
+
+static hipError_t run_gemv_long(const uint8_t* Bp, const uint8_t* Cp, const float* D, int64_t m, int64_t n, int64_t k,
+                                const float* X, float* Y, char* ws, hipStream_t s) {
+  const ApplyLayout L = apply_layout(m, n, k, 1);
+  uint8_t* T = (uint8_t*)ws;
+  uint8_t* XT = (uint8_t*)(ws + L.ts);
+  int* sx = (int*)(ws + L.part);
+  const int nss_x = (int)((n + GV_SS - 1) / GV_SS), nss_t = (int)((k + GV_SS - 1) / GV_SS);
+  hipLaunchKernelGGL(k_gemv_x, dim3((unsigned)((nss_x * GV_SS + GV_NT - 1) / GV_NT)), dim3(GV_NT), 0, s, X, D, n, k,
+                     nss_x, XT, sx);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  e = launch_gemv_long<true>(Cp, k, n, XT, sx, D, nss_t, T, nullptr, s);
+  if (e != hipSuccess) return e;
+  return launch_gemv_long<false>(Bp, m, k, T, sx, nullptr, 0, nullptr, Y, s);
+}
+
 static hipError_t run_apply_kernels(const uint8_t* Bp, const uint8_t* Cp, const float* D, int64_t m, int64_t n,
                                     int64_t k, const float* X, int nb, float* Y, char* ws, hipStream_t s) {
   if (gemv_fits(n, k, nb)) return run_gemv(Bp, Cp, D, m, n, k, X, Y, ws, s);
+  if (gemv_long(n, k, nb)) return run_gemv_long(Bp, Cp, D, m, n, k, X, Y, ws, s);
   if (nb <= AP_VEC_MAX) return run_vec<AP_VEC_MAX>(Bp, Cp, D, m, n, k, X, nb, Y, (float*)ws, s);
   const ApplyLayout L = apply_layout(m, n, k, nb);
   unsigned short* TS = (unsigned short*)(ws + L.ts);

@@ -1,0 +1,96 @@
+"""Inference at the sizes where its loads and segments have edges: packed rows
+of any byte length at any byte address, matrices shorter than one load window,
+and one vector past the length that a workgroup holds (segments of 10240
+components, up to 65536).
+
+The packed matrices lie in buffers whose other bytes are all ones (trit code
+11, i.e. -1), so a byte taken from past a row or a matrix shows in the result.
+Tolerances as derived in test_gpu_apply.py: one vector is exact integer sums
+between two fixed-point conversions, more are fp32 sums of exact products.
+"""
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24
+
+
+def pack(X):
+    rows, cols = X.shape
+    code = np.where(X == 0, 0, np.where(X > 0, 1, 3)).astype(np.uint8)
+    code = np.concatenate([code, np.zeros((rows, (-cols) % 4), np.uint8)], axis=1).reshape(rows, -1, 4)
+    return (code[:, :, 0] | (code[:, :, 1] << 2) | (code[:, :, 2] << 4) | (code[:, :, 3] << 6)).astype(np.uint8)
+
+
+def place(P, offset):
+    """P on the GPU at a byte offset inside a buffer of ones."""
+    buf = torch.full((P.size + offset + 64,), 0xFF, dtype=torch.uint8, device="cuda")
+    view = buf[offset:offset + P.size].view(P.shape)
+    view.copy_(torch.from_numpy(P))
+    return view
+
+
+def check(m, n, k, nb, offset, scale=None):
+    from paper_2607_13511_amd import binding
+    rng = np.random.default_rng([m, n, k, nb, offset])
+    B = rng.integers(-1, 2, size=(m, k)).astype(np.int8)
+    C = rng.integers(-1, 2, size=(k, n)).astype(np.int8)
+    D = rng.standard_normal(k).astype(np.float32).astype(np.float64)
+    X = rng.standard_normal((nb, n)).astype(np.float32).astype(np.float64)
+    if scale is not None:
+        X = (X * scale(rng, X.shape)).astype(np.float32).astype(np.float64)
+    Y = binding.apply(place(pack(B), offset), place(pack(C), offset), torch.from_numpy(D.astype(np.float32)).cuda(),
+                      m, n, torch.from_numpy(X.astype(np.float32)).cuda()).cpu().numpy().astype(np.float64)
+    ref = oracle.apply(B, C, D, X)
+    Bf, Cf = np.abs(B).astype(np.float64), np.abs(C).astype(np.float64)
+    if nb == 1:
+        mx, sx, md = np.max(np.abs(X)), np.sum(np.abs(X)), np.max(np.abs(D))
+        q = Bf @ (np.abs(D) * Cf.sum(axis=1)) * mx + Bf.sum(axis=1) * md * sx
+        bound = U * np.abs(ref) + 2.0 * 2.0 ** -46 * q[None, :]
+    else:
+        bound = ((n + k + 4) * U * (Bf @ (np.abs(D)[:, None] * (Cf @ np.abs(X).T)))).T
+    assert np.all(np.abs(Y - ref) <= bound)
+
+
+@pytest.mark.parametrize("nb", [1, 3, 8])
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (1, 61, 3), (3, 5, 70), (2, 28, 31), (17, 65, 63), (16, 254, 513),
+                                   (65, 1021, 259), (257, 130, 1030)])
+def test_row_lengths(m, n, k, nb):
+    check(m, n, k, nb, 0)
+
+
+@pytest.mark.parametrize("nb", [1, 2, 6])
+@pytest.mark.parametrize("offset", [1, 4, 8, 15])
+def test_byte_addresses(offset, nb):
+    check(33, 256, 320, nb, offset)   # rows of 64 and 80 bytes: only the base is off
+    check(19, 250, 330, nb, offset)
+
+
+@pytest.mark.parametrize("m,n,k", [(40, 10241, 33), (16, 33, 20481), (33, 20480, 48), (17, 30723, 10245),
+                                   (5, 65536, 7), (3, 9, 65535)])
+def test_one_long_vector(m, n, k):
+    check(m, n, k, 1, 0)
+    check(m, n, k, 1, 1, lambda rng, shape: np.exp2(rng.integers(-20, 1, size=shape)))
+
+
+def test_one_long_vector_past_the_segments():
+    check(6, 65537, 12, 3, 0)   # several vectors take the slices at any length
+    from paper_2607_13511_amd import binding
+    small = binding.lib().externd_apply_workspace_bytes(6, 65537, 12, 1)
+    assert small == 256         # 12 floats: the fp32 path past 65536
+
+
+def test_long_vector_nonfinite():
+    from paper_2607_13511_amd import binding
+    C = np.ones((4, 12000), np.int8)
+    B = np.ones((3, 4), np.int8)
+    for bad in (np.nan, np.inf):
+        X = np.ones((1, 12000), np.float32)
+        X[0, 11999] = bad
+        Y = binding.apply(place(pack(B), 0), place(pack(C), 0), torch.ones(4, device="cuda"), 3, 12000,
+                          torch.from_numpy(X).cuda())
+        assert torch.isnan(Y).all()
