@@ -184,10 +184,12 @@ bool carve(Ws& w, void* base, size_t bytes, int64_t m, int64_t n, int64_t k) {
   w.ginvV = (double*)(b + L.off[10]);
   w.gramV = (double*)(b + L.off[11]);
   // the partial Grams take the first NSIDE_INT of the buffer's NSIDE_MAX matrices
-  static_assert((NSIDE_MAX - NSIDE_INT) * 4096 >= USTEP_SLOTS + 2 * FLAG_COPIES * FLAG_STRIDE, "room for counters and flags");
+  static_assert((NSIDE_MAX - NSIDE_INT) * 4096 >= USTEP_SLOTS + 2 * FLAG_COPIES * FLAG_STRIDE + WIDE_SYNC_WORDS,
+                "room for counters and flags");
   w.gparti = (int*)(b + L.off[13]);
   w.utcnt = (unsigned*)(w.gparti + NSIDE_INT * 4096);
   w.gflag = w.utcnt + USTEP_SLOTS;
+  w.wsync = w.gflag + 2 * FLAG_COPIES * FLAG_STRIDE;
   w.colE_part = (double*)(b + L.off[14]);
   w.hw = (double*)(b + L.off[15]);
   w.gvec = (double*)(b + L.off[16]);

@@ -39,6 +39,7 @@ constexpr int DEFLATE_SLOTS = 512;
 // Copies of an in-launch flag, each on a line of its own (words apart).
 constexpr int FLAG_COPIES = 16;
 constexpr int FLAG_STRIDE = 32;
+constexpr int WIDE_SYNC_WORDS = 512;  // arrival words of the wide blocks' side path
 // Threads per workgroup for all kernels except the selection kernel.
 constexpr int NT = 256;
 // Weighted Grams on int8 MFMA: the weights h~_j / max h~ as integers of at
@@ -99,6 +100,7 @@ struct Ws {
   double* gramV;         // BBP x BBP raw V^T H V (no ridge)
   int* gparti;           // NSIDE_INT x BBP x BBP partial integer Grams (scale step entry point)
   unsigned* utcnt;       // USTEP_SLOTS arrival counters of the U-step's row tiles (zero between launches)
+  unsigned* wsync;       // WIDE_SYNC_WORDS arrival words of the wide blocks' side path (zero between launches)
   unsigned* gflag;       // 2 x FLAG_COPIES flags, FLAG_STRIDE apart: set by the V-step's (then the U-step's)
                          // side path once its inverse Gram is stored, cleared by k_tern_v (k_tern_u)
   double* colE_part;     // gd x n_pad partial column energies

@@ -1549,6 +1549,363 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 }
 
 // ---------------------------------------------------------------------------
+// Wide blocks (bb up to BMAX = NQMAX x 64 components, Sec. 2.4): the Gram
+// matrices of Eq. (3) and the matrix of the joint solve of Eq. (4) couple
+// the quarters of a block.  Their inverse, (X^T diag(h~) X + eps I)^{-1} for
+// up to 256 components, is the side path of the contraction launches: Gram
+// workgroups (quarter pair x K slice) add integer Gram blocks with integer
+// atomics, and nq x nq sweep workgroups, each holding one 64 x 64 fp64 block
+// in registers, run the blocked sweep A -> -A^{-1}, one step per quarter:
+//   B_kk = -P, B_kj = P A_kj, B_ik = A_ik P, B_ij = A_ij - (A_ik P) A_kj,
+// P = A_kk^{-1}.  The blocks of row k (the swept matrix is symmetric, so
+// A_ik = A_ki^T) and P travel through memory: written through, then counted
+// or flagged, then read with plain loads (each place is written once per
+// launch and read only after its flag, and a launch starts with clean
+// caches).  Workgroup (k + 1, k + 1) goes from its update of step k straight
+// to its pivot inverse.
+//
+// As launches of their own these were seven, one after the other, behind
+// the contraction: 5.8 (Gram) + 7.5 + 4 x 19.8 + 4.7 us; now 80 us, beside
+// the contraction.
+// ---------------------------------------------------------------------------
+// quarter pair p <-> (q, q') with q <= q' < nq, in row order
+__device__ __forceinline__ void pair_of(int p, int nq, int& q, int& q2) {
+  q = 0;
+  while (p >= nq - q) {
+    p -= nq - q;
+    ++q;
+  }
+  q2 = q + p;
+}
+__host__ __device__ __forceinline__ int pair_index(int q, int q2, int nq) {
+  return q * nq - q * (q - 1) / 2 + (q2 - q);
+}
+
+
+struct WideSide {
+  const v4i* X;          // the factor, MFMA-ready, quarter q at 4 q L_pad
+  const int8_t* W;       // mode 1: its digit-scaled planes
+  int64_t L_pad;
+  int nq, bb;
+  int mode;              // 0: integer Gram, 1: weighted Gram, 2: Gram o raw (Eq. (4))
+  int* gacc;             // pair blocks (int32; mode 1: int64); cleared by a later launch
+  const double* hwmax;
+  double* raw;           // BMAX x BMAX raw Gram: out (mode 0 and 1, if given), in (mode 2)
+  double rel;            // ridge (guard) = rel * trace / bb
+  double* panel;         // block (k, j) at (k NQMAX + j) 4096: A_kj at step k
+  double* pivot;         // block k: P of step k
+  double* ginv;          // out: block (q, q') at (q NQMAX + q') 4096, ginv_index order
+  int* wflag;            // out: 1 for a zero trace
+  unsigned* sync;        // WIDE_SYNC_WORDS, zero at the start; cleared by a later launch
+  int* flags;
+};
+constexpr int GRAM_PAIR_SLICES = 16;  // K slices per quarter pair of the Gram
+// arrival words on lines of their own: Gram workgroups, panels of step k, pivot of step k
+constexpr int WIDE_SYNC_GRAM = 0, WIDE_SYNC_PANEL = 32, WIDE_SYNC_PIVOT = 32 * (1 + NQMAX);
+constexpr int WIDE_SMEM = 2 * 4096 * 8 + 512 * 8;  // LDS bytes of the side path
+static_assert(WIDE_SYNC_PIVOT + 32 * NQMAX <= WIDE_SYNC_WORDS, "arrival words");
+__host__ __device__ __forceinline__ int wide_gram_wgs(int nq) { return nq * (nq + 1) / 2 * GRAM_PAIR_SLICES; }
+__host__ __device__ __forceinline__ int wide_side_wgs(int nq) { return wide_gram_wgs(nq) + nq * nq; }
+
+// Waits (thread 0, then the workgroup) until *p reaches n; bounded as
+// await_flag.
+__device__ __forceinline__ void wide_await(const unsigned* p, unsigned n, int* flags) {
+  if (threadIdx.x == 0) {
+    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+    while (load_coherent(p) < n) {
+      if (__builtin_amdgcn_s_memrealtime() - t0 > SYNC_TICKS) {
+        store_coherent(flags + FLAG_SYNC, 1);
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  __syncthreads();
+}
+// After coherent stores of the whole workgroup: counts it in *p.
+__device__ __forceinline__ void wide_arrive(unsigned* p) {
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Integer Gram block X_q^T X_q' over the K steps [ks0, ks1), on int8 MFMA,
+// added into g (4096 int32) with integer atomics (exact, order-free).
+// red: LDS, 4 x 4096 int32.
+__device__ __forceinline__ void wide_gram_int(const v4i* __restrict__ Xa, const v4i* __restrict__ Xb, int ks0, int ks1,
+                                              int* g, int* red) {
+  constexpr int KR = 4;
+  const int lane = lane_id(), wave = wave_id();
+  const int h = lane >> 5, l32 = lane & 31;
+  v16i acc00 = {}, acc01 = {}, acc10 = {}, acc11 = {};
+  for (int ks = ks0 + wave; ks < ks1; ks += 4 * KR) {
+    v4i a[KR][2], b[KR][2];
+#pragma unroll
+    for (int u = 0; u < KR; ++u) {
+      const int kk = ks + 4 * u;
+      if (kk < ks1) {
+        a[u][0] = Xa[(int64_t)kk * 128 + lane];
+        a[u][1] = Xa[(int64_t)kk * 128 + 64 + lane];
+        b[u][0] = Xb[(int64_t)kk * 128 + lane];
+        b[u][1] = Xb[(int64_t)kk * 128 + 64 + lane];
+      } else {
+        a[u][0] = a[u][1] = b[u][0] = b[u][1] = v4i{};
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < KR; ++u) {
+      acc00 = mfma_i8(a[u][0], b[u][0], acc00);
+      acc01 = mfma_i8(a[u][0], b[u][1], acc01);
+      acc10 = mfma_i8(a[u][1], b[u][0], acc10);
+      acc11 = mfma_i8(a[u][1], b[u][1], acc11);
+    }
+  }
+  int* mine = red + wave * 4096;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int M = 8 * (r >> 2) + 4 * h + (r & 3);
+    const int N = l32;
+    mine[M * 64 + N] = acc00[r];
+    mine[M * 64 + 32 + N] = acc01[r];
+    mine[(32 + M) * 64 + N] = acc10[r];
+    mine[(32 + M) * 64 + 32 + N] = acc11[r];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 4096; e += NT) {
+    const int v = red[e] + red[4096 + e] + red[8192 + e] + red[12288 + e];
+    if (v) __hip_atomic_fetch_add(g + e, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+
+// Blocks of the fp64 exchange: tile (a, b) of a 64 x 64 block at 256 (4 a + b),
+// register r of lane l at 64 r + l.  acc[nt] of wave w is tile (w, nt).
+__device__ __forceinline__ void wide_publish(double* dst, const v4d (&acc)[4]) {
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) store_coherent(dst + 256 * (4 * wave_id() + nt) + 64 * r + lane_id(), acc[nt][r]);
+}
+__device__ __forceinline__ v4d wide_tile(const double* src, int a, int b) {
+  const double* p = src + 256 * (4 * a + b) + lane_id();
+  return v4d{p[0], p[64], p[128], p[192]};
+}
+
+// Workgroup b of the side path (b < wide_side_wgs(nq)).  smem: WIDE_SMEM.
+__device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) {
+  const int nq = a.nq, ngram = wide_gram_wgs(nq);
+  if (b < ngram) {
+    const int p = b / GRAM_PAIR_SLICES, sl = b % GRAM_PAIR_SLICES;
+    int q, q2;
+    pair_of(p, nq, q, q2);
+    const int nks = (int)(a.L_pad / TILE);
+    const int ks0 = (int)((long long)sl * nks / GRAM_PAIR_SLICES);
+    const int ks1 = (int)((long long)(sl + 1) * nks / GRAM_PAIR_SLICES);
+    const v4i* Xa = a.X + (int64_t)q * 4 * a.L_pad;
+    if (a.mode == 1)
+      gram_w_accumulate<false>(Xa, a.W + (int64_t)q2 * BBP * a.L_pad, (int64_t)BMAX * a.L_pad, ks0, ks1,
+                               (long long*)a.gacc + (int64_t)p * 4096, (int*)smem);
+    else
+      wide_gram_int(Xa, a.X + (int64_t)q2 * 4 * a.L_pad, ks0, ks1, a.gacc + (int64_t)p * 4096, (int*)smem);
+    wide_arrive(a.sync + WIDE_SYNC_GRAM);
+    return;
+  }
+  // the sweep is the launch's critical path: its waves win issue arbitration
+  __builtin_amdgcn_s_setprio(3);
+  __shared__ double shd[NT / 64];
+  __shared__ int sexp[BBP];
+  v2d* Pt = (v2d*)smem;     // tiles of P
+  v2d* Yt = Pt + 2048;      // tiles of A_kj
+  v2d* nbuf = Yt + 2048;
+  const int idx = b - ngram, i = idx / nq, j = idx % nq;
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  const int li = lane & 15, lk = lane >> 4;
+  const int bb = a.bb;
+  wide_await(a.sync + WIDE_SYNC_GRAM, (unsigned)ngram, a.flags);
+  const double unit = a.mode == 1 ? a.hwmax[1] : 1.0;
+  auto gram = [&](int p, int e) {
+    return a.mode == 1 ? (double)load_coherent((const long long*)a.gacc + (int64_t)p * 4096 + e) * unit
+                       : (double)load_coherent(a.gacc + (int64_t)p * 4096 + e);
+  };
+  // trace over the real components, the same arithmetic in every workgroup
+  double dv = 0.0;
+  static_assert(BMAX == NT, "one diagonal entry per thread");
+  if ((int)threadIdx.x < bb) {
+    const int c = threadIdx.x, qc = c / BBP, cl = c % BBP;
+    dv = gram(pair_index(qc, qc, nq), cl * 65);
+    if (a.mode == 2) dv *= a.raw[(int64_t)c * BMAX + c];
+  }
+  // the block of this workgroup, in the accumulator layout
+  v4d acc[4];
+  const int p = i <= j ? pair_index(i, j, nq) : pair_index(j, i, nq);
+  const int e0 = i <= j ? (16 * w + lk) * 64 + li : li * 64 + 16 * w + lk;  // entry of nt = r = 0
+  const int er = i <= j ? 4 * 64 : 4, ent = i <= j ? 16 : 16 * 64;
+  if (a.mode == 1) {
+    const long long* g = (const long long*)a.gacc + (int64_t)p * 4096 + e0;
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[nt][r] = (double)load_coherent(g + nt * ent + r * er) * unit;
+  } else {
+    const int* g = a.gacc + (int64_t)p * 4096 + e0;
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[nt][r] = (double)load_coherent(g + nt * ent + r * er);
+  }
+  const double tr = block_sum_d(dv, shd);
+  const bool zero = tr == 0.0;
+  if (idx == 0 && threadIdx.x == 0) *a.wflag = zero ? 1 : 0;
+  const double ridge = zero ? 0.0 : a.rel * tr / (double)bb;
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int gi = BBP * i + 16 * w + lk + 4 * r, gj = BBP * j + 16 * nt + li;
+      const bool real = gi < bb && gj < bb;
+      double v = real ? acc[nt][r] : 0.0;
+      if (a.mode == 2) v *= real ? a.raw[(int64_t)gi * BMAX + gj] : 0.0;
+      else if (a.raw) a.raw[(int64_t)gi * BMAX + gj] = v;
+      acc[nt][r] = gi == gj ? (real && !zero ? v + ridge : 1.0) : (zero ? 0.0 : v);
+    }
+#pragma unroll 1
+  for (int k = 0; k < nq; ++k) {
+    const bool row = i == k, col = j == k;
+    if (row && col) {
+      // P = A_kk^{-1} (see spd_inverse64)
+      const int bq = bb - BBP * k < BBP ? bb - BBP * k : BBP;
+      const int nb = (bq + 15) >> 4;
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (nt == w && lk + 4 * r == li) {
+            int E = 0;
+            frexp(acc[nt][r], &E);
+            sexp[16 * w + li] = E >> 1;
+          }
+      __syncthreads();
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) {
+        v4d x;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = ldexp(acc[nt][r], -(sexp[16 * w + lk + 4 * r] + sexp[16 * nt + li]));
+        put_tile(Pt + 128 * (4 * w + nt), x);
+      }
+      __syncthreads();
+      sweep_tiles(Pt, nbuf, nb);
+      __syncthreads();
+      v4d P[4];
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) {
+        const v4d y = get_tile(Pt + 128 * (4 * w + nt));
+        const double sg = (nt < nb && w < nb) ? -1.0 : 1.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) P[nt][r] = ldexp(sg * y[r], -(sexp[16 * w + lk + 4 * r] + sexp[16 * nt + li]));
+        acc[nt] = -P[nt];
+      }
+      if (nq > 1) {
+        wide_publish(a.pivot + (int64_t)k * 4096, P);
+        wide_arrive(a.sync + WIDE_SYNC_PIVOT + 32 * k);
+      }
+      __syncthreads();  // Pt and sexp are reused
+      continue;
+    }
+    v4d pa[4];  // A_ki tiles (pb, w): rows of A_ik as A operands
+    if (row) {
+      wide_publish(a.panel + (int64_t)(k * NQMAX + j) * 4096, acc);
+      wide_arrive(a.sync + WIDE_SYNC_PANEL + 32 * k);
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) put_tile(Yt + 128 * (4 * w + nt), acc[nt]);
+    } else {
+      wide_await(a.sync + WIDE_SYNC_PANEL + 32 * k, (unsigned)(nq - 1), a.flags);
+#pragma unroll
+      for (int pb = 0; pb < 4; ++pb) pa[pb] = wide_tile(a.panel + (int64_t)(k * NQMAX + i) * 4096, pb, w);
+      if (!col)
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+          put_tile(Yt + 128 * (4 * w + nt), wide_tile(a.panel + (int64_t)(k * NQMAX + j) * 4096, w, nt));
+    }
+    wide_await(a.sync + WIDE_SYNC_PIVOT + 32 * k, 1u, a.flags);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+      put_tile(Pt + 128 * (4 * w + nt), wide_tile(a.pivot + (int64_t)k * 4096, w, nt));
+    __syncthreads();
+    if (row) {
+      // P A_kj
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) acc[nt] = v4d{};
+#pragma unroll 1
+      for (int pb = 0; pb < 4; ++pb) {
+        const v4d x = get_tile(Pt + 128 * (4 * pb + w));
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) mul_tile(x, get_tile(Yt + 128 * (4 * pb + nt)), acc[nt]);
+      }
+    } else if (col) {
+      // A_ik P
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) acc[nt] = v4d{};
+#pragma unroll
+      for (int pb = 0; pb < 4; ++pb) {
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) mul_tile(pa[pb], get_tile(Pt + 128 * (4 * pb + nt)), acc[nt]);
+        __builtin_amdgcn_sched_barrier(0);  // (registers: not every tile read at once)
+      }
+    } else {
+      // T^T = P A_ki, columns of this wave's row block; then A_ij - T A_kj
+      v4d T[4];
+#pragma unroll
+      for (int pb = 0; pb < 4; ++pb) T[pb] = v4d{};
+#pragma unroll
+      for (int pc = 0; pc < 4; ++pc) {
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb) mul_tile(get_tile(Pt + 128 * (4 * pc + pb)), pa[pc], T[pb]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int pb = 0; pb < 4; ++pb) {
+        T[pb] = -T[pb];
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) mul_tile(T[pb], get_tile(Yt + 128 * (4 * pb + nt)), acc[nt]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();  // Pt and Yt are reused
+  }
+  // G^{-1} = -S; the matrix is symmetric, so element (row, col) of block (i,
+  // j) goes to the place of (col, row) of block (j, i): whole 512-byte lines
+  double* out = a.ginv + (int64_t)(j * NQMAX + i) * 4096;
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int gi = BBP * i + 16 * w + lk + 4 * r, gj = BBP * j + 16 * nt + li;
+      const double v = zero ? ((gi >= bb || gj >= bb) && gi == gj ? 1.0 : 0.0) : -acc[nt][r];
+      out[(nt * 16 + 4 * w + r) * 64 + lane] = v;
+    }
+}
+
+// The side path alone (the joint solve at a block's end, the step entry
+// points).  grid: wide_side_wgs(nq).
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_wide_side(WideSide a) {
+  __shared__ __attribute__((aligned(16))) char smem[WIDE_SMEM];
+  wide_side(a, (int)blockIdx.x, smem);
+}
+
+// Clears the Gram blocks (nclr words) and the arrival words of a side path
+// that has run, split over the workgroups of the calling launch.
+__device__ __forceinline__ void wide_clear(int* gacc, int nclr, unsigned* sync, int wg, int nwg) {
+  const int per = (nclr + nwg - 1) / nwg;
+  const int e1 = per * (wg + 1) < nclr ? per * (wg + 1) : nclr;
+  for (int e = per * wg + (int)threadIdx.x; e < e1; e += (int)blockDim.x) gacc[e] = 0;
+  if (wg == 0)
+    for (int e = threadIdx.x; e < WIDE_SYNC_WORDS; e += (int)blockDim.x) sync[e] = 0u;
+}
+__global__ __launch_bounds__(NT) void k_wide_clear(int* gacc, int nclr, unsigned* sync) {
+  wide_clear(gacc, nclr, sync, (int)blockIdx.x, (int)gridDim.x);
+}
+
+// ---------------------------------------------------------------------------
 // Contractions of a wide block (nq = 2 .. 4 quarters of 64 components): one
 // pass over R for all of them.  A workgroup's four waves convert four K
 // steps of its 32 x 32 residual tiles to digit planes at a time, share them
@@ -1584,13 +1941,23 @@ __device__ __forceinline__ void wide_products(const WidePlanes& sp, int buf, int
 }
 
 // P = U^T R of a wide block, row-group partials as k_vstep's: quarter q at
-// Pp + q gv 64 n_pad.  grid: (n_pad/32 column tiles) x gv.
+// Pp + q gv 64 n_pad; the last of a column tile's gv row groups to arrive
+// (tcnt) replaces row group 0's partials by P (fp64, the exact sum scaled by
+// 2^-cshift), while the side path, the inverse Gram of U, still sweeps.
+// grid: the side path, then (n_pad/32 column tiles) x gv.
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_vstep_wide(
-    const float* __restrict__ R, const v4i* __restrict__ Umf, long long* __restrict__ Pp,
-    const int* __restrict__ cshift, int64_t m_pad, int64_t n_pad, int gv, int nq) {
-  __shared__ WidePlanes sp;
+    const float* __restrict__ R, const v4i* __restrict__ Umf, long long* Pp, const int* __restrict__ cshift,
+    int64_t m_pad, int64_t n_pad, int gv, int nq, unsigned* tcnt, WideSide side) {
+  __shared__ __attribute__((aligned(16))) char smem[WIDE_SMEM];
+  static_assert(sizeof(WidePlanes) <= WIDE_SMEM, "the side path's LDS holds the planes");
+  const int nsd = wide_side_wgs(side.nq);
+  if ((int)blockIdx.x < nsd) {
+    wide_side(side, (int)blockIdx.x, smem);
+    return;
+  }
+  WidePlanes& sp = *(WidePlanes*)smem;
   const int nct = (int)(n_pad / TILE);
-  const int ct = blockIdx.x % nct, g = blockIdx.x / nct;
+  const int ct = ((int)blockIdx.x - nsd) % nct, g = ((int)blockIdx.x - nsd) / nct;
   const int nks = (int)(m_pad / TILE);
   const int ks0 = (int)((long long)g * nks / gv), ks1 = (int)((long long)(g + 1) * nks / gv);
   const int lane = lane_id(), wave = wave_id();
@@ -1646,32 +2013,77 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
       wide_products<false>(sp, buf, 3, a[3], trits(nb + 3), acc);
     }
   }
+  if (wave < nq) {
+    long long* Pg = Pp + ((int64_t)(wave * gv + g) * BBP) * n_pad + (int64_t)ct * TILE;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        store_coherent(Pg + (int64_t)(32 * t + 8 * (r >> 2) + 4 * h + (r & 3)) * n_pad + l32, combine_acc(acc, t, r));
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __shared__ int s_last;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned old = __hip_atomic_fetch_add(tcnt + ct, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = old == (unsigned)(gv - 1);
+  }
+  __syncthreads();
+  if (!s_last) return;
+  if (threadIdx.x == 0) store_coherent(tcnt + ct, 0u);
   if (wave >= nq) return;
-  long long* Pg = Pp + ((int64_t)(wave * gv + g) * BBP) * n_pad + (int64_t)ct * TILE;
+  // lane: columns jp, jp + 1 of components lane / 16 + 4 i of its quarter;
+  // plain loads see the written-through partials (k_vstep)
+  const int jp = 2 * (lane & 15);
+  const int64_t j0 = (int64_t)ct * TILE + jp;
+  const int sh0 = cshift[j0], sh1 = cshift[j0 + 1];
+  long long* base = Pp + ((int64_t)wave * gv * BBP + (lane >> 4)) * n_pad + j0;
+#pragma unroll 1
+  for (int i = 0; i < 16; i += 4) {
+    v2l v[4][GV_MAX];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      Pg[(int64_t)(32 * t + 8 * (r >> 2) + 4 * h + (r & 3)) * n_pad + l32] = combine_acc(acc, t, r);
+      for (int gg = 0; gg < GV_MAX; ++gg)
+        v[u][gg] = *(const v2l*)(base + ((int64_t)(gg < gv ? gg : 0) * BBP + 4 * (i + u)) * n_pad);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      long long s0 = 0, s1 = 0;
+#pragma unroll
+      for (int gg = 0; gg < GV_MAX; ++gg) {
+        s0 += gg < gv ? v[u][gg].x : 0ll;
+        s1 += gg < gv ? v[u][gg].y : 0ll;
+      }
+      *(v2d*)(base + (int64_t)(4 * (i + u)) * n_pad) = v2d{ldexp((double)s0, -sh0), ldexp((double)s1, -sh1)};
+    }
+  }
 }
 
 // Q = R diag(h~) V of a wide block, component-major fp64 by quarters, and
-// the rows' measured bounds, as k_ustep.  grid: row groups of `rows` <= 32
-// rows.  Lane l loads 4 consecutive columns of rows 8 q + l / 8 (whole
+// the rows' measured bounds, as k_ustep; beside it the inverse Gram of V.
+// grid: the side path, then row groups of `rows` <= 32 rows.  Lane l loads 4 consecutive columns of rows 8 q + l / 8 (whole
 // 128-byte row segments per instruction), converts them with their rows'
 // exponents and writes each plane's 4 digits as one word of the operand.
 template <bool WEIGHTED>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_ustep_wide(
     const float* __restrict__ R, const v4i* __restrict__ Vmf, const double* __restrict__ hw, double* __restrict__ Q,
-    float* __restrict__ rowb, int64_t m_pad, int64_t n_pad, int rows, int nq) {
+    float* __restrict__ rowb, int64_t m_pad, int64_t n_pad, int rows, int nq, WideSide side) {
   constexpr int QLD = 34;  // doubles per component row of the output transpose
-  __shared__ union {
+  __shared__ __attribute__((aligned(16))) char smem[WIDE_SMEM];
+  const int nsd = wide_side_wgs(side.nq);
+  if ((int)blockIdx.x < nsd) {
+    wide_side(side, (int)blockIdx.x, smem);
+    return;
+  }
+  union Lds {
     WidePlanes sp;
     double tq[4][32 * QLD];
-  } sm;
+  };
+  static_assert(sizeof(Lds) <= WIDE_SMEM, "the side path's LDS holds the planes");
+  Lds& sm = *(Lds*)smem;
   __shared__ int s_row[TILE];
   __shared__ int s_rmax[4][TILE];
-  const int64_t i0 = (int64_t)blockIdx.x * rows;
+  const int64_t i0 = (int64_t)((int)blockIdx.x - nsd) * rows;
   if (i0 >= m_pad) return;
   const int valid = (int)(m_pad - i0 < rows ? m_pad - i0 : rows);
   const int lane = lane_id(), wave = wave_id();
@@ -1817,7 +2229,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 template <int NH>
 __global__ __launch_bounds__(NT) void k_target_wide(const double* __restrict__ X, int64_t xq,
                                                     const double* __restrict__ ginv, double* __restrict__ Y, int64_t L, int64_t Lp, double* ps,
-                                                    double* pm, int* pi, int nq, int64_t ntmax) {
+                                                    double* pm, int* pi, int nq, int64_t ntmax, int* gacc,
+                                                    int nclr, unsigned* sync) {
+  wide_clear(gacc, nclr, sync, (int)(blockIdx.x + gridDim.x * blockIdx.y), (int)(gridDim.x * gridDim.y));
   // X_q' of the tile as [half][component][16]: the 32 lanes of a read phase
   // (two components) cover all 64 banks
   __shared__ __attribute__((aligned(16))) double Xs[2][NH][BBP][16];
@@ -2571,12 +2985,13 @@ __global__ __launch_bounds__(NT) void k_prep(const float* __restrict__ h, int64_
                                              double* fro2_hist, double* fro2w_hist, int nblk_cap,
                                              unsigned* counters, int* flags, int* gacc, double lam,
                                              unsigned long long* argkey, int* gaccW, long long* gacc64,
-                                             int8_t* __restrict__ hdig, unsigned* vtcnt, unsigned* utcnt, unsigned* gflag) {
+                                             int8_t* __restrict__ hdig, unsigned* vtcnt, unsigned* utcnt, unsigned* gflag, unsigned* wsync) {
   __shared__ float smax[NT / 64];
   __shared__ int sbad[NT / 64];
   for (int64_t e = threadIdx.x; e < n_pad / TILE; e += NT) vtcnt[e] = 0u;
   for (int e = threadIdx.x; e < USTEP_SLOTS; e += NT) utcnt[e] = 0u;
   for (int e = threadIdx.x; e < 2 * FLAG_COPIES * FLAG_STRIDE; e += NT) gflag[e] = 0u;
+  for (int e = threadIdx.x; e < WIDE_SYNC_WORDS; e += NT) wsync[e] = 0u;
   for (int e = threadIdx.x; e < nblk_cap; e += NT) {
     fro2_hist[e] = 0.0;
     fro2w_hist[e] = 0.0;
@@ -3378,379 +3793,14 @@ __global__ void k_set_scales(const double* __restrict__ d, int bb, double* dvec,
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
-// Wide blocks (bb up to BMAX = NQMAX x 64 components, Sec. 2.4): the Gram
-// matrices of Eq. (3) and the matrix of the joint solve of Eq. (4) couple
-// the quarters of a block; they are formed here as BMAX x BMAX fp64 matrices
-// (64 x 64 blocks, quarter pairs q <= q') and inverted by a blocked sweep.
-// ---------------------------------------------------------------------------
-// quarter pair p <-> (q, q') with q <= q' < nq, in row order
-__device__ __forceinline__ void pair_of(int p, int nq, int& q, int& q2) {
-  q = 0;
-  while (p >= nq - q) {
-    p -= nq - q;
-    ++q;
-  }
-  q2 = q + p;
-}
-__host__ __device__ __forceinline__ int pair_index(int q, int q2, int nq) {
-  return q * nq - q * (q - 1) / 2 + (q2 - q);
-}
-
-// Integer Gram blocks X_q^T X_q' of a ternary factor (MFMA-ready layout,
-// quarter q at byte 64 q L_pad) for every pair q <= q' < nq, on int8 MFMA,
-// added into gaccW[pair] with integer atomics (exact, order-free); the
-// sweep's first pivot launch clears gaccW again.
-// grid: npairs x nslice workgroups, workgroup (pair, slice) takes a slice of
-// the K steps; after them, in a V-step (Pp given), n_pad / 64 workgroups per
-// 16 components that replace row group 0's int64 partials of the contraction
-// by P (fp64, the sum of the gv partials scaled by 2^-cshift; each thread
-// reads and writes its own entries only).  The sum needs no inverse, so it
-// runs beside the Gram, once for all quarters.
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_gram_pairs(
-    const v4i* __restrict__ Xmf, int64_t L_pad, int nq, int nslice, int* __restrict__ gaccW,
-    long long* Pp, const int* __restrict__ cshift, int64_t n_pad, int gv) {
-  __shared__ int red[4 * 4096];
-  const int ngram = nq * (nq + 1) / 2 * nslice;
-  if ((int)blockIdx.x >= ngram) {
-    // columns j, j + 1 of components cc + 4 u: the partials of a pair in
-    // flight at once, from clamped row groups (masked in the sum)
-    const int b = (int)blockIdx.x - ngram;
-    const int ncol = (int)((n_pad + 63) / 64);
-    const int64_t j = (int64_t)(b % ncol) * 64 + 2 * (threadIdx.x & 31);
-    if (j >= n_pad) return;
-    const int sh0 = cshift[j], sh1 = cshift[j + 1];
-    const int c0 = 16 * (b / ncol) + (threadIdx.x >> 5);
-    v2l v[2][GV_MAX];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int c = c0 + 8 * u, q = c / BBP;
-#pragma unroll
-      for (int g = 0; g < GV_MAX; ++g)
-        v[u][g] = *(const v2l*)(Pp + (((int64_t)q * gv + (g < gv ? g : 0)) * BBP + c % BBP) * n_pad + j);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      long long s0 = 0, s1 = 0;
-#pragma unroll
-      for (int g = 0; g < GV_MAX; ++g) {
-        s0 += g < gv ? v[u][g].x : 0ll;
-        s1 += g < gv ? v[u][g].y : 0ll;
-      }
-      const int c = c0 + 8 * u;
-      *(v2d*)((double*)Pp + ((int64_t)(c / BBP) * gv * BBP + c % BBP) * n_pad + j) =
-          v2d{ldexp((double)s0, -sh0), ldexp((double)s1, -sh1)};
-    }
-    return;
-  }
-  const int p = blockIdx.x / nslice, sl = blockIdx.x % nslice;
-  int q, q2;
-  pair_of(p, nq, q, q2);
-  const int nks = (int)(L_pad / TILE);
-  const int ks0 = (int)((long long)sl * nks / nslice), ks1 = (int)((long long)(sl + 1) * nks / nslice);
-  const v4i* Xa = Xmf + (int64_t)q * 4 * L_pad;
-  const v4i* Xb = Xmf + (int64_t)q2 * 4 * L_pad;
-  constexpr int KR = 4;
-  const int lane = lane_id(), wave = wave_id();
-  const int h = lane >> 5, l32 = lane & 31;
-  v16i acc00 = {}, acc01 = {}, acc10 = {}, acc11 = {};
-  for (int ks = ks0 + wave; ks < ks1; ks += 4 * KR) {
-    v4i a[KR][2], b[KR][2];
-#pragma unroll
-    for (int u = 0; u < KR; ++u) {
-      const int kk = ks + 4 * u;
-      if (kk < ks1) {
-        a[u][0] = Xa[(int64_t)kk * 128 + lane];
-        a[u][1] = Xa[(int64_t)kk * 128 + 64 + lane];
-        b[u][0] = Xb[(int64_t)kk * 128 + lane];
-        b[u][1] = Xb[(int64_t)kk * 128 + 64 + lane];
-      } else {
-        a[u][0] = a[u][1] = b[u][0] = b[u][1] = v4i{};
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < KR; ++u) {
-      acc00 = mfma_i8(a[u][0], b[u][0], acc00);
-      acc01 = mfma_i8(a[u][0], b[u][1], acc01);
-      acc10 = mfma_i8(a[u][1], b[u][0], acc10);
-      acc11 = mfma_i8(a[u][1], b[u][1], acc11);
-    }
-  }
-  int* mine = red + wave * 4096;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int M = 8 * (r >> 2) + 4 * h + (r & 3);
-    const int N = l32;
-    mine[M * 64 + N] = acc00[r];
-    mine[M * 64 + 32 + N] = acc01[r];
-    mine[(32 + M) * 64 + N] = acc10[r];
-    mine[(32 + M) * 64 + 32 + N] = acc11[r];
-  }
-  __syncthreads();
-  int* g = gaccW + (int64_t)p * 4096;
-  for (int e = threadIdx.x; e < 4096; e += NT) {
-    const int v = red[e] + red[4096 + e] + red[8192 + e] + red[12288 + e];
-    if (v) __hip_atomic_fetch_add(g + e, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
-
-// Weighted Gram blocks V_q^T diag(H) V_q' of V (Sec. 2.5) for every pair
-// q <= q' < nq on int8 MFMA from the digit-scaled planes of V (the
-// arithmetic of gram_w_accumulate), added into g64[pair] (int64 atomics, exact and
-// order-free); the sweep's first pivot launch clears g64 again.
-// grid: npairs x nslice workgroups, workgroup (pair, slice) takes a slice of
-// the K steps.
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_gram_pairs_w(
-    const v4i* __restrict__ Vmf, const int8_t* __restrict__ Wmf, int64_t n_pad, int nq, int nslice,
-    long long* __restrict__ g64) {
-  __shared__ int red[4 * 4096];
-  const int p = blockIdx.x / nslice, sl = blockIdx.x % nslice;
-  int q, q2;
-  pair_of(p, nq, q, q2);
-  const int nks = (int)(n_pad / TILE);
-  const int ks0 = (int)((long long)sl * nks / nslice), ks1 = (int)((long long)(sl + 1) * nks / nslice);
-  gram_w_accumulate<false>(Vmf + (int64_t)q * 4 * n_pad, Wmf + (int64_t)q2 * BBP * n_pad, (int64_t)BMAX * n_pad, ks0,
-                           ks1, g64 + (int64_t)p * 4096, red);
-}
-
-// The matrix to sweep, A (BMAX-stride row-major, nq x nq blocks), from one
-// pair block per workgroup (both triangles):
-//   mode 0: (G + eps I) from the integer Gram blocks gaccW, the raw Gram
-//           also into raw (if given);
-//   mode 1: (G + eps I) from the weighted integer Gram blocks g64 times
-//           their unit (hwmax[1]), the raw Gram into raw;
-//   mode 2: (G_U o G_V + delta I) from gaccW (G_U) and raw (G_V), Eq. (4);
-// with eps or delta = rel * trace / bb over the bb real components and the
-// identity on the padding components.  A zero trace sets wflag[0] (the
-// result is then zero targets, or zero scales) and leaves the identity in A.
-// grid: npairs.
-__global__ __launch_bounds__(NT) void k_wide_prep(int mode, const int* __restrict__ gaccW,
-                                                  const double* __restrict__ hwmax, double* raw, int bb, int nq,
-                                                  double rel, double* __restrict__ A, int* __restrict__ wflag) {
-  __shared__ double shd[NT / 64];
-  const int p = blockIdx.x;
-  int q, q2;
-  pair_of(p, nq, q, q2);
-  // trace over the real components, the same arithmetic in every workgroup
-  double dv = 0.0;
-  const int c = threadIdx.x;  // BMAX == NT: one diagonal entry per thread
-  if (c < bb) {
-    const int qc = c / BBP, cl = c % BBP, pd = pair_index(qc, qc, nq);
-    if (mode == 0) dv = (double)gaccW[(int64_t)pd * 4096 + cl * 65];
-    else if (mode == 1)
-      dv = (double)((const long long*)gaccW)[(int64_t)pd * 4096 + cl * 65] * hwmax[1];
-    else
-      dv = (double)gaccW[(int64_t)pd * 4096 + cl * 65] * raw[(int64_t)c * BMAX + c];
-  }
-  const double tr = block_sum_d(dv, shd);
-  const bool zero = tr == 0.0;
-  if (p == 0 && threadIdx.x == 0) *wflag = zero ? 1 : 0;
-  const double ridge = zero ? 0.0 : rel * tr / (double)bb;
-  // The block's values first, every load issued before any is used (a loop
-  // that stores each value would wait for each load in turn).
-  constexpr int PER = 4096 / NT;
-  double vals[PER];
-  if (mode == 1) {
-    const double unit = hwmax[1];
-    long long gv[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) gv[u] = ((const long long*)gaccW)[(int64_t)p * 4096 + threadIdx.x + NT * u];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) vals[u] = (double)gv[u] * unit;
-  } else if (mode == 2) {
-    int gv[PER];
-    double rv[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = threadIdx.x + NT * u;
-      gv[u] = gaccW[(int64_t)p * 4096 + e];
-      rv[u] = raw[(int64_t)(BBP * q + (e >> 6)) * BMAX + BBP * q2 + (e & 63)];
-    }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) vals[u] = (double)gv[u] * rv[u];
-  } else {
-    int gv[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) gv[u] = gaccW[(int64_t)p * 4096 + threadIdx.x + NT * u];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) vals[u] = (double)gv[u];
-  }
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = threadIdx.x + NT * u;
-    const int r = e >> 6, cc = e & 63;
-    const int gi = BBP * q + r, gj = BBP * q2 + cc;
-    const bool real = gi < bb && gj < bb;
-    double v = vals[u];
-    if (!real) v = 0.0;
-    if (raw && mode != 2) {
-      raw[(int64_t)gi * BMAX + gj] = v;
-      raw[(int64_t)gj * BMAX + gi] = v;
-    }
-    double a = (gi == gj) ? (real && !zero ? v + ridge : 1.0) : (zero ? 0.0 : v);
-    A[(int64_t)gi * BMAX + gj] = a;
-    A[(int64_t)gj * BMAX + gi] = a;
-  }
-}
-
-// C (64 x 64 block of this workgroup, rows 16 w .. of wave w) += X Y for
-// 64 x 64 operands with leading dimensions ldx, ldy, on fp64 MFMA:
-// acc[nt][r] <-> row 16 w + lane / 16 + 4 r, column 16 nt + lane % 16.
-__device__ __forceinline__ void gemm64(const double* X, int64_t ldx, const double* Y, int64_t ldy, v4d (&acc)[4]) {
-  const int lane = lane_id(), w = wave_id();
-  const int li = lane & 15, lk = lane >> 4;
-#pragma unroll 4
-  for (int ks = 0; ks < 16; ++ks) {
-    const double a = X[(int64_t)(16 * w + li) * ldx + 4 * ks + lk];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = mfma_f64(a, Y[(int64_t)(4 * ks + lk) * ldy + 16 * nt + li], acc[nt]);
-  }
-}
-
-// C += X Y for 64 x 64 operands in LDS, both stored K-major: XT[kk][row]
-// (XT = X^T) and Y[kk][col], row strides ldx and ldy (80 doubles: lanes
-// 0..31 of a read then cover all 64 banks); the accumulator layout of
-// gemm64.
-__device__ __forceinline__ void gemm64_kmajor(const double* XT, int ldx, const double* Y, int ldy, v4d (&acc)[4]) {
-  const int lane = lane_id(), w = wave_id();
-  const int li = lane & 15, lk = lane >> 4;
-#pragma unroll 4
-  for (int ks = 0; ks < 16; ++ks) {
-    const double a = XT[(4 * ks + lk) * ldx + 16 * w + li];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = mfma_f64(a, Y[(4 * ks + lk) * ldy + 16 * nt + li], acc[nt]);
-  }
-}
-
-// One step of the blocked sweep as one launch: every workgroup inverts the
-// pivot block itself (the same arithmetic in each, so all hold the same
-// P = A_kk^{-1}) and updates its own block, A -> B:
-//   B_kk = -P, B_kj = P A_kj, B_ik = A_ik P, B_ij = A_ij - (A_ik P) A_kj.
-// The swept matrix stays symmetric, so A_ik^T is the stored block A_ki and
-// P^T = P.  All operand blocks are loaded into LDS at once (one memory
-// latency) and the products read LDS.  nk: 4 x 4 pivots holding real
-// components; step 0 also clears the integer Gram blocks (nclear entries,
-// split over the workgroups) for the next accumulation.  grid: nq x nq.
-constexpr int SWEEP_LD = 80;
-__global__ __launch_bounds__(NT) void k_wide_step(const double* __restrict__ A, double* __restrict__ B, int k,
-                                                  int nq, int nk, int* gaccW, int nclear) {
-  __shared__ double Gs[4096];                   // the pivot block, then P (row stride 64)
-  __shared__ double pbuf[1024];
-  __shared__ double XT[BBP * SWEEP_LD];         // A_ki = A_ik^T, then (A_ik P)^T
-  __shared__ double Ys[BBP * SWEEP_LD];         // A_kj
-  const int i = blockIdx.x / nq, j = blockIdx.x % nq;
-  const int lane = lane_id(), w = wave_id();
-  const int li = lane & 15, lk = lane >> 4;
-  if (nclear) {
-    const int per = (nclear + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int e0 = per * (int)blockIdx.x, e1 = e0 + per < nclear ? e0 + per : nclear;
-    for (int e = e0 + threadIdx.x; e < e1; e += NT) gaccW[e] = 0;
-  }
-  const double* Akk = A + (int64_t)BBP * k * BMAX + BBP * k;
-  const double* Aki = A + (int64_t)BBP * k * BMAX + BBP * i;
-  const double* Akj = A + (int64_t)BBP * k * BMAX + BBP * j;
-  const double* Aij = A + (int64_t)BBP * i * BMAX + BBP * j;
-  double* Bij = B + (int64_t)BBP * i * BMAX + BBP * j;
-  const bool gen = i != k && j != k;
-  // A_ij for the general blocks, in the accumulator layout (issued first)
-  double aij[4][4];
-  if (gen) {
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) aij[nt][r] = Aij[(int64_t)(16 * w + lk + 4 * r) * BMAX + 16 * nt + li];
-  }
-  // every load of the three blocks issued before the first LDS store (a
-  // loop that stores each value would wait for each load in turn); blocks
-  // a workgroup does not use read the pivot block again
-  constexpr int PER = 4096 / NT;
-  const double* Xsrc = (j == k || gen) ? Aki : Akk;
-  const double* Ysrc = (i == k || gen) ? Akj : Akk;
-  double gv[PER], xv[PER], yv[PER];
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int e = threadIdx.x + NT * q;
-    const int64_t o = (int64_t)(e >> 6) * BMAX + (e & 63);
-    gv[q] = Akk[o];
-    xv[q] = Xsrc[o];
-    yv[q] = Ysrc[o];
-  }
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int e = threadIdx.x + NT * q;
-    const int r = e >> 6, c = e & 63;
-    Gs[e] = gv[q];
-    XT[r * SWEEP_LD + c] = xv[q];
-    Ys[r * SWEEP_LD + c] = yv[q];
-  }
-  __syncthreads();
-  spd_inverse64(Gs, pbuf, nk);  // Gs = P (ends with a barrier)
-  v4d acc[4] = {v4d{}, v4d{}, v4d{}, v4d{}};
-  double sgn = 1.0;
-  if (i == k && j == k) {
-    for (int e = threadIdx.x; e < 4096; e += NT) Bij[(int64_t)(e >> 6) * BMAX + (e & 63)] = -Gs[e];
-    return;
-  } else if (i == k) {
-    gemm64_kmajor(Gs, BBP, Ys, SWEEP_LD, acc);  // P A_kj (P^T = P)
-  } else if (j == k) {
-    gemm64_kmajor(XT, SWEEP_LD, Gs, BBP, acc);  // A_ik P
-  } else {
-    gemm64_kmajor(XT, SWEEP_LD, Gs, BBP, acc);  // T = A_ik P
-    __syncthreads();                            // every wave is done with A_ki
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) XT[(16 * nt + li) * SWEEP_LD + 16 * w + lk + 4 * r] = acc[nt][r];  // T^T
-    __syncthreads();
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = v4d{};
-    gemm64_kmajor(XT, SWEEP_LD, Ys, SWEEP_LD, acc);
-    sgn = -1.0;
-  }
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t o = (int64_t)(16 * w + lk + 4 * r) * BMAX + 16 * nt + li;
-      Bij[o] = (sgn < 0.0 ? aij[nt][r] : 0.0) + sgn * acc[nt][r];
-    }
-}
-
-// G^{-1} = -S (S: the fully swept matrix) into nq x nq blocks in the fp64
-// MFMA operand order of the target kernels (block (q, q') at
-// ginvW + (q NQMAX + q') 4096); with zero trace (wflag) the inverse is zero
-// on the real components and the identity on the padding.  grid: nq x nq.
-__global__ __launch_bounds__(NT) void k_wide_ginv(const double* __restrict__ S, int nq, int bb,
-                                                  const int* __restrict__ wflag, double* __restrict__ ginvW) {
-  const int i = blockIdx.x / nq, j = blockIdx.x % nq;
-  const bool zero = *wflag != 0;
-  double* out = ginvW + (int64_t)(i * NQMAX + j) * 4096;
-  constexpr int PER = 4096 / NT;
-  double sv[PER];  // every load before the first store
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = threadIdx.x + NT * u;
-    sv[u] = S[(int64_t)(BBP * i + (e >> 6)) * BMAX + BBP * j + (e & 63)];
-  }
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = threadIdx.x + NT * u;
-    const int r = e >> 6, c = e & 63;
-    const int gi = BBP * i + r, gj = BBP * j + c;
-    double v;
-    if (zero) v = (gi >= bb || gj >= bb) ? (gi == gj ? 1.0 : 0.0) : 0.0;
-    else v = -sv[u];
-    out[ginv_index(r, c)] = v;
-  }
-}
-
-// Joint scales of a wide block, d = M^{-1} g (Eq. (4)) with M^{-1} = -S and
-// g_c = diag(U^T Q)_c (the per-split partial sums in split order); zero
-// trace: d = 0.  d into dvec, dF (fp32) and D (the block's output).
-// One workgroup; row c of the product by thread c (columns in order).
-__global__ __launch_bounds__(NT) void k_wide_scales(const double* __restrict__ S, const double* __restrict__ gvec,
+// Joint scales of a wide block, d = M^{-1} g (Eq. (4)) with M^{-1} in blocks
+// (k_wide_side) and g_c = diag(U^T Q)_c (the per-split partial sums in split
+// order); zero trace: d = 0.  d into dvec, dF (fp32) and D (the block's
+// output).  One workgroup; row c of the product by thread c (columns in
+// order).  Also clears the side path's Gram blocks and arrival words.
+__global__ __launch_bounds__(NT) void k_wide_scales(const double* __restrict__ ginv, const double* __restrict__ gvec,
                                                     int bb, const int* __restrict__ wflag, double* dvec, float* dF,
-                                                    float* Dout) {
+                                                    float* Dout, int* gacc, int nclr, unsigned* sync) {
   __shared__ double g[BMAX];
   const int c = threadIdx.x;  // BMAX == NT
   double gc = 0.0;
@@ -3758,10 +3808,13 @@ __global__ __launch_bounds__(NT) void k_wide_scales(const double* __restrict__ S
 #pragma unroll
     for (int k = 0; k < TERN_SPLIT_MAX; ++k) gc += gvec[c * TERN_SPLIT_MAX + k];
   g[c] = gc;
+  wide_clear(gacc, nclr, sync, 0, 1);
   __syncthreads();
   double d = 0.0;
   if (c < bb && *wflag == 0) {
-    for (int c2 = 0; c2 < bb; ++c2) d += -S[(int64_t)c * BMAX + c2] * g[c2];
+    const double* row = ginv + (int64_t)(c / BBP) * NQMAX * 4096;
+#pragma unroll 8
+    for (int c2 = 0; c2 < bb; ++c2) d += row[(c2 / BBP) * 4096 + ginv_index(c % BBP, c2 % BBP)] * g[c2];
   }
   dvec[c] = d;
   dF[c] = (float)d;
@@ -3778,7 +3831,7 @@ static inline unsigned grid_for(int64_t total) {
 hipError_t launch_prep(const Ws& w, const float* h, hipStream_t s, double lam) {
   hipLaunchKernelGGL(k_prep, dim3(1), dim3(NT), 0, s, h, w.n, w.n_pad, w.hw, w.hwmax, w.fro2_hist,
                      w.fro2w_hist, w.nblk_cap, w.counters, w.flags, w.gacc, lam, w.argkey, w.gaccW, w.gacc64,
-                     w.hdig, w.vtcnt, w.utcnt, w.gflag);
+                     w.hdig, w.vtcnt, w.utcnt, w.gflag, w.wsync);
   return hipGetLastError();
 }
 
@@ -3887,79 +3940,47 @@ hipError_t launch_ustep(const Ws& w, int blk, int bb, double tau, bool weighted,
 // ---- wide blocks (nq = ceil(bb / 64) > 1 quarters) ----
 static int nq_of(int bb) { return (bb + BBP - 1) / BBP; }
 static int bb_of_quarter(int bb, int q) { return bb - BBP * q < BBP ? bb - BBP * q : BBP; }
-constexpr int GRAM_PAIR_SLICES = 16;  // K slices per quarter pair of the integer Gram
-
-// Blocked sweep of the matrix prepared in wA0 (nq quarters): one launch
-// per pivot block (k_wide_step: every workgroup inverts the pivot and
-// updates its block); *out receives the buffer holding -A^{-1}.  The first
-// step clears the integer Gram blocks.
-static hipError_t wide_sweep(const Ws& w, int bb, hipStream_t s, const double** out, bool clear64 = false) {
-  const int nq = nq_of(bb), npairs = nq * (nq + 1) / 2;
-  const int nclear = (clear64 ? 2 : 1) * npairs * 4096;  // int32 words of the Gram blocks used
-  double* A = w.wA0;
-  double* B = w.wA1;
-  for (int k = 0; k < nq; ++k) {
-    const int bq = bb_of_quarter(bb, k);
-    hipLaunchKernelGGL(k_wide_step, dim3((unsigned)(nq * nq)), dim3(NT), 0, s, (const double*)A, B, k, nq,
-                       (bq + 3) / 4, w.gaccW, k == 0 ? nclear : 0);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    double* t = A;
-    A = B;
-    B = t;
-  }
-  *out = A;
-  return hipSuccess;
+// The side path's arguments: the inverse Gram of U (which = 0) or V (which =
+// 1, weighted with h~ when `weighted`; its raw Gram is kept in gramVW for
+// the joint solve).
+static WideSide wide_side_args(const Ws& w, int which, bool weighted, int bb) {
+  WideSide a{};
+  a.X = (const v4i*)(which ? w.Vmf : w.Umf);
+  a.W = (const int8_t*)w.Wmf;
+  a.L_pad = which ? w.n_pad : w.m_pad;
+  a.nq = nq_of(bb);
+  a.bb = bb;
+  a.mode = which && weighted ? 1 : 0;
+  a.gacc = w.gaccW;
+  a.hwmax = w.hwmax;
+  a.raw = which ? w.gramVW : nullptr;
+  a.rel = EXTERND_RIDGE_REL;
+  a.panel = w.wA0;
+  a.pivot = w.wA1;
+  a.ginv = which ? w.ginvVW : w.ginvUW;
+  a.wflag = w.wflag;
+  a.sync = w.wsync;
+  a.flags = w.flags;
+  return a;
 }
-
-// (X^T diag(h~) X + eps I)^{-1} of the block's U (which = 0) or V (which = 1,
-// weighted with h~ when `weighted`) into ginvUW / ginvVW; for V the raw Gram
-// is kept in gramVW for the joint solve.
-static hipError_t wide_gram_inverse(const Ws& w, int which, bool weighted, int bb, hipStream_t s) {
-  static_assert(BMAX == NT, "one diagonal entry per thread in the wide preparation");
-  const int nq = nq_of(bb), npairs = nq * (nq + 1) / 2;
-  hipError_t e;
-  if (which == 1 && weighted) {
-    hipLaunchKernelGGL(k_gram_pairs_w, dim3((unsigned)(npairs * GRAM_PAIR_SLICES)), dim3(NT), 0, s,
-                       (const v4i*)w.Vmf, (const int8_t*)w.Wmf, w.n_pad, nq, GRAM_PAIR_SLICES, (long long*)w.gaccW);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wide_prep, dim3((unsigned)npairs), dim3(NT), 0, s, 1, (const int*)w.gaccW,
-                       (const double*)w.hwmax, w.gramVW, bb, nq, EXTERND_RIDGE_REL, w.wA0, w.wflag);
-  } else {
-    const v4i* X = (const v4i*)(which ? w.Vmf : w.Umf);
-    const unsigned nsum = which ? 0u : (unsigned)((w.n_pad + 63) / 64 * (nq * BBP / 16));
-    hipLaunchKernelGGL(k_gram_pairs, dim3((unsigned)(npairs * GRAM_PAIR_SLICES) + nsum), dim3(NT), 0, s, X,
-                       which ? w.n_pad : w.m_pad, nq, GRAM_PAIR_SLICES, w.gaccW, w.Pp, (const int*)w.cshift,
-                       w.n_pad, w.gv);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wide_prep, dim3((unsigned)npairs), dim3(NT), 0, s, 0, (const int*)w.gaccW,
-                       (const double*)w.hwmax, which ? w.gramVW : (double*)nullptr, bb, nq, EXTERND_RIDGE_REL,
-                       w.wA0, w.wflag);
-  }
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const double* S = nullptr;
-  e = wide_sweep(w, bb, s, &S, which == 1 && weighted);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_wide_ginv, dim3((unsigned)(nq * nq)), dim3(NT), 0, s, S, nq, bb, (const int*)w.wflag,
-                     which ? w.ginvVW : w.ginvUW);
-  return hipGetLastError();
+// int32 words of the Gram blocks that a side path used
+static int wide_clear_words(int bb, bool weighted) {
+  const int nq = nq_of(bb);
+  return (weighted ? 2 : 1) * nq * (nq + 1) / 2 * 4096;
 }
 
 hipError_t launch_vstep_wide(const Ws& w, int blk, int bb, double tau, hipStream_t s, Timer* tm, bool weighted) {
   const int nq = nq_of(bb);
   hipError_t e;
-  EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_VSTEP, k_vstep_wide, dim3((unsigned)((w.n_pad / TILE) * w.gv)), dim3(NT), 0,
-                       s, w.R, (const v4i*)w.Umf, w.Pp, (const int*)w.cshift, w.m_pad, w.n_pad, w.gv, nq);
+  EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_VSTEP, k_vstep_wide,
+                       dim3((unsigned)(wide_side_wgs(nq) + (w.n_pad / TILE) * w.gv)), dim3(NT), 0, s, w.R,
+                       (const v4i*)w.Umf, w.Pp, (const int*)w.cshift, w.m_pad, w.n_pad, w.gv, nq, w.vtcnt,
+                       wide_side_args(w, 0, false, bb));
   e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = wide_gram_inverse(w, 0, false, bb, s);
   if (e != hipSuccess) return e;
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_VTARGET, k_target_wide<1>, dim3((unsigned)(w.n_pad / 16), (unsigned)nq),
                        dim3(NT), 0, s, (const double*)w.Pp, (int64_t)BBP * w.gv * w.n_pad, (const double*)w.ginvUW, w.Y, w.n, w.n_pad, w.tps, w.tpm,
-                       w.tpi, nq, w.ntmax);
+                       w.tpi, nq, w.ntmax, w.gaccW, wide_clear_words(bb, false), w.wsync);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_TERNV, k_tern_v, dim3(BBP * w.nsv, (unsigned)nq), dim3(NT), 0, s,
@@ -3998,21 +4019,21 @@ hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weig
     if (e != hipSuccess) return e;
     q0 = 1;
   }
+  const WideSide side = wide_side_args(w, 1, weighted, bb);
+  const unsigned nsd = (unsigned)wide_side_wgs(nq);
   const v4i* Vq = (const v4i*)(w.Vmf + (int64_t)BBP * q0 * w.n_pad);
   double* Qq = w.Q + (int64_t)BBP * q0 * w.m_pad;
   if (weighted)
-    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, k_ustep_wide<true>, dim3(nrow), dim3(NT), 0, s, w.R, Vq,
-                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows_wide, nq - q0);
+    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, k_ustep_wide<true>, dim3(nsd + nrow), dim3(NT), 0, s, w.R, Vq,
+                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows_wide, nq - q0, side);
   else
-    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, k_ustep_wide<false>, dim3(nrow), dim3(NT), 0, s, w.R, Vq,
-                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows_wide, nq - q0);
+    EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_USTEP, k_ustep_wide<false>, dim3(nsd + nrow), dim3(NT), 0, s, w.R, Vq,
+                         (const double*)w.hw, Qq, w.rowb, w.m_pad, w.n_pad, w.urows_wide, nq - q0, side);
   e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = wide_gram_inverse(w, 1, weighted, bb, s);
   if (e != hipSuccess) return e;
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_UTARGET, k_target_wide<2>, dim3((unsigned)(w.m_pad / TILE), (unsigned)nq),
                        dim3(NT), 0, s, (const double*)w.Q, (int64_t)BBP * w.m_pad, (const double*)w.ginvVW, w.Z, w.m, w.m_pad, w.tps, w.tpm,
-                       w.tpi, nq, w.ntmax);
+                       w.tpi, nq, w.ntmax, w.gaccW, wide_clear_words(bb, weighted), w.wsync);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   EXTERND_LAUNCH_TIMED(tm, EXTERND_KCLASS_TERNU, k_tern_u, dim3(BBP * w.nsu, (unsigned)nq), dim3(NT), 0, s,
@@ -4025,27 +4046,26 @@ hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weig
 // The raw V^T H V of a wide block into gramVW (the step entry point of the
 // joint solve; the factorization leaves it from its last U-step).
 hipError_t launch_gram_wide_raw(const Ws& w, int bb, bool weighted, hipStream_t s) {
-  return wide_gram_inverse(w, 1, weighted, bb, s);
+  const WideSide a = wide_side_args(w, 1, weighted, bb);
+  hipLaunchKernelGGL(k_wide_side, dim3((unsigned)wide_side_wgs(a.nq)), dim3(NT), 0, s, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_wide_clear, dim3(16), dim3(NT), 0, s, w.gaccW, wide_clear_words(bb, weighted), w.wsync);
+  return hipGetLastError();
 }
 
 // Joint scales of a wide block (Eq. (4)): [(U^T U) o (V^T H V) + delta I]
 // d = g with the raw V^T H V of the last U-step, d into dvec, dF and D_block.
 hipError_t launch_scale_wide(const Ws& w, int bb, float* D_block, hipStream_t s) {
-  const int nq = nq_of(bb), npairs = nq * (nq + 1) / 2;
-  hipLaunchKernelGGL(k_gram_pairs, dim3((unsigned)(npairs * GRAM_PAIR_SLICES)), dim3(NT), 0, s, (const v4i*)w.Umf,
-                     w.m_pad, nq, GRAM_PAIR_SLICES, w.gaccW, (long long*)nullptr, (const int*)nullptr,
-                     (int64_t)0, 0);
-  hipError_t e = hipGetLastError();
+  WideSide a = wide_side_args(w, 0, false, bb);
+  a.mode = 2;
+  a.raw = w.gramVW;
+  a.rel = EXTERND_SCALE_GUARD_REL;
+  hipLaunchKernelGGL(k_wide_side, dim3((unsigned)wide_side_wgs(a.nq)), dim3(NT), 0, s, a);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_wide_prep, dim3((unsigned)npairs), dim3(NT), 0, s, 2, (const int*)w.gaccW,
-                     (const double*)nullptr, w.gramVW, bb, nq, EXTERND_SCALE_GUARD_REL, w.wA0, w.wflag);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const double* S = nullptr;
-  e = wide_sweep(w, bb, s, &S);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_wide_scales, dim3(1), dim3(NT), 0, s, S, (const double*)w.gvec, bb, (const int*)w.wflag,
-                     w.dvec, w.dF, D_block);
+  hipLaunchKernelGGL(k_wide_scales, dim3(1), dim3(NT), 0, s, (const double*)a.ginv, (const double*)w.gvec, bb,
+                     (const int*)w.wflag, w.dvec, w.dF, D_block, w.gaccW, wide_clear_words(bb, false), w.wsync);
   return hipGetLastError();
 }
 
