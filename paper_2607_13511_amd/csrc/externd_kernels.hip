@@ -1599,7 +1599,7 @@ struct WideSide {
   unsigned* sync;        // WIDE_SYNC_WORDS, zero at the start; cleared by a later launch
   int* flags;
 };
-constexpr int GRAM_PAIR_SLICES = 16;  // K slices per quarter pair of the Gram
+constexpr int GRAM_PAIR_SLICES = 8;  // K slices per quarter pair of the Gram (16: 1 us slower, twice the atomics)
 // arrival words on lines of their own: Gram workgroups, panels of step k, pivot of step k
 constexpr int WIDE_SYNC_GRAM = 0, WIDE_SYNC_PANEL = 32, WIDE_SYNC_PIVOT = 32 * (1 + NQMAX);
 constexpr int WIDE_SMEM = 2 * 4096 * 8 + 512 * 8;  // LDS bytes of the side path
@@ -1714,9 +1714,6 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
   __builtin_amdgcn_s_setprio(3);
   __shared__ double shd[NT / 64];
   __shared__ int sexp[BBP];
-  v2d* Pt = (v2d*)smem;     // tiles of P
-  v2d* Yt = Pt + 2048;      // tiles of A_kj
-  v2d* nbuf = Yt + 2048;
   const int idx = b - ngram, i = idx / nq, j = idx % nq;
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const int li = lane & 15, lk = lane >> 4;
@@ -1771,6 +1768,16 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
 #pragma unroll 1
   for (int k = 0; k < nq; ++k) {
     const bool row = i == k, col = j == k;
+    // an offset of zero that the compiler cannot see through: hoisted out of
+    // the loop, the addresses below would take the registers of the sweep
+    // (spilled, and every reload waits for the stores in flight)
+    unsigned z = 0;
+    asm volatile("" : "+v"(z));
+    v2d* Pt = (v2d*)smem + z;  // tiles of P
+    v2d* Yt = Pt + 2048;       // tiles of A_kj
+    v2d* nbuf = Yt + 2048;
+    double* panel = a.panel + (int64_t)k * NQMAX * 4096 + z;
+    double* pivot = a.pivot + (int64_t)k * 4096 + z;
     if (row && col) {
       // P = A_kk^{-1} (see spd_inverse64)
       const int bq = bb - BBP * k < BBP ? bb - BBP * k : BBP;
@@ -1805,7 +1812,7 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
         acc[nt] = -P[nt];
       }
       if (nq > 1) {
-        wide_publish(a.pivot + (int64_t)k * 4096, P);
+        wide_publish(pivot, P);
         wide_arrive(a.sync + WIDE_SYNC_PIVOT + 32 * k);
       }
       __syncthreads();  // Pt and sexp are reused
@@ -1813,23 +1820,23 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
     }
     v4d pa[4];  // A_ki tiles (pb, w): rows of A_ik as A operands
     if (row) {
-      wide_publish(a.panel + (int64_t)(k * NQMAX + j) * 4096, acc);
+      wide_publish(panel + j * 4096, acc);
       wide_arrive(a.sync + WIDE_SYNC_PANEL + 32 * k);
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) put_tile(Yt + 128 * (4 * w + nt), acc[nt]);
     } else {
       wide_await(a.sync + WIDE_SYNC_PANEL + 32 * k, (unsigned)(nq - 1), a.flags);
 #pragma unroll
-      for (int pb = 0; pb < 4; ++pb) pa[pb] = wide_tile(a.panel + (int64_t)(k * NQMAX + i) * 4096, pb, w);
+      for (int pb = 0; pb < 4; ++pb) pa[pb] = wide_tile(panel + i * 4096, pb, w);
       if (!col)
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt)
-          put_tile(Yt + 128 * (4 * w + nt), wide_tile(a.panel + (int64_t)(k * NQMAX + j) * 4096, w, nt));
+          put_tile(Yt + 128 * (4 * w + nt), wide_tile(panel + j * 4096, w, nt));
     }
     wide_await(a.sync + WIDE_SYNC_PIVOT + 32 * k, 1u, a.flags);
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
-      put_tile(Pt + 128 * (4 * w + nt), wide_tile(a.pivot + (int64_t)k * 4096, w, nt));
+      put_tile(Pt + 128 * (4 * w + nt), wide_tile(pivot, w, nt));
     __syncthreads();
     if (row) {
       // P A_kj
