@@ -239,7 +239,10 @@ int externd_factorize_refined(const float* A, int64_t m, int64_t n, double mu, d
  *    that of the two conversions and the final rounding: at most
  *    u |y| + 2^-46 [ (|B| (|D| (|C| 1))) max|x| + (|B| 1) max|D| sum|x| ]
  *    per output, u = 2^-24 (entries of x within 2^22 of max |x| convert
- *    exactly).  A NaN or infinite entry of x or D makes every output NaN.
+ *    exactly).  With n or k above 10240 t is rounded to fp32 first, its
+ *    scale from max |t|: u (|y| + |B| |t|) + 2^-46 [ (|B| (|D| (|C| 1)))
+ *    max|x| + (|B| 1) max|t| ].  A NaN or infinite entry of x or D makes
+ *    every output NaN.
  *  - Otherwise one vector runs on fp32 FMA and two or more on bf16 matrix
  *    cores with exact operands (trits are exact in bf16; every fp32 vector
  *    entry is split exactly into three bf16 parts), with fp32 sums: at most
@@ -257,8 +260,7 @@ int externd_factorize_refined(const float* A, int64_t m, int64_t n, double mu, d
  *  workspace  device, >= externd_apply_workspace_bytes(m, n, k, nb) bytes,
  *             256-byte aligned.  nb = 1: the intermediate diag(D) C x
  *             (n, k <= 10240: its six 8-bit digit planes, 1536 bytes per
- *             256 entries, and an exponent word; n, k <= 65536: those of x
- *             too; else 4 k bytes).  nb >= 2: its bf16 parts (6 nb k bytes) and
+ *             256 entries, and an exponent word; else 4 k bytes).  nb >= 2: its bf16 parts (6 nb k bytes) and
  *             partial sums over slices of the contracted dimensions (at
  *             most nb max(n, m) k / 32 bytes, rounded up to whole row
  *             groups).

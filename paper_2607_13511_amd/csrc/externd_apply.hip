@@ -9,7 +9,7 @@
 //
 // One vector (a matrix-vector product): integer matrix cores, with the
 // vector's digit planes in LDS (k_gemv_c, k_gemv_b) or, beyond 10240
-// entries, brought there by segments (k_gemv_x, k_gemv_long).  Beyond 65536
+// entries, brought there by segments (k_gemv_long).  Beyond 65536
 // entries k_apply_vec_c then k_apply_vec_b:
 // fp32 FMA on the vector ALUs.  The signed 2-bit field extract (v_bfe_i32)
 // of a code is the trit itself (01 -> 1, 11 -> -1, 00 -> 0).  A workgroup
@@ -876,102 +876,75 @@ __global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void
 
 // ---- one vector, n or k beyond GV_MAX_LEN (both at most GV_LONG_MAX) ----
 //
-// The same arithmetic, with the vector's digit planes in memory and brought
-// into LDS a segment of GV_MAX_SS super-steps at a time.  x is converted
-// once, by a launch of its own (k_gemv_x), as the planes no longer fit a
-// workgroup; then the two sides are the same kernel.  Bound by the memory's
-// read of the trits: 8192 x 28672, k = 20480 (189 MB) takes 66 us; fp32
-// FMA on decoded trits, one byte a lane, was bound by the decode at 112 us.
+// The same integer sums, with the vector's digit planes brought into LDS a
+// segment of GV_MAX_SS super-steps at a time; the intermediate t is fp32 in
+// the workspace, and both sides are one kernel.  Bound by the memory's read
+// of the trits: 8192 x 28672, k = 20480 (189 MB) takes 68 us; fp32 FMA on
+// decoded trits, one byte a lane, was bound by the decode at 112 us.
 constexpr int64_t GV_LONG_MAX = 65536;  // int64 sums of 48-bit entries stay below 2^63
 
-// X's digit planes XT (256 nss components, zero past n) and the exponents
-// sX[0] = x's, sX[1] = t's (GV_NONFINITE for a non-finite x or D).  Every
-// workgroup forms the statistics of all of x and D with the same arithmetic
-// and converts GV_NT components.  grid: ceil(256 nss / GV_NT).
-__global__ __launch_bounds__(GV_NT) void k_gemv_x(const float* __restrict__ X, const float* __restrict__ D, int64_t n,
-                                                  int64_t k, int nss, uint8_t* __restrict__ XT,
-                                                  int* __restrict__ sX) {
-  __shared__ double sh[3 * (GV_NT / 64)];
-  const int tid = threadIdx.x;
-  double sx = 0.0, mx = 0.0, md = 0.0;
-  bool bad = false;
-  // four entries a load (any alignment), eight loads of either vector in
-  // flight: the latency of a few rounds is the launch's time
-  constexpr int U = 8;
-  const int64_t n4 = n >> 2, k4 = k >> 2;
-  for (int64_t c0 = tid; c0 < (n4 > k4 ? n4 : k4); c0 += U * GV_NT) {
-    float v[U][4], d[U][4];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t cx = c0 + u * GV_NT, cd = c0 + u * GV_NT;
-      if (n4 > 0) __builtin_memcpy(v[u], X + 4 * (cx < n4 ? cx : 0), 16);
-      if (k4 > 0) __builtin_memcpy(d[u], D + 4 * (cd < k4 ? cd : 0), 16);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const double a = c0 + u * GV_NT < n4 ? fabs((double)v[u][e]) : 0.0;
-        const double b = c0 + u * GV_NT < k4 ? fabs((double)d[u][e]) : 0.0;
-        bad |= !(a <= 1.0e300) || !(b <= 1.0e300);
-        sx += a;
-        mx = fmax(mx, a);
-        md = fmax(md, b);
-      }
-  }
-  if (tid < 3) {  // the entries past the last whole four
-    const double a = 4 * n4 + tid < n ? fabs((double)X[4 * n4 + tid]) : 0.0;
-    const double b = 4 * k4 + tid < k ? fabs((double)D[4 * k4 + tid]) : 0.0;
-    bad |= !(a <= 1.0e300) || !(b <= 1.0e300);
-    sx += a;
-    mx = fmax(mx, a);
-    md = fmax(md, b);
-  }
-  if (bad) mx = INFINITY;
-  gv_sum_max2(sx, mx, md, sh);
-  const bool finite = mx < INFINITY;
-  const int s_x = gv_shift(mx);
-  const int64_t c = (int64_t)blockIdx.x * GV_NT + tid;
-  if (c < (int64_t)nss * GV_SS) {
-    const float x = (c < n && finite) ? X[c] : 0.0f;
-    int8_t d[GV_PLANES];
-    gv_digits((long long)rint(ldexp((double)x, s_x)), d);
-#pragma unroll
-    for (int p = 0; p < GV_PLANES; ++p) XT[gv_digit_offset(c, p)] = (uint8_t)d[p];
-  }
-  if (blockIdx.x == 0 && tid == 0) {
-    sX[0] = s_x;
-    sX[1] = finite ? gv_shift(md * sx) : GV_NONFINITE;
-  }
-}
-
-// CSIDE: T = the digit planes of diag(D) (P v) (256 nss_t components, zero
-// past the rows), exponent s[1]; else Y = P v.  v: the digit planes V of len
-// components, exponent s[CSIDE ? 0 : 1].  grid: ceil(rows / GV_ROWS).
-template <bool ALIGNED, bool CSIDE>
+// dst[i] = scale_i sum_c P_ic v_c (scale: fp32 per row, or null).  Every
+// workgroup forms max |v| itself (the same value in each), which fixes the
+// exponent; a non-finite entry makes every result NaN.  grid: ceil(rows /
+// GV_ROWS).
+template <bool ALIGNED>
 __global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void k_gemv_long(
-    const uint8_t* __restrict__ P, int64_t rows, int64_t len, const uint8_t* __restrict__ V,
-    const int* __restrict__ s, const float* __restrict__ D, int nss_t, uint8_t* __restrict__ T,
-    float* __restrict__ Y) {
+    const uint8_t* __restrict__ P, int64_t rows, int64_t len, const float* __restrict__ V,
+    const float* __restrict__ scale, float* __restrict__ dst) {
   __shared__ __attribute__((aligned(16))) uint8_t dig[GV_MAX_SS * GV_SSB];
   __shared__ __attribute__((aligned(16))) uint8_t zero16[16];
   __shared__ int xch[GV_NT / 64][64][4];
+  __shared__ float shm[GV_NT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int nss = (int)((len + GV_SS - 1) / GV_SS);
   const int64_t rb = (len + 3) >> 2;
   const int64_t r0 = (int64_t)blockIdx.x * GV_ROWS;
-  const int s_v = s[CSIDE ? 0 : 1], s_t = s[1];
   if (tid < 4) ((int*)zero16)[tid] = 0;
+  // max |v| as the largest bit pattern (Inf and NaN above every number):
+  // four entries a load (any alignment), eight loads in flight
+  unsigned mb = 0u;
+  {
+    constexpr int U = 8;
+    const int64_t n4 = len >> 2;
+    for (int64_t c0 = tid; c0 < n4; c0 += U * GV_NT) {
+      unsigned v[U][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u) __builtin_memcpy(v[u], V + 4 * (c0 + u * GV_NT < n4 ? c0 + u * GV_NT : c0), 16);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mb = max(mb, v[u][e] & 0x7fffffffu);
+    }
+    if (4 * n4 + tid < len) mb = max(mb, __float_as_uint(V[4 * n4 + tid]) & 0x7fffffffu);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mb = max(mb, (unsigned)__shfl_xor((int)mb, o, 64));
+    if (lane == 0) shm[wv] = __uint_as_float(mb);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < GV_NT / 64; ++q) mb = max(mb, __float_as_uint(shm[q]));
+  }
+  const bool finite = mb < 0x7f800000u;
+  const int s_v = gv_shift(finite ? (double)__uint_as_float(mb) : 0.0);
+  // v 2^s rounded (ties to even) by adding 1.5 2^52: the difference of the bit
+  // patterns is the integer
+  const double p2s = ldexp(1.0, s_v), magic = 6755399441055744.0;
+  const long long debias = 0x8080808080ll - __double_as_longlong(magic);
   int out[4] = {0, 0, 0, 0};
   for (int base = 0; base < nss; base += GV_MAX_SS) {
     const int ns = nss - base < GV_MAX_SS ? nss - base : GV_MAX_SS;
-    constexpr int NCP = (GV_MAX_SS * GV_SSB / 16 + GV_NT - 1) / GV_NT;
-    const int ncp = ns * GV_SSB / 16;
-    v4i_g cp[NCP];
+    // unit w of the segment: trit position i, bytes 4 e4 .. + 3 of group g of
+    // super-step ss, i.e. components 64 g + 16 e4 + 4 j + i, j < 4: one word
+    // of each plane
+    constexpr int NU = GV_MAX_SS * 64 / GV_NT;
+    static_assert(GV_MAX_SS * 64 % GV_NT == 0, "whole units per thread");
+    const float* Vs = V + (int64_t)base * GV_SS;
+    const int left = (int)(len - (int64_t)base * GV_SS);  // entries from the segment on
+    float x[NU][4];
 #pragma unroll
-    for (int j = 0; j < NCP; ++j) {
-      const int e = tid + GV_NT * j;
-      cp[j] = ((const v4i_g*)(V + (int64_t)base * GV_SSB))[e < ncp ? e : 0];
+    for (int u = 0; u < NU; ++u) {
+      const int w = tid + GV_NT * u, c = (w >> 6) * GV_SS + 16 * ((w >> 2) & 15) + (w & 3);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[u][j] = Vs[c + 4 * j < left ? c + 4 * j : 0];
     }
     __builtin_amdgcn_sched_barrier(0);
     const GvWave v = gv_wave(P, rows, rb, ns, r0, base);
@@ -980,9 +953,30 @@ __global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();  // the previous segment has been read
 #pragma unroll
-    for (int j = 0; j < NCP; ++j) {
-      const int e = tid + GV_NT * j;
-      if (e < ncp) ((v4i_g*)dig)[e] = cp[j];
+    for (int u = 0; u < NU; ++u) {
+      const int w = tid + GV_NT * u, ss = w >> 6, g = (w >> 4) & 3, e4 = (w >> 2) & 3, i = w & 3;
+      const int c = ss * GV_SS + 16 * ((w >> 2) & 15) + i;
+      unsigned lo[4], hi[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const double t = fma((double)(c + 4 * j < left && finite ? x[u][j] : 0.0f), p2s, magic);
+        const unsigned long long q = (unsigned long long)(__double_as_longlong(t) + debias);
+        lo[j] = (unsigned)q;
+        hi[j] = (unsigned)(q >> 32);
+      }
+      // byte p of the four words is plane p's word
+      const unsigned a0 = __builtin_amdgcn_perm(lo[1], lo[0], 0x05010400u), a1 = __builtin_amdgcn_perm(lo[1], lo[0], 0x07030602u);
+      const unsigned b0 = __builtin_amdgcn_perm(lo[3], lo[2], 0x05010400u), b1 = __builtin_amdgcn_perm(lo[3], lo[2], 0x07030602u);
+      const unsigned a2 = __builtin_amdgcn_perm(hi[1], hi[0], 0x05010400u), b2 = __builtin_amdgcn_perm(hi[3], hi[2], 0x05010400u);
+      if (ss < ns) {
+        unsigned* d = (unsigned*)(dig + (int64_t)ss * GV_SSB + (((i * 4 + g) * GV_PLANES) << 4)) + e4;
+        d[0] = __builtin_amdgcn_perm(b0, a0, 0x05040100u) ^ 0x80808080u;
+        d[4] = __builtin_amdgcn_perm(b0, a0, 0x07060302u) ^ 0x80808080u;
+        d[8] = __builtin_amdgcn_perm(b1, a1, 0x05040100u) ^ 0x80808080u;
+        d[12] = __builtin_amdgcn_perm(b1, a1, 0x07060302u) ^ 0x80808080u;
+        d[16] = __builtin_amdgcn_perm(b2, a2, 0x05040100u) ^ 0x80808080u;
+        d[20] = __builtin_amdgcn_perm(b2, a2, 0x07060302u);
+      }
     }
     __syncthreads();
     int o[4];
@@ -993,23 +987,10 @@ __global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void
   const long long y = gv_combine(out, xch);
   if (wv % GV_KSPLIT == 0 && lane < 16) {
     const int64_t i = r0 + 16 * (wv / GV_KSPLIT) + lane;
-    if (CSIDE) {
-      if (i < (int64_t)nss_t * GV_SS) {
-        long long q = 0;
-        if (i < rows && s_t != GV_NONFINITE) q = (long long)rint(ldexp((double)y, s_t - s_v) * (double)D[i]);
-        int8_t d[GV_PLANES];
-        gv_digits(q, d);
-#pragma unroll
-        for (int p = 0; p < GV_PLANES; ++p) T[gv_digit_offset(i, p)] = (uint8_t)d[p];
-      }
-    } else if (i < rows) {
-      Y[i] = s_t == GV_NONFINITE ? NAN : (float)ldexp((double)y, -s_v);
+    if (i < rows) {
+      const double r = finite ? ldexp((double)y, -s_v) : NAN;
+      dst[i] = (float)(scale ? r * (double)scale[i] : r);
     }
-  }
-  if (CSIDE && blockIdx.x == gridDim.x - 1) {
-    for (int64_t c = (int64_t)gridDim.x * GV_ROWS + tid; c < (int64_t)nss_t * GV_SS; c += GV_NT)
-#pragma unroll
-      for (int p = 0; p < GV_PLANES; ++p) T[gv_digit_offset(c, p)] = 0;
   }
 }
 
@@ -1050,15 +1031,8 @@ static ApplyLayout apply_layout(int64_t m, int64_t n, int64_t k, int nb) {
     L.total = L.ts + 256;
     return L;
   }
-  if (gemv_long(n, k, nb)) {
-    // the digit planes of t and x and the exponent words
-    L.ts = al256((size_t)((k + GV_SS - 1) / GV_SS) * GV_SSB);
-    L.part = L.ts + al256((size_t)((n + GV_SS - 1) / GV_SS) * GV_SSB);
-    L.total = L.part + 256;
-    return L;
-  }
   if (nb <= AP_VEC_MAX) {
-    // vector-ALU path: T, nb x kq floats (kq = k rounded up to 4)
+    // T, nb x kq floats (kq = k rounded up to 4)
     L.total = al256(sizeof(float) * (size_t)nb * (size_t)((k + 3) & ~(int64_t)3));
     return L;
   }
@@ -1144,37 +1118,23 @@ static hipError_t run_gemv(const uint8_t* Bp, const uint8_t* Cp, const float* D,
   return hipGetLastError();
 }
 
-template <bool CSIDE>
-static hipError_t launch_gemv_long(const uint8_t* P, int64_t rows, int64_t len, const uint8_t* V, const int* sx,
-                                   const float* D, int nss_t, uint8_t* T, float* Y, hipStream_t s) {
+static hipError_t launch_gemv_long(const uint8_t* P, int64_t rows, int64_t len, const float* V, const float* scale,
+                                   float* dst, hipStream_t s) {
   const dim3 grid((unsigned)((rows + GV_ROWS - 1) / GV_ROWS));
   if (((len + 3) / 4) % 16 == 0 && ((uintptr_t)P % 16) == 0)
-    hipLaunchKernelGGL((k_gemv_long<true, CSIDE>), grid, dim3(GV_NT), 0, s, P, rows, len, V, sx, D, nss_t, T, Y);
+    hipLaunchKernelGGL(k_gemv_long<true>, grid, dim3(GV_NT), 0, s, P, rows, len, V, scale, dst);
   else
-    hipLaunchKernelGGL((k_gemv_long<false, CSIDE>), grid, dim3(GV_NT), 0, s, P, rows, len, V, sx, D, nss_t, T, Y);
+    hipLaunchKernelGGL(k_gemv_long<false>, grid, dim3(GV_NT), 0, s, P, rows, len, V, scale, dst);
   return hipGetLastError();
-}
-
-static hipError_t run_gemv_long(const uint8_t* Bp, const uint8_t* Cp, const float* D, int64_t m, int64_t n, int64_t k,
-                                const float* X, float* Y, char* ws, hipStream_t s) {
-  const ApplyLayout L = apply_layout(m, n, k, 1);
-  uint8_t* T = (uint8_t*)ws;
-  uint8_t* XT = (uint8_t*)(ws + L.ts);
-  int* sx = (int*)(ws + L.part);
-  const int nss_x = (int)((n + GV_SS - 1) / GV_SS), nss_t = (int)((k + GV_SS - 1) / GV_SS);
-  hipLaunchKernelGGL(k_gemv_x, dim3((unsigned)((nss_x * GV_SS + GV_NT - 1) / GV_NT)), dim3(GV_NT), 0, s, X, D, n, k,
-                     nss_x, XT, sx);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = launch_gemv_long<true>(Cp, k, n, XT, sx, D, nss_t, T, nullptr, s);
-  if (e != hipSuccess) return e;
-  return launch_gemv_long<false>(Bp, m, k, T, sx, nullptr, 0, nullptr, Y, s);
 }
 
 static hipError_t run_apply_kernels(const uint8_t* Bp, const uint8_t* Cp, const float* D, int64_t m, int64_t n,
                                     int64_t k, const float* X, int nb, float* Y, char* ws, hipStream_t s) {
   if (gemv_fits(n, k, nb)) return run_gemv(Bp, Cp, D, m, n, k, X, Y, ws, s);
-  if (gemv_long(n, k, nb)) return run_gemv_long(Bp, Cp, D, m, n, k, X, Y, ws, s);
+  if (gemv_long(n, k, nb)) {
+    const hipError_t e = launch_gemv_long(Cp, k, n, X, D, (float*)ws, s);
+    return e != hipSuccess ? e : launch_gemv_long(Bp, m, k, (const float*)ws, nullptr, Y, s);
+  }
   if (nb <= AP_VEC_MAX) return run_vec<AP_VEC_MAX>(Bp, Cp, D, m, n, k, X, nb, Y, (float*)ws, s);
   const ApplyLayout L = apply_layout(m, n, k, nb);
   unsigned short* TS = (unsigned short*)(ws + L.ts);

@@ -1,7 +1,7 @@
 """Inference at the sizes where its loads and segments have edges: packed rows
 of any byte length at any byte address, matrices shorter than one load window,
 and one vector past the length that a workgroup holds (segments of 10240
-components, up to 65536).
+components, up to 65536, with the intermediate rounded to fp32).
 
 The packed matrices lie in buffers whose other bytes are all ones (trit code
 11, i.e. -1), so a byte taken from past a row or a matrix shows in the result.
@@ -49,8 +49,13 @@ def check(m, n, k, nb, offset, scale=None):
     Bf, Cf = np.abs(B).astype(np.float64), np.abs(C).astype(np.float64)
     if nb == 1:
         mx, sx, md = np.max(np.abs(X)), np.sum(np.abs(X)), np.max(np.abs(D))
-        q = Bf @ (np.abs(D) * Cf.sum(axis=1)) * mx + Bf.sum(axis=1) * md * sx
-        bound = U * np.abs(ref) + 2.0 * 2.0 ** -46 * q[None, :]
+        t = D * (C.astype(np.float64) @ X[0])
+        mt, rounded = md * sx, 0.0
+        if n > 10240 or k > 10240:      # t in fp32, its exponent from max |t|
+            mt, rounded = np.max(np.abs(t)) * (1.0 + U), Bf @ np.abs(t)
+        q = Bf @ (np.abs(D) * Cf.sum(axis=1)) * mx + Bf.sum(axis=1) * mt
+        # twice the conversions (fp64 roundings); 1 + 2^-20: second-order terms
+        bound = (U * (np.abs(ref) + rounded) * (1.0 + 2.0 ** -20) + 2.0 * 2.0 ** -46 * q)[None, :][0]
     else:
         bound = ((n + k + 4) * U * (Bf @ (np.abs(D)[:, None] * (Cf @ np.abs(X).T)))).T
     assert np.all(np.abs(Y - ref) <= bound)
