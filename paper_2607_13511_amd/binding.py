@@ -123,11 +123,17 @@ def workspace_bytes(m: int, n: int, k: int = 0) -> int:
 # ---------------------------------------------------------------------------
 # torch marshalling
 # ---------------------------------------------------------------------------
+_torch_module = None   # torch, once a GPU has been seen
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise RuntimeError("externd needs a HIP GPU (torch.cuda is not available)")
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        if not torch.cuda.is_available():
+            raise RuntimeError("externd needs a HIP GPU (torch.cuda is not available)")
+        _torch_module = torch
+    return _torch_module
 
 
 def _dev_ptr(t) -> int:
@@ -135,8 +141,10 @@ def _dev_ptr(t) -> int:
 
 
 def _stream_ptr(torch, stream) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is None:
+        # the current stream's handle without building a Stream object for it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return int(stream.cuda_stream)
 
 
 def _workspace(torch, m, n, k, device):
@@ -147,7 +155,7 @@ def _workspace(torch, m, n, k, device):
 
 
 def _req(t, torch, dtype, shape, name):
-    if not (t.is_cuda and t.dtype == dtype and t.is_contiguous() and tuple(t.shape) == tuple(shape)):
+    if not (t.is_cuda and t.dtype is dtype and t.is_contiguous() and t.shape == shape):
         raise ValueError(f"{name}: expected a contiguous {dtype} CUDA tensor of shape {tuple(shape)}, "
                          f"got {t.dtype} {tuple(t.shape)} on {t.device}")
 
@@ -255,12 +263,17 @@ def apply(B_packed, C_packed, D, m: int, n: int, X, stream=None, workspace=None)
     _req(B_packed, torch, torch.uint8, (m, (k + 3) // 4), "B_packed")
     _req(C_packed, torch, torch.uint8, (k, (n + 3) // 4), "C_packed")
     Y = torch.empty((nb, m), dtype=torch.float32, device=X.device)
-    nbytes = lib().externd_apply_workspace_bytes(m, n, k, nb)
-    if nbytes == 0:
-        raise ExterndError(EINVAL, "externd_apply_workspace_bytes")
+    L = lib()
+    # the library checks a given workspace's size itself
+    if workspace is None or not 1 <= nb <= APPLY_MAX_BATCH or max(m, n, k) > 1 << 31:
+        nbytes = L.externd_apply_workspace_bytes(m, n, k, nb)
+        if nbytes == 0:
+            raise ExterndError(EINVAL, "externd_apply_workspace_bytes")
     ws = workspace if workspace is not None else torch.empty(nbytes, dtype=torch.uint8, device=X.device)
-    _check(lib().externd_apply(_dev_ptr(B_packed), _dev_ptr(C_packed), _dev_ptr(D), m, n, k, _dev_ptr(X), nb,
-                               _dev_ptr(Y), _dev_ptr(ws), ws.numel(), _stream_ptr(torch, stream)), "externd_apply")
+    st = L.externd_apply(B_packed.data_ptr(), C_packed.data_ptr(), D.data_ptr(), m, n, k, X.data_ptr(), nb,
+                         Y.data_ptr(), ws.data_ptr(), ws.numel(), _stream_ptr(torch, stream))
+    if st != OK:
+        raise ExterndError(st, "externd_apply")
     return Y
 
 
