@@ -100,11 +100,17 @@ __device__ __forceinline__ void row_sum15(double& x) {
   dpp_sum_step<DPP_ROW_SHR4, 0xF>(x);
   dpp_sum_step<DPP_ROW_SHR8, 0xF>(x);
 }
-__device__ __forceinline__ void row_argmax15(double& v, int& i) {
-  dpp_argmax_step<DPP_ROW_SHR1, 0xF>(v, i);
-  dpp_argmax_step<DPP_ROW_SHR2, 0xF>(v, i);
-  dpp_argmax_step<DPP_ROW_SHR4, 0xF>(v, i);
-  dpp_argmax_step<DPP_ROW_SHR8, 0xF>(v, i);
+__device__ __forceinline__ void row_max15(double& x) {
+  dpp_max_step<DPP_ROW_SHR1, 0xF>(x);
+  dpp_max_step<DPP_ROW_SHR2, 0xF>(x);
+  dpp_max_step<DPP_ROW_SHR4, 0xF>(x);
+  dpp_max_step<DPP_ROW_SHR8, 0xF>(x);
+}
+__device__ __forceinline__ void row_imin15(int& x) {
+  dpp_imin_step<DPP_ROW_SHR1, 0xF>(x);
+  dpp_imin_step<DPP_ROW_SHR2, 0xF>(x);
+  dpp_imin_step<DPP_ROW_SHR4, 0xF>(x);
+  dpp_imin_step<DPP_ROW_SHR8, 0xF>(x);
 }
 
 }  // namespace externd

@@ -1042,19 +1042,21 @@ __device__ __forceinline__ void tile_stats(const v4d (&x)[2], int w, int64_t i0,
     const double a0 = ia < L ? fabs(x[0][r]) : 0.0, a1 = ib < L ? fabs(x[1][r]) : 0.0;
     double s = a0 + a1;
     // invalid indices never win the max; the 16 lanes of a row (one
-    // component) are reduced on DPP into lane 15 of the row
-    double mv = ia < L ? a0 : -1.0;
-    long long mi = ia;
-    argmax_merge(mv, mi, ib < L ? a1 : -1.0, ib);
-    int mi32 = (int)mi;
+    // component) are reduced on DPP into lane 15 of the row: sum and max, then
+    // the smallest index that attains the max (cheaper than carrying the
+    // index through the max: U-step of 9728x2560 25.9 -> 25.2 us)
+    const double v0 = ia < L ? a0 : -1.0, v1 = ib < L ? a1 : -1.0;
+    double mv = fmax(v0, v1);
     row_sum15(s);
-    row_argmax15(mv, mi32);
-    mi = mi32;
+    row_max15(mv);
+    mv = row_bcast<15>(mv);
+    int mi = v0 == mv ? (int)ia : (v1 == mv ? (int)ib : INT_MAX);
+    row_imin15(mi);
     if (li == 15) {
       const int c = 16 * w + lk + 4 * r;
       ps[(int64_t)c * ntile + tile] = s;
       pm[(int64_t)c * ntile + tile] = mv;
-      pi[(int64_t)c * ntile + tile] = (int)mi;
+      pi[(int64_t)c * ntile + tile] = mi;
     }
   }
 }
@@ -2232,12 +2234,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // next one in flight during the products): straight from memory, every wave
 // of the workgroup read it again, and the vector memory path, not the MFMA,
 // set the time.  9728x2560, block 256: V 51 -> 15 us,
-// U 65 -> 33 us for the four quarters (one launch per quarter before).
+// U 65 -> 32 us for the four quarters (one launch per quarter before).
+// Five waves a SIMD: up to 1280 workgroups are resident at once, which holds
+// the U-step's rows of this shape (1216; with four a SIMD the rest ran in a
+// second pass on a nearly idle chip, 33.9 us).
 template <int NH>
-__global__ __launch_bounds__(NT) void k_target_wide(const double* __restrict__ X, int64_t xq,
-                                                    const double* __restrict__ ginv, double* __restrict__ Y, int64_t L, int64_t Lp, double* ps,
-                                                    double* pm, int* pi, int nq, int64_t ntmax, int* gacc,
-                                                    int nclr, unsigned* sync) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(5))) void k_target_wide(
+    const double* __restrict__ X, int64_t xq, const double* __restrict__ ginv, double* __restrict__ Y, int64_t L,
+    int64_t Lp, double* ps, double* pm, int* pi, int nq, int64_t ntmax, int* gacc, int nclr, unsigned* sync) {
   wide_clear(gacc, nclr, sync, (int)(blockIdx.x + gridDim.x * blockIdx.y), (int)(gridDim.x * gridDim.y));
   // X_q' of the tile as [half][component][16]: the 32 lanes of a read phase
   // (two components) cover all 64 banks
