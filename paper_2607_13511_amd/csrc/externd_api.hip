@@ -21,7 +21,7 @@ static inline int clampi(int64_t v, int64_t lo, int64_t hi) { return (int)(v < l
 
 struct Layout {
   int64_t m_pad, n_pad;
-  int gv, gd, nblk_cap;
+  int gv, gvcap, gd, nblk_cap;
   int urows, ntr, gu, urows_wide, nsu, nsv;
   size_t off[48];
   size_t total;
@@ -81,13 +81,16 @@ static Layout make_layout(int64_t m, int64_t n, int64_t k) {
   L.m_pad = round_up(m, TILE);
   L.n_pad = round_up(n, TILE);
   const int64_t nct = L.n_pad / TILE, nrt = L.m_pad / TILE;
-  // V-step: about 480 column-tile x row-group workgroups.  Deflation and
-  // staging: as many row groups as keep the whole deflation grid resident
-  // in one pass (a second, partial pass leaves its CUs moving 1.5 shares of
-  // the residual while the others idle).
-  L.gv = clampi((480 + nct - 1) / nct, 1, nrt < GV_MAX ? nrt : GV_MAX);
+  // V-step: about 480 column-tile x row-group workgroups, but no more than
+  // are resident at once (2 a CU): a second, partial pass takes as long as a
+  // full one.  9728 columns: 608 workgroups in two passes 31.4 us, 304 in one
+  // 29.3.  The partials' space holds the uncut number of groups (the U-step's
+  // column groups use it too).  Deflation and staging: as many row groups as
+  // keep the whole deflation grid resident in one pass, for the same reason.
+  L.gvcap = clampi((480 + nct - 1) / nct, 1, nrt < GV_MAX ? nrt : GV_MAX);
+  L.gv = clampi(512 / nct, 1, L.gvcap);
   L.gd = clampi(DEFLATE_SLOTS / nct, 1, nrt < 64 ? nrt : 64);
-  ustep_split(L.m_pad, L.n_pad, L.gv, &L.urows, &L.ntr, &L.gu);
+  ustep_split(L.m_pad, L.n_pad, L.gvcap, &L.urows, &L.ntr, &L.gu);
   L.urows_wide = clampi((L.m_pad + USTEP_FREE - 1) / USTEP_FREE, 1, TILE);
   L.nsu = clampi((L.m_pad + TERN_CHUNK - 1) / TERN_CHUNK, 1, TERN_SPLIT_MAX);
   L.nsv = clampi((L.n_pad + TERN_CHUNK - 1) / TERN_CHUNK, 1, TERN_SPLIT_MAX);
@@ -103,7 +106,7 @@ static Layout make_layout(int64_t m, int64_t n, int64_t k) {
       (size_t)(BMAX * L.n_pad),                        // 4 Vr
       sizeof(double) * (size_t)(BMAX * L.m_pad),       // 5 Q
       sizeof(double) * (size_t)(BMAX * L.m_pad),       // 6 Z
-      sizeof(long long) * (size_t)(L.gv * BMAX * L.n_pad),  // 7 Pp
+      sizeof(long long) * (size_t)(L.gvcap * BMAX * L.n_pad),  // 7 Pp
       sizeof(double) * (size_t)(BMAX * L.n_pad),       // 8 Y
       sizeof(double) * 4096,                           // 9 ginvU
       sizeof(double) * 4096,                           // 10 ginvV
