@@ -256,8 +256,8 @@ def collect_traffic(dbs, copy_bytes: int):
     copy_f = max(v[1] for k, v in cfetch.items() if "copyBuffer" in k)
     copy_w = max(v[1] for k, v in cwrite.items() if "copyBuffer" in k)
     ff, fw = copy_bytes / copy_f, copy_bytes / copy_w
-    classes = {"vstep_contraction": "k_vstep", "ustep_contraction": "k_ustep<false>", "deflate": "k_deflate<false>",
-               "vstep_target": "k_vtarget", "ustep_target": "k_utarget", "ternarize_v": "k_tern_v",
+    classes = {"vstep_contraction": "k_vstep", "ustep_contraction": "k_ustep<false, false>",
+               "deflate": "k_deflate<false>", "ternarize_v": "k_tern_v",
                "ternarize_u": "k_tern_u"}
     out = {"kernel_source_sha256": kernel_source_hash(), "copy_bytes": copy_bytes,
            "fetch_scale": ff, "write_scale": fw, "kernels": {}}
@@ -292,9 +292,12 @@ def collect_traffic(dbs, copy_bytes: int):
     print(json.dumps(out))
 
 
-KERNEL_CLASS = {"k_vstep": "vstep_contraction", "k_ustep": "ustep_contraction", "k_ustep<false>": "ustep_contraction",
-                "k_ustep<true>": "ustep_contraction", "k_deflate": "deflate", "k_deflate<false>": "deflate",
-                "k_deflate<true>": "deflate", "k_vtarget": "vstep_target", "k_utarget": "ustep_target",
+KERNEL_CLASS = {"k_vstep": "vstep_contraction", "k_vstep_wide": "vstep_contraction",
+                "k_ustep<false, false>": "ustep_contraction", "k_ustep<false, true>": "ustep_contraction",
+                "k_ustep<true, false>": "ustep_contraction", "k_ustep<true, true>": "ustep_contraction",
+                "k_ustep_wide<false>": "ustep_contraction", "k_ustep_wide<true>": "ustep_contraction",
+                "k_deflate<false>": "deflate", "k_deflate<true>": "deflate", "k_deflate_wide": "deflate",
+                "k_target_wide<1>": "vstep_target", "k_target_wide<2>": "ustep_target",
                 "k_tern_v": "ternarize_v", "k_tern_u": "ternarize_u"}
 
 

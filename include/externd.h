@@ -53,7 +53,9 @@ extern "C" {
 #define EXTERND_ESYNC        -6  /* a bounded wait between the workgroups of one kernel
                                     launch ran out (the U-step's row groups and the
                                     V-step's last row group of each column tile wait at
-                                    most 20 ms for the inverse Gram of the same launch);
+                                    most 20 ms for the inverse Gram of the same launch,
+                                    and in blocks wider than 64 the workgroups that build
+                                    that inverse wait at most 20 ms for each other);
                                     the factors of such a call are not to be used       */
 #define EXTERND_ESCRATCH     -7  /* the call needs more than the fixed device scratch of
                                     an allocation-free entry point                       */

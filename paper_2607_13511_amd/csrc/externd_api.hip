@@ -138,8 +138,8 @@ static Layout make_layout(int64_t m, int64_t n, int64_t k) {
       sizeof(int) * (size_t)L.n_pad,                   // 36 cshift
       sizeof(long long) * 4096 * NPAIR_MAX,            // 37 gaccW (int32 Grams, int64 weighted Grams)
       sizeof(double) * BMAX * BMAX,                    // 38 gramVW
-      sizeof(double) * BMAX * BMAX,                    // 39 wA0
-      sizeof(double) * BMAX * BMAX,                    // 40 wA1
+      sizeof(double) * BMAX * BMAX,                    // 39 wpanel
+      sizeof(double) * BMAX * BMAX,                    // 40 wpivot
       (size_t)(WDIG * BMAX * L.n_pad),                 // 41 Wmf
       sizeof(double) * BMAX * BMAX,                    // 42 ginvUW
       sizeof(double) * BMAX * BMAX,                    // 43 ginvVW
@@ -220,8 +220,8 @@ bool carve(Ws& w, void* base, size_t bytes, int64_t m, int64_t n, int64_t k) {
   w.cshift = (int*)(b + L.off[36]);
   w.gaccW = (int*)(b + L.off[37]);
   w.gramVW = (double*)(b + L.off[38]);
-  w.wA0 = (double*)(b + L.off[39]);
-  w.wA1 = (double*)(b + L.off[40]);
+  w.wpanel = (double*)(b + L.off[39]);
+  w.wpivot = (double*)(b + L.off[40]);
   w.ginvUW = (double*)(b + L.off[42]);
   w.ginvVW = (double*)(b + L.off[43]);
   w.wflag = (int*)(b + L.off[45]);

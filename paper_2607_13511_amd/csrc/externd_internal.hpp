@@ -87,7 +87,7 @@ struct Ws {
   int8_t* Vr;            // n_pad x BBP
   int8_t* Umf;           // BBP x m_pad bytes, U in the MFMA-ready operand layout
   int8_t* Vmf;           // BBP x n_pad bytes, V in the MFMA-ready operand layout
-  double* tps;           // BBP x tiles: per-32-index-tile sum |x| of a target component
+  double* tps;           // BBP x tiles: per-tile sum |x| of a target component (tiles: 32 or 16 indices, or a U-step's rows)
   double* tpm;           // BBP x tiles: per-tile max |x|
   int* tpi;              // BBP x tiles: per-tile smallest index attaining the max
   int* gacc;             // 2 x 4096: integer Gram accumulators of the V-step (U) and U-step (V)
@@ -126,8 +126,8 @@ struct Ws {
   int* gaccW;            // NPAIR_MAX x 4096: integer Gram blocks X_q^T X_q' (q <= q') of a factor (int32;
                          // int64 for the weighted Grams of V)
   double* gramVW;        // BMAX x BMAX raw V^T H V (row-major), for the joint solve
-  double* wA0;           // BMAX x BMAX: the matrix being swept (ping)
-  double* wA1;           // BMAX x BMAX: (pong)
+  double* wpanel;        // NQMAX x NQMAX blocks of 4096: the panels that the side path's workgroups exchange
+  double* wpivot;        // BMAX x BMAX: block k the pivot inverse of step k
   double* ginvUW;        // NQMAX x NQMAX blocks of 4096 (fp64 MFMA operand order): (U^T U + eps I)^{-1}
   double* ginvVW;        // the same for (V^T H V + eps I)^{-1}
   int* wflag;            // 1: the swept matrix had zero trace

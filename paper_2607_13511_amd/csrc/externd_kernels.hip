@@ -1062,8 +1062,8 @@ __device__ __forceinline__ void tile_stats(const v4d (&x)[2], int w, int64_t i0,
 }
 
 // ---------------------------------------------------------------------------
-// V-step contraction P = U^T R  (Eq. (3), first half; the target
-// Y = G_U^{-1} P follows in k_vtarget)
+// V-step contraction P = U^T R and target Y = G_U^{-1} P  (Eq. (3), first
+// half)
 // grid: nside side WGs (the U Gram U^T U on int8 MFMA over K slices, then
 //       in the last of them the ridge and inverse G_U^{-1}) followed by
 //       (n_pad/32 column tiles) x gv row groups, each storing its exact
@@ -1096,8 +1096,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   // as in the U-step, the second workgroups on the side workgroups' CUs
   // (grid indices 256 .. 256 + nside - 1) stay empty
   const int b0 = blockIdx.x - nside;
-  if (nside && b0 >= 256 - nside && b0 < 256) return;
-  const int b = (nside && b0 >= 256) ? b0 - nside : b0;
+  if (b0 >= 256 - nside && b0 < 256) return;
+  const int b = b0 >= 256 ? b0 - nside : b0;
   const int nct = (int)(n_pad / TILE);
   if (b >= nct * gv) return;
   const int ct = b % nct, g = b / nct;
@@ -1149,11 +1149,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   // out[t][M = component][N = column]: this row group's partial P tile, at
   // the column's fixed-point scale
   long long* Pg = Pp + ((int64_t)g * BBP) * n_pad + (int64_t)ct * TILE;
-  if (!Y) {
-    reduce_waves(smem, acc, ks1 - ks0 <= FOLD_KMAX,
-                 [&](int t, int M, int N, long long v) { Pg[(int64_t)(32 * t + M) * n_pad + N] = v; });
-    return;
-  }
   // The partials go out written through, and the last of the column tile's
   // gv row groups to arrive forms its targets Y = G_U^{-1} P (Eq. (3) first
   // half) and their T_tau statistics (one 32-column tile).
@@ -1248,8 +1243,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 }
 
 // ---------------------------------------------------------------------------
-// U-step Q = R diag(h~) V  (Eq. (3) second half, Sec. 2.5); the target
-// Z = Q G_V^{-1} follows in k_utarget
+// U-step Q = R diag(h~) V and target Z = Q G_V^{-1}  (Eq. (3) second half,
+// Sec. 2.5); with Z null (and nside 0) Q alone: quarter 0 of a wide block's
+// first U-step
 // grid: nside side WGs (V^T V on int8 MFMA over K slices, weighted
 //       V^T diag(H) V from the weights' digit planes; the last of them adds
 //       the ridge and inverts; the raw Gram is kept for the scale solve)
@@ -4105,8 +4101,8 @@ static WideSide wide_side_args(const Ws& w, int which, bool weighted, int bb) {
   a.hwmax = w.hwmax;
   a.raw = which ? w.gramVW : nullptr;
   a.rel = EXTERND_RIDGE_REL;
-  a.panel = w.wA0;
-  a.pivot = w.wA1;
+  a.panel = w.wpanel;
+  a.pivot = w.wpivot;
   a.ginv = which ? w.ginvVW : w.ginvUW;
   a.wflag = w.wflag;
   a.sync = w.wsync;
