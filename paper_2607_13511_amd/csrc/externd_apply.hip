@@ -417,9 +417,28 @@ __global__ __launch_bounds__(NT_AP) void k_apply_ysum(const float* __restrict__ 
 
 // ---- vector-ALU path (nb <= AP_VEC_MAX) ----
 
-__device__ __forceinline__ float trit_of(unsigned byte, int t) {
+__device__ __forceinline__ int trit_of(unsigned byte, int t) {
   // the builtin is declared unsigned; its v_bfe_i32 result is the signed trit
-  return (float)(int)__builtin_amdgcn_sbfe((int)byte, 2 * t, 2);
+  return (int)__builtin_amdgcn_sbfe((int)byte, 2 * t, 2);
+}
+
+// Sums of eight values over the wave in a fixed order: lane l receives that of
+// value l / 8 (returned) in v[0].  Each exchange halves the values that a
+// lane still carries: 10 of them instead of 48.
+__device__ __forceinline__ int wave_sum8(double (&v)[8]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int h = 4; h > 0; h >>= 1) {
+    const bool up = lane & (8 * h);
+#pragma unroll
+    for (int i = 0; i < h; ++i) {
+      const double mine = up ? v[i + h] : v[i], other = up ? v[i] : v[i + h];
+      v[i] = mine + __shfl_xor(other, 8 * h, 64);
+    }
+  }
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, 64);
+  return lane >> 3;
 }
 
 // Rows r0 .. r0 + VEC_RPW - 1 of the packed matrix P (rows x len trits)
@@ -456,7 +475,7 @@ __device__ __forceinline__ void rows_times_vectors(const uint8_t* __restrict__ P
 #pragma unroll
       for (int r = 0; r < VEC_RPW; ++r)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[r][b] = fmaf(trit_of(byte[r], t), v[t], acc[r][b]);
+        for (int t = 0; t < 4; ++t) acc[r][b] = fmaf((float)trit_of(byte[r], t), v[t], acc[r][b]);
     }
   }
 #pragma unroll
@@ -881,7 +900,48 @@ __global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void
 // the workspace, and both sides are one kernel.  Bound by the memory's read
 // of the trits: 8192 x 28672, k = 20480 (189 MB) takes 68 us; fp32 FMA on
 // decoded trits, one byte a lane, was bound by the decode at 112 us.
+//
+// An entry at most GV_RANGE binades below the largest converts exactly.  A
+// vector with a smaller nonzero entry takes fp64 sums of decoded trits instead
+// (gl_wide): a row whose trits skip the large entries keeps its own relative
+// accuracy.  Every workgroup scans the whole vector, so all of them take the
+// same side.
 constexpr int64_t GV_LONG_MAX = 65536;  // int64 sums of 48-bit entries stay below 2^63
+constexpr int GV_RANGE = 22;
+
+// Rows r0 .. r0 + nrows - 1 by fp64 sums, eight rows at a time over the whole
+// workgroup (the lanes by a shuffle tree, then the waves in order).
+// red: LDS, 8 (GV_NT / 64) doubles.
+__device__ __forceinline__ void gl_wide(const uint8_t* __restrict__ P, int64_t rows, int64_t len, int64_t r0,
+                                        int nrows, const float* __restrict__ V, const float* __restrict__ scale,
+                                        float* __restrict__ dst, double* red) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int64_t rb = (len + 3) >> 2;
+  for (int64_t q0 = r0; q0 < r0 + nrows && q0 < rows; q0 += 8) {
+    double acc[8] = {};
+    for (int64_t p = tid; p < rb; p += GV_NT) {
+      unsigned byte[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) byte[r] = P[(q0 + r < rows ? q0 + r : rows - 1) * rb + p];
+      double v[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = 4 * p + t < len ? (double)V[4 * p + t] : 0.0;
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[r] = fma((double)trit_of(byte[r], t), v[t], acc[r]);
+    }
+    const int r = wave_sum8(acc);
+    if ((lane & 7) == 0) red[8 * wv + r] = acc[0];
+    __syncthreads();
+    if (tid < 8 && q0 + tid < rows) {
+      double y = 0.0;
+      for (int w = 0; w < (GV_NT / 64); ++w) y += red[8 * w + tid];
+      dst[q0 + tid] = (float)(scale ? y * (double)scale[q0 + tid] : y);
+    }
+    __syncthreads();
+  }
+}
 
 // dst[i] = scale_i sum_c P_ic v_c (scale: fp32 per row, or null).  Every
 // workgroup forms max |v| itself (the same value in each), which fixes the
@@ -894,15 +954,16 @@ __global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void
   __shared__ __attribute__((aligned(16))) uint8_t dig[GV_MAX_SS * GV_SSB];
   __shared__ __attribute__((aligned(16))) uint8_t zero16[16];
   __shared__ int xch[GV_NT / 64][64][4];
-  __shared__ float shm[GV_NT / 64];
+  __shared__ unsigned shm[2 * (GV_NT / 64)];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int nss = (int)((len + GV_SS - 1) / GV_SS);
   const int64_t rb = (len + 3) >> 2;
   const int64_t r0 = (int64_t)blockIdx.x * GV_ROWS;
   if (tid < 4) ((int*)zero16)[tid] = 0;
-  // max |v| as the largest bit pattern (Inf and NaN above every number):
-  // four entries a load (any alignment), eight loads in flight
-  unsigned mb = 0u;
+  // max |v| as the largest bit pattern (Inf and NaN above every number), and
+  // the smallest nonzero one (less one; zero wraps above them): four entries a
+  // load (any alignment), eight loads in flight
+  unsigned mb = 0u, mn = 0xffffffffu;
   {
     constexpr int U = 8;
     const int64_t n4 = len >> 2;
@@ -913,17 +974,39 @@ __global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) mb = max(mb, v[u][e] & 0x7fffffffu);
+        for (int e = 0; e < 4; ++e) {
+          const unsigned a = v[u][e] & 0x7fffffffu;
+          mb = max(mb, a);
+          mn = min(mn, a - 1u);
+        }
     }
-    if (4 * n4 + tid < len) mb = max(mb, __float_as_uint(V[4 * n4 + tid]) & 0x7fffffffu);
+    if (4 * n4 + tid < len) {
+      const unsigned a = __float_as_uint(V[4 * n4 + tid]) & 0x7fffffffu;
+      mb = max(mb, a);
+      mn = min(mn, a - 1u);
+    }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mb = max(mb, (unsigned)__shfl_xor((int)mb, o, 64));
-    if (lane == 0) shm[wv] = __uint_as_float(mb);
+    for (int o = 32; o > 0; o >>= 1) {
+      mb = max(mb, (unsigned)__shfl_xor((int)mb, o, 64));
+      mn = min(mn, (unsigned)__shfl_xor((int)mn, o, 64));
+    }
+    if (lane == 0) {
+      shm[wv] = mb;
+      shm[GV_NT / 64 + wv] = mn;
+    }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < GV_NT / 64; ++q) mb = max(mb, __float_as_uint(shm[q]));
+    for (int q = 0; q < GV_NT / 64; ++q) {
+      mb = max(mb, shm[q]);
+      mn = min(mn, shm[GV_NT / 64 + q]);
+    }
   }
   const bool finite = mb < 0x7f800000u;
+  // biased exponents (denormals: that of the smallest normal number)
+  if (finite && mb != 0u && max((int)(mb >> 23), 1) - max((int)((mn + 1u) >> 23), 1) > GV_RANGE) {
+    gl_wide(P, rows, len, r0, GV_ROWS, V, scale, dst, (double*)dig);
+    return;
+  }
   const int s_v = gv_shift(finite ? (double)__uint_as_float(mb) : 0.0);
   // v 2^s rounded (ties to even) by adding 1.5 2^52: the difference of the bit
   // patterns is the integer

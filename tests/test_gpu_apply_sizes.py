@@ -1,12 +1,17 @@
 """Inference at the sizes where its loads and segments have edges: packed rows
 of any byte length at any byte address, matrices shorter than one load window,
-and one vector past the length that a workgroup holds (segments of 10240
-components, up to 65536, with the intermediate rounded to fp32).
+and one vector past the length that a workgroup holds at once (more than
+10240 components: segments of 10240, up to 65536, with the intermediate
+rounded to fp32).
 
 The packed matrices lie in buffers whose other bytes are all ones (trit code
 11, i.e. -1), so a byte taken from past a row or a matrix shows in the result.
-Tolerances as derived in test_gpu_apply.py: one vector is exact integer sums
-between two fixed-point conversions, more are fp32 sums of exact products.
+Tolerances.  As derived in test_gpu_apply.py, one vector is exact integer sums
+between two fixed-point conversions, more are fp32 sums of exact products.  One
+long vector is converted without loss and summed exactly, or, where its entries
+span more than 22 binades, summed in fp64 (n + k + 4 roundings of 2^-53 of the
+absolute sum); t and y are rounded to fp32 (u |B| |t| and u |y|).  No bound of
+it names the largest entry.
 """
 import numpy as np
 import pytest
@@ -49,16 +54,25 @@ def check(m, n, k, nb, offset, scale=None):
     Bf, Cf = np.abs(B).astype(np.float64), np.abs(C).astype(np.float64)
     if nb == 1:
         mx, sx, md = np.max(np.abs(X)), np.sum(np.abs(X)), np.max(np.abs(D))
-        t = D * (C.astype(np.float64) @ X[0])
-        mt, rounded = md * sx, 0.0
-        if n > 10240 or k > 10240:      # t in fp32, its exponent from max |t|
-            mt, rounded = np.max(np.abs(t)) * (1.0 + U), Bf @ np.abs(t)
-        q = Bf @ (np.abs(D) * Cf.sum(axis=1)) * mx + Bf.sum(axis=1) * mt
-        # twice the conversions (fp64 roundings); 1 + 2^-20: second-order terms
-        bound = (U * (np.abs(ref) + rounded) * (1.0 + 2.0 ** -20) + 2.0 * 2.0 ** -46 * q)[None, :][0]
+        if max(n, k) > 10240:
+            bound = long_bound(B, C, D, X[0], ref)
+        else:
+            q = Bf @ (np.abs(D) * Cf.sum(axis=1)) * mx + Bf.sum(axis=1) * md * sx
+            # twice the conversions (fp64 roundings); 1 + 2^-20: second-order terms
+            bound = U * np.abs(ref[0]) * (1.0 + 2.0 ** -20) + 2.0 * 2.0 ** -46 * q
+        assert np.all(np.abs(Y[0] - ref[0]) <= bound)
     else:
         bound = ((n + k + 4) * U * (Bf @ (np.abs(D)[:, None] * (Cf @ np.abs(X).T)))).T
-    assert np.all(np.abs(Y - ref) <= bound)
+        assert np.all(np.abs(Y - ref) <= bound)
+
+
+def long_bound(B, C, D, x, ref):
+    """Of one long vector; 1 + 2^-20: second-order terms."""
+    (m, k), n = B.shape, C.shape[1]
+    Bf, Cf = np.abs(B).astype(np.float64), np.abs(C).astype(np.float64)
+    t = D * (C.astype(np.float64) @ x)
+    return (U * (np.abs(ref[0]) + Bf @ np.abs(t)) * (1.0 + 2.0 ** -20)
+            + (n + k + 4) * 2.0 ** -53 * (Bf @ (np.abs(D) * (Cf @ np.abs(x)))))
 
 
 @pytest.mark.parametrize("nb", [1, 3, 8])
@@ -80,6 +94,39 @@ def test_byte_addresses(offset, nb):
 def test_one_long_vector(m, n, k):
     check(m, n, k, 1, 0)
     check(m, n, k, 1, 1, lambda rng, shape: np.exp2(rng.integers(-20, 1, size=shape)))
+
+
+@pytest.mark.parametrize("gap", [20, 24, 30, 38, 39, 40, 60, 120])
+@pytest.mark.parametrize("side", ["x", "t"])
+def test_long_vector_small_entries(side, gap):
+    """One entry 2^gap above the others, where half of the rows have no trit:
+    their results keep their own accuracy."""
+    from paper_2607_13511_amd import binding
+    print(f"[apply] {side} gap {gap}", flush=True)
+    m, n, k = (35, 12005, 50) if side == "x" else (50, 37, 12005)
+    rng = np.random.default_rng([gap, n])
+    B = rng.integers(-1, 2, size=(m, k)).astype(np.int8)
+    C = rng.integers(-1, 2, size=(k, n)).astype(np.int8)
+    D = rng.standard_normal(k).astype(np.float32).astype(np.float64)
+    x = rng.standard_normal(n).astype(np.float32).astype(np.float64)
+    at = 7777
+    if side == "x":
+        x[at] = 2.0 ** gap
+        C[::2, at] = 0
+        B[::3, 1::2] = 0     # these outputs see only rows of C without the large entry
+    else:
+        D[at] *= 2.0 ** gap
+        C[at, 3] = 1
+        B[::2, at] = 0
+    if gap == 120:           # the others denormal in fp32
+        x = (x * 2.0 ** -135).astype(np.float32).astype(np.float64)
+        if side == "x":
+            D = D * 2.0 ** 80
+    Y = binding.apply(place(pack(B), 3), place(pack(C), 3), torch.from_numpy(D.astype(np.float32)).cuda(), m, n,
+                      torch.from_numpy(x.astype(np.float32)[None, :]).cuda()).cpu().numpy().astype(np.float64)
+    ref = oracle.apply(B, C, D, x[None, :])
+    bound = long_bound(B, C, D, x, ref) + 2.0 ** -149 * (1.0 + np.abs(B).sum(axis=1))   # denormal t and y
+    assert np.all(np.abs(Y[0] - ref[0]) <= bound)
 
 
 def test_one_long_vector_past_the_segments():
