@@ -242,10 +242,10 @@ int externd_factorize_refined(const float* A, int64_t m, int64_t n, double mu, d
  *    u |y| + 2^-46 [ (|B| (|D| (|C| 1))) max|x| + (|B| 1) max|D| sum|x| ]
  *    per output, u = 2^-24 (entries of x within 2^22 of max |x| convert
  *    exactly).  With n or k above 10240 no entry is rounded in conversion: a
- *    vector is summed exactly or, where its nonzero entries span more than 22
- *    binades, in fp64 (trits decoded), and only t and y are rounded, to fp32: u (|y| + |B| |t|) + (n + k + 4) 2^-53
- *    |B| (|D| (|C| |x|)), whatever the largest entry.  A NaN or infinite entry
- *    of x or D makes every output NaN.
+ *    vector is summed exactly (in groups of 38 binades, added in fp64) or,
+ *    where its side is small, in fp64, and only t and y are rounded, to fp32:
+ *    u (|y| + |B| |t|) + (n + k + 4) 2^-53 |B| (|D| (|C| |x|)), whatever the
+ *    largest entry.  A NaN or infinite entry of x or D makes every output NaN.
  *  - Otherwise one vector runs on fp32 FMA and two or more on bf16 matrix
  *    cores with exact operands (trits are exact in bf16; every fp32 vector
  *    entry is split exactly into three bf16 parts), with fp32 sums: at most

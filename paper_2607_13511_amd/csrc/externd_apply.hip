@@ -10,14 +10,15 @@
 // One vector (a matrix-vector product): integer matrix cores, with the
 // vector's digit planes in LDS (k_gemv_c, k_gemv_b) or, beyond 10240
 // entries, brought there by segments (k_gemv_long).  Beyond 65536
-// entries k_apply_vec_c then k_apply_vec_b:
-// fp32 FMA on the vector ALUs.  The signed 2-bit field extract (v_bfe_i32)
+// entries, and in double for a short or small side beside one past 10240
+// (long_side), k_apply_vec_c and k_apply_vec_b:
+// FMA on the vector ALUs.  The signed 2-bit field extract (v_bfe_i32)
 // of a code is the trit itself (01 -> 1, 11 -> -1, 00 -> 0).  A workgroup
 // takes VEC_RPW consecutive rows; lane l of wave w takes byte
 // p = 64 w + l + 256 i of the rows (elements 4p .. 4p+3), so the vector
 // entries a wave needs are contiguous and each loaded slice serves all
 // VEC_RPW rows from registers.  Each wave sums its lanes with a fixed
-// shuffle tree and the four waves are added in wave order through LDS.  For
+// shuffle tree (double: wave_sum8) and the four waves are added in wave order through LDS.  For
 // one vector the matrix-core path below spends more on decoding trits and
 // staging than this path spends on arithmetic; from two vectors on it is
 // the faster one.
@@ -443,19 +444,20 @@ __device__ __forceinline__ int wave_sum8(double (&v)[8]) {
 
 // Rows r0 .. r0 + VEC_RPW - 1 of the packed matrix P (rows x len trits)
 // times the nb vectors V (V[b * vs + j], j < len), summed over the
-// workgroup: dst[(r0 + r) + b * b_stride] = scale[r0 + r] * sum.
-template <int NB, bool ALIGNED>
+// workgroup: dst[(r0 + r) + b * b_stride] = scale[r0 + r] * sum.  Acc double:
+// a non-finite entry counts as NaN, and makes every result NaN.
+template <int NB, bool ALIGNED, typename Acc>
 __device__ __forceinline__ void rows_times_vectors(const uint8_t* __restrict__ P, int64_t rows, int64_t len,
                                                    int64_t r0, const float* __restrict__ V, int64_t vs, int nb,
                                                    const float* scale, float* dst, int64_t b_stride) {
-  __shared__ float part[4][VEC_RPW * NB];
+  __shared__ Acc part[4][VEC_RPW * NB];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t rb = (len + 3) >> 2;
-  float acc[VEC_RPW][NB];
+  Acc acc[VEC_RPW][NB];
 #pragma unroll
   for (int r = 0; r < VEC_RPW; ++r)
 #pragma unroll
-    for (int b = 0; b < NB; ++b) acc[r][b] = 0.0f;
+    for (int b = 0; b < NB; ++b) acc[r][b] = 0;
   for (int64_t p = 64 * w + lane; p < rb; p += NT_AP) {
     unsigned byte[VEC_RPW];
 #pragma unroll
@@ -472,26 +474,41 @@ __device__ __forceinline__ void rows_times_vectors(const uint8_t* __restrict__ P
 #pragma unroll
         for (int t = 0; t < 4; ++t) v[t] = j + t < len ? V[b * vs + j + t] : 0.0f;
       }
+      if (sizeof(Acc) == 8)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] += v[t] - v[t];
 #pragma unroll
       for (int r = 0; r < VEC_RPW; ++r)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[r][b] = fmaf((float)trit_of(byte[r], t), v[t], acc[r][b]);
+        for (int t = 0; t < 4; ++t) acc[r][b] = fma((Acc)trit_of(byte[r], t), (Acc)v[t], acc[r][b]);
     }
   }
-#pragma unroll
-  for (int r = 0; r < VEC_RPW; ++r)
+  if (sizeof(Acc) == 8) {
+    static_assert(VEC_RPW == 8, "rows of the transposing sum");
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
+      double v[8];
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) acc[r][b] += __shfl_xor(acc[r][b], o, 64);
-      if (lane == 0) part[w][r * NB + b] = acc[r][b];
+      for (int r = 0; r < 8; ++r) v[r] = acc[r][b];
+      const int r = wave_sum8(v);
+      if ((lane & 7) == 0) part[w][r * NB + b] = v[0];
     }
+  } else {
+#pragma unroll
+    for (int r = 0; r < VEC_RPW; ++r)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc[r][b] += __shfl_xor(acc[r][b], o, 64);
+        if (lane == 0) part[w][r * NB + b] = acc[r][b];
+      }
+  }
   __syncthreads();
   if (threadIdx.x < VEC_RPW * NB) {
     const int r = threadIdx.x / NB, b = threadIdx.x % NB;
     if (r0 + r < rows && b < nb) {
-      const float v = ((part[0][threadIdx.x] + part[1][threadIdx.x]) + part[2][threadIdx.x]) + part[3][threadIdx.x];
-      dst[(r0 + r) + b * b_stride] = (scale ? scale[r0 + r] : 1.0f) * v;
+      const Acc v = ((part[0][threadIdx.x] + part[1][threadIdx.x]) + part[2][threadIdx.x]) + part[3][threadIdx.x];
+      dst[(r0 + r) + b * b_stride] = (float)((Acc)(scale ? scale[r0 + r] : 1.0f) * v);
     }
   }
 }
@@ -499,7 +516,7 @@ __device__ __forceinline__ void rows_times_vectors(const uint8_t* __restrict__ P
 // T[b * kq + c] = D[c] sum_j C[c][j] X[b][j] (kq = k rounded up to 4; the
 // padding entries are zero: B's padding trits are zero, and 0 times an
 // unset float could be NaN).  grid: ceil(k / VEC_RPW).
-template <int NB>
+template <int NB, typename Acc>
 __global__ __launch_bounds__(NT_AP) void k_apply_vec_c(const uint8_t* __restrict__ Cp, const float* __restrict__ D,
                                                         int64_t n, int64_t k, int64_t kq,
                                                         const float* __restrict__ X, int nb, float* __restrict__ T) {
@@ -507,15 +524,15 @@ __global__ __launch_bounds__(NT_AP) void k_apply_vec_c(const uint8_t* __restrict
     const int pad = (int)(kq - k);
     T[(threadIdx.x / pad) * kq + k + threadIdx.x % pad] = 0.0f;
   }
-  rows_times_vectors<NB, false>(Cp, k, n, (int64_t)blockIdx.x * VEC_RPW, X, n, nb, D, T, kq);
+  rows_times_vectors<NB, false, Acc>(Cp, k, n, (int64_t)blockIdx.x * VEC_RPW, X, n, nb, D, T, kq);
 }
 
 // Y[b * m + i] = sum_c B[i][c] T[b * kq + c].  grid: ceil(m / VEC_RPW).
-template <int NB>
+template <int NB, typename Acc>
 __global__ __launch_bounds__(NT_AP) void k_apply_vec_b(const uint8_t* __restrict__ Bp, int64_t m, int64_t k,
                                                         int64_t kq, const float* __restrict__ T, int nb,
                                                         float* __restrict__ Y) {
-  rows_times_vectors<NB, true>(Bp, m, k, (int64_t)blockIdx.x * VEC_RPW, T, kq, nb, nullptr, Y, m);
+  rows_times_vectors<NB, sizeof(Acc) == 4, Acc>(Bp, m, k, (int64_t)blockIdx.x * VEC_RPW, T, kq, nb, nullptr, Y, m);
 }
 
 // ---- one vector on integer matrix cores (nb = 1, n and k <= GV_MAX_LEN) ----
@@ -896,184 +913,317 @@ __global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void
 // ---- one vector, n or k beyond GV_MAX_LEN (both at most GV_LONG_MAX) ----
 //
 // The same integer sums, with the vector's digit planes brought into LDS a
-// segment of GV_MAX_SS super-steps at a time; the intermediate t is fp32 in
-// the workspace, and both sides are one kernel.  Bound by the memory's read
-// of the trits: 8192 x 28672, k = 20480 (189 MB) takes 68 us; fp32 FMA on
-// decoded trits, one byte a lane, was bound by the decode at 112 us.
+// segment of GL_SEG super-steps at a time; the intermediate t is fp32 in the
+// workspace, and both sides are one kernel.
 //
-// An entry at most GV_RANGE binades below the largest converts exactly.  A
-// vector with a smaller nonzero entry takes fp64 sums of decoded trits instead
-// (gl_wide): a row whose trits skip the large entries keeps its own relative
-// accuracy.  Every workgroup scans the whole vector, so all of them take the
-// same side.
-constexpr int64_t GV_LONG_MAX = 65536;  // int64 sums of 48-bit entries stay below 2^63
-constexpr int GV_RANGE = 22;
+// No bit of an entry is lost: with 2^up the power of two that brings the
+// largest entry below 2^30, v 2^up = A + B 2^-31, A the nearest integer and B
+// an integer below 2^31 in magnitude, four balanced digit planes each (the
+// MFMA's columns 6 and 7 were idle); the sums of A and of B are combined in
+// fp64.  Entries more than GL_RANGE binades below the largest wait for a
+// further pass over the row tiles, which starts from the largest of them, so
+// that a row whose trits skip the large entries keeps its own relative
+// accuracy; the passes are added in fp64.  Every workgroup scans the whole
+// vector, so all of them make the same passes.
+//
+// Converting the vector costs a workgroup about as much as multiplying it by
+// two 16-row tiles, so one workgroup of 16 waves per CU takes all of that CU's
+// tiles (up to GL_TMAX a round), and a segment's super-steps are split
+// between the waves (with few super-steps, the tiles between groups of waves).
+// Bound by the memory's read of the trits where there are many rows: 8192 x
+// 28672, k = 20480 (189 MB) takes 48 us, 3.9 TB/s; with few rows by the chain
+// scan, convert, multiply: m = 256, n = 28672, k = 500 takes 17.7 us.  With 32
+// rows to a workgroup of eight waves and byte-addressed loads 61.7 and 32.3 us;
+// fp32 FMA on decoded trits 105.6 and 22.6.  A vector of two passes: 102 and 32 us.
+constexpr int64_t GV_LONG_MAX = 65536;
+constexpr int GL_WAVES = 16, GL_NT = 64 * GL_WAVES;
+constexpr int GL_PLANES = 8;
+constexpr int GL_RANGE = 37;                   // binades below the largest entry that a pass converts
+constexpr int GL_BLK = GL_PLANES * 16 + 16;    // bytes of an (ss, i, g) block: the pad spreads a wave's stores over all banks
+constexpr int GL_SSB = 16 * GL_BLK;            // per super-step
+constexpr int GL_SEG = 64;                     // super-steps of a segment
+constexpr int GL_STEPS = GL_SEG / GL_WAVES;    // of a wave
+constexpr int GL_TMAX = 8;                     // 16-row tiles of a workgroup
+constexpr int GL_CUS = 256;                    // workgroups at a time, one per CU (LDS)
+static_assert(GL_TMAX * 16 * GL_PLANES == GL_NT, "one (tile, row, plane) sum per thread");
 
-// Rows r0 .. r0 + nrows - 1 by fp64 sums, eight rows at a time over the whole
-// workgroup (the lanes by a shuffle tree, then the waves in order).
-// red: LDS, 8 (GV_NT / 64) doubles.
-__device__ __forceinline__ void gl_wide(const uint8_t* __restrict__ P, int64_t rows, int64_t len, int64_t r0,
-                                        int nrows, const float* __restrict__ V, const float* __restrict__ scale,
-                                        float* __restrict__ dst, double* red) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t rb = (len + 3) >> 2;
-  for (int64_t q0 = r0; q0 < r0 + nrows && q0 < rows; q0 += 8) {
-    double acc[8] = {};
-    for (int64_t p = tid; p < rb; p += GV_NT) {
-      unsigned byte[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) byte[r] = P[(q0 + r < rows ? q0 + r : rows - 1) * rb + p];
-      double v[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) v[t] = 4 * p + t < len ? (double)V[4 * p + t] : 0.0;
-#pragma unroll
-      for (int r = 0; r < 8; ++r)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[r] = fma((double)trit_of(byte[r], t), v[t], acc[r]);
-    }
-    const int r = wave_sum8(acc);
-    if ((lane & 7) == 0) red[8 * wv + r] = acc[0];
-    __syncthreads();
-    if (tid < 8 && q0 + tid < rows) {
-      double y = 0.0;
-      for (int w = 0; w < (GV_NT / 64); ++w) y += red[8 * w + tid];
-      dst[q0 + tid] = (float)(scale ? y * (double)scale[q0 + tid] : y);
-    }
-    __syncthreads();
+// The 16 packed bytes of lane (rr, g) for super-step ss of the row at byte
+// offset `row` of P.  A chunk past the row is loaded from the row's start: it
+// meets zero digits, as do the bytes past the row's end.  ALIGNED: rb and the
+// base are multiples of 16.  Else (the base a multiple of 4, total >= 20) the
+// five words around the chunk, shifted into place by gl_trits: 16-byte
+// loads run at full rate at any word address, but take three times as long
+// off it.  Words past the matrix's last ones are loaded from its last 20
+// bytes (window_fix).
+template <bool ALIGNED>
+struct GlChunk {
+  unsigned w[ALIGNED ? 4 : 5];
+};
+__device__ __forceinline__ int64_t gl_offset(int64_t row, int rb, int ss, int g) {
+  const int o = ss * 64 + 16 * g;
+  return row + (o < rb ? o : 0);
+}
+template <bool ALIGNED>
+__device__ __forceinline__ GlChunk<ALIGNED> gl_load(const uint8_t* __restrict__ P, int64_t o, int64_t total) {
+  GlChunk<ALIGNED> c;
+  if constexpr (ALIGNED) {
+    __builtin_memcpy(c.w, __builtin_assume_aligned(P + o, 16), 16);
+  } else {
+    o &= ~(int64_t)3;
+    const uint8_t* A = P + (o < total - 20 ? o : total - 20);
+    __builtin_memcpy(c.w, A, 16);
+    __builtin_memcpy(&c.w[4], A + 16, 4);
   }
+  return c;
+}
+template <bool ALIGNED>
+__device__ __forceinline__ v4i_g gl_trits(GlChunk<ALIGNED> c, int64_t o, int64_t total) {
+  v4i_g v;
+  if constexpr (ALIGNED) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = (int)c.w[q];
+  } else {
+    if (__any((o & ~(int64_t)3) > total - 20)) window_fix<20>(o & ~(int64_t)3, total, c.w);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = (int)__builtin_amdgcn_alignbyte(c.w[q + 1], c.w[q], (unsigned)o & 3u);
+  }
+  return v;
 }
 
-// dst[i] = scale_i sum_c P_ic v_c (scale: fp32 per row, or null).  Every
-// workgroup forms max |v| itself (the same value in each), which fixes the
-// exponent; a non-finite entry makes every result NaN.  grid: ceil(rows /
-// GV_ROWS).
+// Super-steps first .. first + cnt - 1: the share of wave wk of ks of the ns
+// super-steps from super-step base on.
+struct GlShare {
+  int first, cnt;
+  __device__ __forceinline__ int step(int j) const { return first + j; }
+};
+__device__ __forceinline__ GlShare gl_share(int base, int ns, int wk, int ks) {
+  const int share = (ns + ks - 1) / ks, s0 = wk * share;
+  return GlShare{base + s0, min(max(ns - s0, 0), share)};
+}
+
+// dst[i] = scale_i sum_c P_ic v_c (scale: fp32 per row, or null).  A
+// non-finite entry makes every result NaN.  Workgroup b takes the 16-row
+// tiles b nt .. b nt + nt - 1, nt <= GL_TMAX, in groups of ks waves (a power
+// of two, at least a quarter of a segment's super-steps): group q takes tiles
+// q, q + GL_WAVES / ks, ...  grid: ceil(ceil(rows / 16) / nt).
 template <bool ALIGNED>
-__global__ __launch_bounds__(GV_NT) __attribute__((amdgpu_waves_per_eu(4))) void k_gemv_long(
-    const uint8_t* __restrict__ P, int64_t rows, int64_t len, const float* __restrict__ V,
-    const float* __restrict__ scale, float* __restrict__ dst) {
-  __shared__ __attribute__((aligned(16))) uint8_t dig[GV_MAX_SS * GV_SSB];
-  __shared__ __attribute__((aligned(16))) uint8_t zero16[16];
-  __shared__ int xch[GV_NT / 64][64][4];
-  __shared__ unsigned shm[2 * (GV_NT / 64)];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int nss = (int)((len + GV_SS - 1) / GV_SS);
-  const int64_t rb = (len + 3) >> 2;
-  const int64_t r0 = (int64_t)blockIdx.x * GV_ROWS;
-  if (tid < 4) ((int*)zero16)[tid] = 0;
-  // max |v| as the largest bit pattern (Inf and NaN above every number), and
-  // the smallest nonzero one (less one; zero wraps above them): four entries a
-  // load (any alignment), eight loads in flight
-  unsigned mb = 0u, mn = 0xffffffffu;
-  {
-    constexpr int U = 8;
-    const int64_t n4 = len >> 2;
-    for (int64_t c0 = tid; c0 < n4; c0 += U * GV_NT) {
-      unsigned v[U][4];
+__global__ __launch_bounds__(GL_NT) void k_gemv_long(const uint8_t* __restrict__ P, int64_t rows, int len,
+                                                     const float* __restrict__ V, const float* __restrict__ scale,
+                                                     float* __restrict__ dst, int nt, int ks) {
+  __shared__ __attribute__((aligned(16))) uint8_t dig[GL_SEG * GL_SSB];
+  __shared__ unsigned smm[2 * GL_WAVES];
+  __shared__ int sums[GL_NT];  // [tile][row][plane]: int32 is enough for 65536 x 128
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nss = (len + GV_SS - 1) / GV_SS, rb = (len + 3) >> 2;
+  const int64_t total = rows * rb, r0 = (int64_t)blockIdx.x * 16 * nt;
+  const int wk = wv & (ks - 1), t0 = wv / ks, dt = GL_WAVES / ks;
+  // a pass takes the entries of bit pattern lo .. mx; finite, and mn the
+  // smallest nonzero entry's pattern less one, from the first on
+  unsigned mx = 0u, mn = 0xffffffffu, lo = 0xffffffffu;
+  bool finite = true, later = false;
+  double y = 0.0;  // of the row that this thread sums
+  for (;;) {
+    // opaque, so that no address is kept in registers from pass to pass
+    int lane = tid & 63;
+    asm volatile("" : "+v"(lane));
+    const int g = lane >> 4, p = lane & (GL_PLANES - 1);
+    // byte offset of this lane's row of a tile (rows past the matrix: its last one)
+    auto row_of = [&](int t) {
+      const int64_t rr = r0 + 16 * t + (lane & 15);
+      return (rr < rows ? rr : rows - 1) * rb;
+    };
+    // Wave wv converts super-steps wv + GL_WAVES u of a segment.  Lane: trit
+    // position i, bytes 4 e4 .. + 3 of group g, i.e. components 64 g + 16 e4 +
+    // 4 j + i, j < 4: one word of each plane.
+    constexpr int NU = GL_SEG / GL_WAVES;
+    unsigned x[NU][4];
+    auto load_x = [&](int base) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) __builtin_memcpy(v[u], V + 4 * (c0 + u * GV_NT < n4 ? c0 + u * GV_NT : c0), 16);
+      for (int u = 0; u < NU; ++u) {
+        const int c = (base + wv + GL_WAVES * u) * GV_SS + 16 * (lane >> 2) + (lane & 3);
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+        for (int j = 0; j < 4; ++j) x[u][j] = __float_as_uint(V[(unsigned)(c + 4 * j < len ? c + 4 * j : 0)]);
+      }
+    };
+    load_x(0);
+    // the first trits after them (a wait for x then does not wait for it)
+    __builtin_amdgcn_sched_barrier(0);
+    GlChunk<ALIGNED> buf[GL_STEPS];
+    int64_t row = row_of(t0);
+    {
+      const GlShare sh = gl_share(0, nss < GL_SEG ? nss : GL_SEG, wk, ks);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const unsigned a = v[u][e] & 0x7fffffffu;
-          mb = max(mb, a);
-          mn = min(mn, a - 1u);
-        }
+      for (int j = 0; j < GL_STEPS; ++j)
+        buf[j] = gl_load<ALIGNED>(P, j < sh.cnt ? gl_offset(row, rb, sh.step(j), g) : 0, total);
     }
-    if (4 * n4 + tid < len) {
-      const unsigned a = __float_as_uint(V[4 * n4 + tid]) & 0x7fffffffu;
-      mb = max(mb, a);
-      mn = min(mn, a - 1u);
+    __builtin_amdgcn_sched_barrier(0);
+    // the largest |v| (below lo) and the smallest nonzero one, as bit patterns
+    // (Inf and NaN above every number; zero minus one above them): the first
+    // segment's from x, then four entries a load (any alignment), four loads in
+    // flight
+    mx = 0u;
+    if (later) {
+      constexpr int U = 8;
+      for (int c0 = tid; c0 < len; c0 += U * GL_NT) {
+        unsigned v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = __float_as_uint(V[c0 + u * GL_NT < len ? c0 + u * GL_NT : c0]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const unsigned a = v[u] & 0x7fffffffu;
+          mx = max(mx, a < lo ? a : 0u);
+        }
+      }
+    } else {
+      auto take = [&](unsigned v) {
+        const unsigned a = v & 0x7fffffffu;
+        mx = max(mx, a);
+        mn = min(mn, a - 1u);
+      };
+      constexpr int U = 4;
+      const int n4 = len >> 2;
+      for (int c0 = GL_SEG * GV_SS / 4 + tid; c0 < n4; c0 += U * GL_NT) {
+        unsigned v[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) __builtin_memcpy(v[u], V + 4 * (c0 + u * GL_NT < n4 ? c0 + u * GL_NT : c0), 16);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) take(v[u][e]);
+      }
+      if (4 * n4 + tid < len) take(__float_as_uint(V[4 * n4 + tid]));
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) take(x[u][j]);  // (entries past the vector repeat its first)
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
-      mb = max(mb, (unsigned)__shfl_xor((int)mb, o, 64));
+      mx = max(mx, (unsigned)__shfl_xor((int)mx, o, 64));
       mn = min(mn, (unsigned)__shfl_xor((int)mn, o, 64));
     }
     if (lane == 0) {
-      shm[wv] = mb;
-      shm[GV_NT / 64 + wv] = mn;
+      smm[wv] = mx;
+      smm[GL_WAVES + wv] = mn;
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < GV_NT / 64; ++q) {
-      mb = max(mb, shm[q]);
-      mn = min(mn, shm[GV_NT / 64 + q]);
+    for (int q = 0; q < GL_WAVES; ++q) {
+      mx = max(mx, smm[q]);
+      mn = min(mn, smm[GL_WAVES + q]);
     }
-  }
-  const bool finite = mb < 0x7f800000u;
-  // biased exponents (denormals: that of the smallest normal number)
-  if (finite && mb != 0u && max((int)(mb >> 23), 1) - max((int)((mn + 1u) >> 23), 1) > GV_RANGE) {
-    gl_wide(P, rows, len, r0, GV_ROWS, V, scale, dst, (double*)dig);
-    return;
-  }
-  const int s_v = gv_shift(finite ? (double)__uint_as_float(mb) : 0.0);
-  // v 2^s rounded (ties to even) by adding 1.5 2^52: the difference of the bit
-  // patterns is the integer
-  const double p2s = ldexp(1.0, s_v), magic = 6755399441055744.0;
-  const long long debias = 0x8080808080ll - __double_as_longlong(magic);
-  int out[4] = {0, 0, 0, 0};
-  for (int base = 0; base < nss; base += GV_MAX_SS) {
-    const int ns = nss - base < GV_MAX_SS ? nss - base : GV_MAX_SS;
-    // unit w of the segment: trit position i, bytes 4 e4 .. + 3 of group g of
-    // super-step ss, i.e. components 64 g + 16 e4 + 4 j + i, j < 4: one word
-    // of each plane
-    constexpr int NU = GV_MAX_SS * 64 / GV_NT;
-    static_assert(GV_MAX_SS * 64 % GV_NT == 0, "whole units per thread");
-    const float* Vs = V + (int64_t)base * GV_SS;
-    const int left = (int)(len - (int64_t)base * GV_SS);  // entries from the segment on
-    float x[NU][4];
+    mx = __builtin_amdgcn_readfirstlane(mx);
+    mn = __builtin_amdgcn_readfirstlane(mn);
+    finite = mx < 0x7f800000u;
+    // biased exponent (denormals: that of the smallest normal number)
+    const int emax = max((int)(mx >> 23), 1);
+    lo = emax > GL_RANGE + 1 ? (unsigned)(emax - GL_RANGE) << 23 : 0u;
+    const bool part = finite && (mn + 1u < lo || later);
+    // v 2^up = A + B 2^-31 with A = rint(v 2^up), |A| <= 2^30
+    const int up = 156 - emax;
+    sums[tid] = 0;
+    for (int base = 0; base < nss; base += GL_SEG) {
+      const int ns = nss - base < GL_SEG ? nss - base : GL_SEG;
+      const int left = len - base * GV_SS;  // entries from the segment on
+      const GlShare sh = gl_share(base, ns, wk, ks);
+      if (part)  // uniform
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int w = tid + GV_NT * u, c = (w >> 6) * GV_SS + 16 * ((w >> 2) & 15) + (w & 3);
+        for (int u = 0; u < NU; ++u)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) x[u][j] = Vs[c + 4 * j < left ? c + 4 * j : 0];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    const GvWave v = gv_wave(P, rows, rb, ns, r0, base);
-    v4i_g buf[GV_NSTEP];
-    gv_prefetch<ALIGNED>(v, rb, buf);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();  // the previous segment has been read
+          for (int j = 0; j < 4; ++j) {
+            const unsigned a = x[u][j] & 0x7fffffffu;
+            x[u][j] = a >= lo && a <= mx ? x[u][j] : 0u;
+          }
+      __syncthreads();  // the previous segment has been read
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int w = tid + GV_NT * u, ss = w >> 6, g = (w >> 4) & 3, e4 = (w >> 2) & 3, i = w & 3;
-      const int c = ss * GV_SS + 16 * ((w >> 2) & 15) + i;
-      unsigned lo[4], hi[4];
+      for (int u = 0; u < NU; ++u) {
+        const int ss = wv + GL_WAVES * u, ug = lane >> 4, e4 = (lane >> 2) & 3, i = lane & 3;
+        if (ss >= ns) continue;  // uniform
+        const int c = ss * GV_SS + 16 * (lane >> 2) + i;
+        unsigned lo[4], hi[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const double t = fma((double)(c + 4 * j < left && finite ? x[u][j] : 0.0f), p2s, magic);
-        const unsigned long long q = (unsigned long long)(__double_as_longlong(t) + debias);
-        lo[j] = (unsigned)q;
-        hi[j] = (unsigned)(q >> 32);
+        for (int j = 0; j < 4; ++j) {
+          const float v = __builtin_amdgcn_ldexpf(c + 4 * j < left ? __uint_as_float(x[u][j]) : 0.0f, up);
+          const float a = rintf(v);
+          hi[j] = (unsigned)((int)a + 0x00808080);  // (digits re-centred)
+          lo[j] = (unsigned)((int)((v - a) * 0x1p31f) + 0x00808080);
+        }
+        // byte p of the four words is plane p's word
+        unsigned pl[GL_PLANES];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const unsigned* q = h ? hi : lo;
+          const unsigned a0 = __builtin_amdgcn_perm(q[1], q[0], 0x05010400u), a1 = __builtin_amdgcn_perm(q[1], q[0], 0x07030602u);
+          const unsigned b0 = __builtin_amdgcn_perm(q[3], q[2], 0x05010400u), b1 = __builtin_amdgcn_perm(q[3], q[2], 0x07030602u);
+          pl[4 * h + 0] = __builtin_amdgcn_perm(b0, a0, 0x05040100u) ^ 0x80808080u;
+          pl[4 * h + 1] = __builtin_amdgcn_perm(b0, a0, 0x07060302u) ^ 0x80808080u;
+          pl[4 * h + 2] = __builtin_amdgcn_perm(b1, a1, 0x05040100u) ^ 0x80808080u;
+          pl[4 * h + 3] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+        }
+        unsigned* d = (unsigned*)(dig + ss * GL_SSB + (i * 4 + ug) * GL_BLK) + e4;
+#pragma unroll
+        for (int q = 0; q < GL_PLANES; ++q) d[4 * q] = pl[q];
       }
-      // byte p of the four words is plane p's word
-      const unsigned a0 = __builtin_amdgcn_perm(lo[1], lo[0], 0x05010400u), a1 = __builtin_amdgcn_perm(lo[1], lo[0], 0x07030602u);
-      const unsigned b0 = __builtin_amdgcn_perm(lo[3], lo[2], 0x05010400u), b1 = __builtin_amdgcn_perm(lo[3], lo[2], 0x07030602u);
-      const unsigned a2 = __builtin_amdgcn_perm(hi[1], hi[0], 0x05010400u), b2 = __builtin_amdgcn_perm(hi[3], hi[2], 0x05010400u);
-      if (ss < ns) {
-        unsigned* d = (unsigned*)(dig + (int64_t)ss * GV_SSB + (((i * 4 + g) * GV_PLANES) << 4)) + e4;
-        d[0] = __builtin_amdgcn_perm(b0, a0, 0x05040100u) ^ 0x80808080u;
-        d[4] = __builtin_amdgcn_perm(b0, a0, 0x07060302u) ^ 0x80808080u;
-        d[8] = __builtin_amdgcn_perm(b1, a1, 0x05040100u) ^ 0x80808080u;
-        d[12] = __builtin_amdgcn_perm(b1, a1, 0x07060302u) ^ 0x80808080u;
-        d[16] = __builtin_amdgcn_perm(b2, a2, 0x05040100u) ^ 0x80808080u;
-        d[20] = __builtin_amdgcn_perm(b2, a2, 0x07060302u);
+      // the next segment's entries, in flight during the products (!ALIGNED has
+      // no registers for them)
+      if (ALIGNED && base + GL_SEG < nss) load_x(base + GL_SEG);
+      __syncthreads();
+#pragma unroll 1
+      for (int t = t0; t < nt; t += dt) {
+        // what follows: the group's next tile, or the next segment's first one
+        const bool wrap = t + dt >= nt, more = !wrap || base + GL_SEG < nss;
+        const int64_t next = row_of(wrap ? t0 : t + dt);
+        const int base2 = base + GL_SEG;
+        const GlShare sh2 = wrap ? gl_share(base2, nss - base2 < GL_SEG ? nss - base2 : GL_SEG, wk, ks) : sh;
+        v4i_g acc[4][2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][0] = acc[i][1] = v4i_g{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < GL_STEPS; ++j) {
+          if (j < sh.cnt) {  // uniform
+            const v4i_g w = gl_trits<ALIGNED>(buf[j], gl_offset(row, rb, sh.step(j), g), total);
+            // columns 8 .. 15 repeat 0 .. 7; they are not read
+            const uint8_t* bsrc = dig + (sh.step(j) - base) * GL_SSB + g * GL_BLK + 16 * p;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const v4i_g bo = *(const v4i_g*)(bsrc + i * 4 * GL_BLK);
+              const v4i_g a0 = w & (0x01010101 << (2 * i)), a1 = w & (0x02020202 << (2 * i));
+              acc[i][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bo, acc[i][0], 0, 0, 0);
+              acc[i][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bo, acc[i][1], 0, 0, 0);
+            }
+          }
+          // the step after it in the same place, in flight during this tile's other
+          // steps; no branch (its merge would wait for every load in flight): where
+          // there is none, the matrix's first bytes
+          buf[j] = gl_load<ALIGNED>(P, more && j < sh2.cnt ? gl_offset(next, rb, sh2.step(j), g) : 0, total);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if ((lane & 15) < GL_PLANES && sh.cnt > 0)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            atomicAdd(&sums[(16 * t + 4 * g + r) * GL_PLANES + p],
+                      ((acc[0][0][r] - acc[0][1][r])) + ((acc[1][0][r] - acc[1][1][r]) >> 2) +
+                          ((acc[2][0][r] - acc[2][1][r]) >> 4) + ((acc[3][0][r] + acc[3][1][r]) >> 6));
+        row = next;
       }
+      if (!ALIGNED && base + GL_SEG < nss) load_x(base + GL_SEG);
     }
+    // each row's planes combine: the exact sum of the pass, rounded once (both
+    // halves are below 2^53)
     __syncthreads();
-    int o[4];
-    gv_tile<ALIGNED>(v, rb, buf, dig, zero16, o);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) out[r] += o[r];
+    long long v = (long long)sums[tid] << (8 * (p & 3));
+    v += __shfl_xor(v, 1, 64);
+    v += __shfl_xor(v, 2, 64);
+    const long long vh = __shfl_xor(v, 4, 64);
+    y += ldexp(fma((double)vh, 0x1p31, (double)v), -31 - up);
+    if (!finite || mn + 1u >= lo) break;
+    later = true;
   }
-  const long long y = gv_combine(out, xch);
-  if (wv % GV_KSPLIT == 0 && lane < 16) {
-    const int64_t i = r0 + 16 * (wv / GV_KSPLIT) + lane;
-    if (i < rows) {
-      const double r = finite ? ldexp((double)y, -s_v) : NAN;
-      dst[i] = (float)(scale ? r * (double)scale[i] : r);
-    }
+  const int rt = tid / (16 * GL_PLANES);
+  const int64_t i = r0 + tid / GL_PLANES;
+  if (tid % GL_PLANES == 0 && rt < nt && i < rows) {
+    const double r = finite ? y : NAN;
+    dst[i] = (float)(scale ? r * (double)scale[i] : r);
   }
 }
 
@@ -1171,11 +1321,11 @@ template <int NB>
 static hipError_t run_vec(const uint8_t* Bp, const uint8_t* Cp, const float* D, int64_t m, int64_t n, int64_t k,
                           const float* X, int nb, float* Y, float* T, hipStream_t s) {
   const int64_t kq = (k + 3) & ~(int64_t)3;
-  hipLaunchKernelGGL(k_apply_vec_c<NB>, dim3((unsigned)((k + VEC_RPW - 1) / VEC_RPW)), dim3(NT_AP), 0, s, Cp, D, n, k,
+  hipLaunchKernelGGL((k_apply_vec_c<NB, float>), dim3((unsigned)((k + VEC_RPW - 1) / VEC_RPW)), dim3(NT_AP), 0, s, Cp, D, n, k,
                      kq, X, nb, T);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_apply_vec_b<NB>, dim3((unsigned)((m + VEC_RPW - 1) / VEC_RPW)), dim3(NT_AP), 0, s, Bp, m, k,
+  hipLaunchKernelGGL((k_apply_vec_b<NB, float>), dim3((unsigned)((m + VEC_RPW - 1) / VEC_RPW)), dim3(NT_AP), 0, s, Bp, m, k,
                      kq, (const float*)T, nb, Y);
   return hipGetLastError();
 }
@@ -1201,22 +1351,57 @@ static hipError_t run_gemv(const uint8_t* Bp, const uint8_t* Cp, const float* D,
   return hipGetLastError();
 }
 
+// Tiles a workgroup: as few as fill one round of the CUs, at most GL_TMAX.
 static hipError_t launch_gemv_long(const uint8_t* P, int64_t rows, int64_t len, const float* V, const float* scale,
                                    float* dst, hipStream_t s) {
-  const dim3 grid((unsigned)((rows + GV_ROWS - 1) / GV_ROWS));
-  if (((len + 3) / 4) % 16 == 0 && ((uintptr_t)P % 16) == 0)
-    hipLaunchKernelGGL(k_gemv_long<true>, grid, dim3(GV_NT), 0, s, P, rows, len, V, scale, dst);
+  const int64_t tiles = (rows + 15) / 16;
+  const int64_t wgs = (tiles + GL_CUS * GL_TMAX - 1) / (GL_CUS * GL_TMAX) * GL_CUS;  // of whole rounds
+  const int nt = (int)((tiles + wgs - 1) / wgs);
+  const dim3 grid((unsigned)((tiles + nt - 1) / nt));
+  // few super-steps: several tiles at a time
+  const int64_t nss = (len + GV_SS - 1) / GV_SS;
+  int ks = GL_WAVES;
+  while (ks > 1 && GL_WAVES / (ks / 2) <= nt && ks / 2 * GL_STEPS >= nss) ks /= 2;
+  const bool al = ((len + 3) / 4) % 16 == 0 && ((uintptr_t)P % 16) == 0;
+  if (al)
+    hipLaunchKernelGGL(k_gemv_long<true>, grid, dim3(GL_NT), 0, s, P, rows, (int)len, V, scale, dst, nt, ks);
   else
-    hipLaunchKernelGGL(k_gemv_long<false>, grid, dim3(GV_NT), 0, s, P, rows, len, V, scale, dst);
+    hipLaunchKernelGGL(k_gemv_long<false>, grid, dim3(GL_NT), 0, s, P, rows, (int)len, V, scale, dst, nt, ks);
   return hipGetLastError();
+}
+
+// Which kernel takes a side (rows x len) of one long vector: k_gemv_long, or
+// fp64 sums of decoded trits (k_apply_vec_c, k_apply_vec_b).  The latter has no
+// scan and conversion, about 2 us, but takes longer per trit.  us,
+// k_gemv_long against fp64 sums, rows x len: 256 x 512 5.1, 3.6; 2048 x 4096
+// 5.7, 5.4; 2048 x 6001 7.6, 6.8; 16 x 8192 6.4, 7.6; 4096 x 4096 6.0, 6.6; 8192
+// x 1000 6.2, 5.9; 8192 x 2048 6.2, 7.4; 12288 x 64 5.8, 6.4; 16384 x 512 5.7, 8.1.
+// k_gemv_long reads whole words (a base off them is a caller's slice) and at
+// least 20 bytes.
+static bool long_side(const uint8_t* P, int64_t rows, int64_t len) {
+  return ((uintptr_t)P & 3u) == 0 && rows * ((len + 3) >> 2) >= 20 &&
+         (len > 6144 || rows * (len + 1024) >= (int64_t)16 << 20);
 }
 
 static hipError_t run_apply_kernels(const uint8_t* Bp, const uint8_t* Cp, const float* D, int64_t m, int64_t n,
                                     int64_t k, const float* X, int nb, float* Y, char* ws, hipStream_t s) {
   if (gemv_fits(n, k, nb)) return run_gemv(Bp, Cp, D, m, n, k, X, Y, ws, s);
   if (gemv_long(n, k, nb)) {
-    const hipError_t e = launch_gemv_long(Cp, k, n, X, D, (float*)ws, s);
-    return e != hipSuccess ? e : launch_gemv_long(Bp, m, k, (const float*)ws, nullptr, Y, s);
+    const int64_t kq = (k + 3) & ~(int64_t)3;
+    float* T = (float*)ws;
+    hipError_t e;
+    if (long_side(Cp, k, n)) {
+      e = launch_gemv_long(Cp, k, n, X, D, T, s);
+    } else {
+      hipLaunchKernelGGL((k_apply_vec_c<1, double>), dim3((unsigned)((k + VEC_RPW - 1) / VEC_RPW)), dim3(NT_AP), 0, s,
+                         Cp, D, n, k, kq, X, 1, T);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess) return e;
+    if (long_side(Bp, m, k)) return launch_gemv_long(Bp, m, k, T, nullptr, Y, s);
+    hipLaunchKernelGGL((k_apply_vec_b<1, double>), dim3((unsigned)((m + VEC_RPW - 1) / VEC_RPW)), dim3(NT_AP), 0, s, Bp,
+                       m, k, kq, (const float*)T, 1, Y);
+    return hipGetLastError();
   }
   if (nb <= AP_VEC_MAX) return run_vec<AP_VEC_MAX>(Bp, Cp, D, m, n, k, X, nb, Y, (float*)ws, s);
   const ApplyLayout L = apply_layout(m, n, k, nb);

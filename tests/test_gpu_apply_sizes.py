@@ -1,16 +1,16 @@
 """Inference at the sizes where its loads and segments have edges: packed rows
 of any byte length at any byte address, matrices shorter than one load window,
 and one vector past the length that a workgroup holds at once (more than
-10240 components: segments of 10240, up to 65536, with the intermediate
+10240 components: segments of 16384, up to 65536, with the intermediate
 rounded to fp32).
 
 The packed matrices lie in buffers whose other bytes are all ones (trit code
 11, i.e. -1), so a byte taken from past a row or a matrix shows in the result.
 Tolerances.  As derived in test_gpu_apply.py, one vector is exact integer sums
 between two fixed-point conversions, more are fp32 sums of exact products.  One
-long vector is converted without loss and summed exactly, or, where its entries
-span more than 22 binades, summed in fp64 (n + k + 4 roundings of 2^-53 of the
-absolute sum); t and y are rounded to fp32 (u |B| |t| and u |y|).  No bound of
+long vector is converted without loss and summed exactly by groups of 38 binades,
+added in fp64, or summed in fp64 where its side is small (n + k + 4 roundings of
+2^-53 of the absolute sum); t and y are rounded to fp32 (u |B| |t| and u |y|).  No bound of
 it names the largest entry.
 """
 import numpy as np
@@ -96,6 +96,15 @@ def test_one_long_vector(m, n, k):
     check(m, n, k, 1, 1, lambda rng, shape: np.exp2(rng.integers(-20, 1, size=shape)))
 
 
+@pytest.mark.parametrize("m,n,k", [(4096, 10241, 20), (4097, 10241, 20), (12289, 10300, 61), (32768, 10241, 16),
+                                   (32769, 10241, 16), (9, 16640, 4100), (4113, 33, 16641)])
+def test_one_long_vector_tiles(m, n, k):
+    """Workgroups of one, two, more and the most row tiles, also over several
+    segments, on each side; rows off every load width, at word addresses and off them."""
+    for offset in (0, 4, 6):
+        check(m, n, k, 1, offset)
+
+
 @pytest.mark.parametrize("gap", [20, 24, 30, 38, 39, 40, 60, 120])
 @pytest.mark.parametrize("side", ["x", "t"])
 def test_long_vector_small_entries(side, gap):
@@ -136,6 +145,12 @@ def test_one_long_vector_past_the_segments():
     assert small == 256         # 12 floats: the fp32 path past 65536
 
 
+def test_long_vector_spread():
+    """Entries over 120 binades: several passes of k_gemv_long on either side."""
+    check(35, 12005, 50, 1, 0, lambda rng, shape: np.exp2(rng.integers(-120, 1, size=shape)))
+    check(40, 17000, 700, 1, 4, lambda rng, shape: np.exp2(rng.integers(-100, 1, size=shape) * (rng.random(shape) < 0.01)))
+
+
 def test_long_vector_nonfinite():
     from paper_2607_13511_amd import binding
     C = np.ones((4, 12000), np.int8)
@@ -144,5 +159,16 @@ def test_long_vector_nonfinite():
         X = np.ones((1, 12000), np.float32)
         X[0, 11999] = bad
         Y = binding.apply(place(pack(B), 0), place(pack(C), 0), torch.ones(4, device="cuda"), 3, 12000,
+                          torch.from_numpy(X).cuda())
+        assert torch.isnan(Y).all()
+
+
+def test_small_side_nonfinite():
+    from paper_2607_13511_amd import binding
+    C, B = np.ones((12000, 20), np.int8), np.ones((3, 12000), np.int8)
+    for bad in (np.nan, np.inf):
+        X = np.ones((1, 20), np.float32)
+        X[0, 19] = bad
+        Y = binding.apply(place(pack(B), 0), place(pack(C), 0), torch.ones(12000, device="cuda"), 3, 20,
                           torch.from_numpy(X).cuda())
         assert torch.isnan(Y).all()
