@@ -2,7 +2,7 @@
 of any byte length at any byte address, matrices shorter than one load window,
 and one vector past the length that a workgroup holds at once (more than
 10240 components: segments of 16384, up to 65536, with the intermediate
-rounded to fp32).
+rounded to fp32; fp32 sums past 65536).
 
 The packed matrices lie in buffers whose other bytes are all ones (trit code
 11, i.e. -1), so a byte taken from past a row or a matrix shows in the result.
@@ -54,7 +54,9 @@ def check(m, n, k, nb, offset, scale=None):
     Bf, Cf = np.abs(B).astype(np.float64), np.abs(C).astype(np.float64)
     if nb == 1:
         mx, sx, md = np.max(np.abs(X)), np.sum(np.abs(X)), np.max(np.abs(D))
-        if max(n, k) > 10240:
+        if max(n, k) > 65536:
+            bound = (n + k + 4) * U * (Bf @ (np.abs(D) * (Cf @ np.abs(X[0]))))
+        elif max(n, k) > 10240:
             bound = long_bound(B, C, D, X[0], ref)
         else:
             q = Bf @ (np.abs(D) * Cf.sum(axis=1)) * mx + Bf.sum(axis=1) * md * sx
@@ -138,11 +140,14 @@ def test_long_vector_small_entries(side, gap):
     assert np.all(np.abs(Y[0] - ref[0]) <= bound)
 
 
-def test_one_long_vector_past_the_segments():
-    check(6, 65537, 12, 3, 0)   # several vectors take the slices at any length
-    from paper_2607_13511_amd import binding
-    small = binding.lib().externd_apply_workspace_bytes(6, 65537, 12, 1)
-    assert small == 256         # 12 floats: the fp32 path past 65536
+@pytest.mark.parametrize("m,n,k", [(6, 65537, 12), (9, 20, 65537)])
+def test_one_vector_past_the_long_path(m, n, k):
+    check(m, n, k, 1, 0)
+    check(m, n, k, 1, 1)
+
+
+def test_several_long_vectors():
+    check(6, 65537, 12, 3, 0)   # the slices, at any length
 
 
 def test_long_vector_spread():
