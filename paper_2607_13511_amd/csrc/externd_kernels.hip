@@ -1593,6 +1593,7 @@ struct WideSide {
   double* panel;         // block (k, j) at (k NQMAX + j) 4096: A_kj at step k
   double* pivot;         // block k: P of step k
   double* ginv;          // out: block (q, q') at (q NQMAX + q') 4096, ginv_index order
+  double* mat;           // mode 2, out: the matrix itself, in the same layout
   int* wflag;            // out: 1 for a zero trace
   unsigned* sync;        // WIDE_SYNC_WORDS, zero at the start; cleared by a later launch
   int* flags;
@@ -1690,6 +1691,8 @@ __device__ __forceinline__ v4d wide_tile(const double* src, int a, int b) {
 }
 
 // Workgroup b of the side path (b < wide_side_wgs(nq)).  smem: WIDE_SMEM.
+// JOINT: mode 2.
+template <bool JOINT>
 __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) {
   const int nq = a.nq, ngram = wide_gram_wgs(nq);
   if (b < ngram) {
@@ -1728,7 +1731,7 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
   if ((int)threadIdx.x < bb) {
     const int c = threadIdx.x, qc = c / BBP, cl = c % BBP;
     dv = gram(pair_index(qc, qc, nq), cl * 65);
-    if (a.mode == 2) dv *= a.raw[(int64_t)c * BMAX + c];
+    if (JOINT) dv *= a.raw[(int64_t)c * BMAX + c];
   }
   // the block of this workgroup, in the accumulator layout
   v4d acc[4];
@@ -1759,10 +1762,17 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
       const int gi = BBP * i + 16 * w + lk + 4 * r, gj = BBP * j + 16 * nt + li;
       const bool real = gi < bb && gj < bb;
       double v = real ? acc[nt][r] : 0.0;
-      if (a.mode == 2) v *= real ? a.raw[(int64_t)gi * BMAX + gj] : 0.0;
+      if (JOINT) v *= real ? a.raw[(int64_t)gi * BMAX + gj] : 0.0;
       else if (a.raw) a.raw[(int64_t)gi * BMAX + gj] = v;
       acc[nt][r] = gi == gj ? (real && !zero ? v + ridge : 1.0) : (zero ? 0.0 : v);
     }
+  // (the matrix is symmetric: stored as G^{-1} below)
+  if (JOINT)
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        a.mat[(int64_t)(j * NQMAX + i) * 4096 + (nt * 16 + 4 * w + r) * 64 + lane] = acc[nt][r];
 #pragma unroll 1
   for (int k = 0; k < nq; ++k) {
     const bool row = i == k, col = j == k;
@@ -1803,7 +1813,17 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
       v4d P[4];
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) {
-        const v4d y = get_tile(Pt + 128 * (4 * w + nt));
+        v4d y = get_tile(Pt + 128 * (4 * w + nt));
+        if (JOINT) {
+          // the mean with the transpose: the rows of a later quarter take A_ki^T P
+          // where the columns take P A_kj, and where M is singular but for its
+          // guard (components alike in two quarters) 1e-6 between the two would
+          // outweigh the scales
+          const double* T = (const double*)(Pt + 128 * (4 * nt + w));
+#pragma unroll
+          for (int r = 0; r < 4; ++r)  // row li, column lk + 4 r of tile (nt, w)
+            y[r] = 0.5 * (y[r] + T[128 * (li >> 3) + 2 * (16 * (li & 3) + lk + 4 * r) + ((li >> 2) & 1)]);
+        }
         const double sg = (nt < nb && w < nb) ? -1.0 : 1.0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) P[nt][r] = ldexp(sg * y[r], -(sexp[16 * w + lk + 4 * r] + sexp[16 * nt + li]));
@@ -1892,9 +1912,10 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
 
 // The side path alone (the joint solve at a block's end, the step entry
 // points).  grid: wide_side_wgs(nq).
+template <bool JOINT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_wide_side(WideSide a) {
   __shared__ __attribute__((aligned(16))) char smem[WIDE_SMEM];
-  wide_side(a, (int)blockIdx.x, smem);
+  wide_side<JOINT>(a, (int)blockIdx.x, smem);
 }
 
 // Clears the Gram blocks (nclr words) and the arrival words of a side path
@@ -1957,7 +1978,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   static_assert(sizeof(WidePlanes) <= WIDE_SMEM, "the side path's LDS holds the planes");
   const int nsd = wide_side_wgs(side.nq);
   if ((int)blockIdx.x < nsd) {
-    wide_side(side, (int)blockIdx.x, smem);
+    wide_side<false>(side, (int)blockIdx.x, smem);
     return;
   }
   WidePlanes& sp = *(WidePlanes*)smem;
@@ -2077,7 +2098,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
   __shared__ __attribute__((aligned(16))) char smem[WIDE_SMEM];
   const int nsd = wide_side_wgs(side.nq);
   if ((int)blockIdx.x < nsd) {
-    wide_side(side, (int)blockIdx.x, smem);
+    wide_side<false>(side, (int)blockIdx.x, smem);
     return;
   }
   union Lds {
@@ -3929,32 +3950,56 @@ __global__ void k_set_scales(const double* __restrict__ d, int bb, double* dvec,
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-// Joint scales of a wide block, d = M^{-1} g (Eq. (4)) with M^{-1} in blocks
-// (k_wide_side) and g_c = diag(U^T Q)_c (the per-split partial sums in split
-// order); zero trace: d = 0.  d into dvec, dF (fp32) and D (the block's
-// output).  One workgroup; row c of the product by thread c (columns in
-// order).  Also clears the side path's Gram blocks and arrival words.
-__global__ __launch_bounds__(NT) void k_wide_scales(const double* __restrict__ ginv, const double* __restrict__ gvec,
-                                                    int bb, const int* __restrict__ wflag, double* dvec, float* dF,
-                                                    float* Dout, int* gacc, int nclr, unsigned* sync) {
-  __shared__ double g[BMAX];
-  const int c = threadIdx.x;  // BMAX == NT
-  double gc = 0.0;
+// Joint scales of a wide block, d = M^{-1} g (Eq. (4)) with M^{-1} and M in
+// blocks (k_wide_side) and g_c = diag(U^T Q)_c (the per-split partial sums in
+// split order), refined once, d += M^{-1} (g - M d): the rounding of the inverse
+// of a nearly singular M (components alike) is 1e-7 of the block's energy
+// decrease, after it 1e-14.  Zero trace: d = 0.  d into dvec, dF (fp32) and D (the
+// block's output).  One workgroup of 4 x BMAX threads: row c = tid % BMAX of the
+// products, quarter tid / BMAX of their columns in order, the quarters added in
+// order.  Bound by the latency of the columns' loads: with a row a thread 18 us
+// for one product, now 27 for the three.  Also clears the side path's Gram
+// blocks and arrival words.
+__global__ __launch_bounds__(4 * BMAX) void k_wide_scales(const double* __restrict__ ginv,
+                                                          const double* __restrict__ mat,
+                                                          const double* __restrict__ gvec, int bb,
+                                                          const int* __restrict__ wflag, double* dvec, float* dF,
+                                                          float* Dout, int* gacc, int nclr, unsigned* sync) {
+  __shared__ double x[BMAX], part[NQMAX][BMAX];
+  static_assert(BMAX == NQMAX * BBP, "one column quarter per thread group");
+  const int c = threadIdx.x % BMAX, h = __builtin_amdgcn_readfirstlane(threadIdx.x / BMAX);
+  const bool live = h * BBP < bb && c < bb;
+  double g = 0.0;
   if (c < bb)
 #pragma unroll
-    for (int k = 0; k < TERN_SPLIT_MAX; ++k) gc += gvec[c * TERN_SPLIT_MAX + k];
-  g[c] = gc;
+    for (int k = 0; k < TERN_SPLIT_MAX; ++k) g += gvec[c * TERN_SPLIT_MAX + k];
+  // row c of A x (x zero past bb), in every thread of the row
+  auto times = [&](const double* __restrict__ A, double v) {
+    __syncthreads();
+    if (h == 0) x[c] = v;
+    __syncthreads();
+    double s = 0.0;
+    if (live) {
+      const double* row = A + (int64_t)((c / BBP) * NQMAX + h) * 4096;
+#pragma unroll 32
+      for (int e = 0; e < BBP; ++e) s += row[ginv_index(c % BBP, e)] * x[BBP * h + e];
+    }
+    part[h][c] = s;
+    __syncthreads();
+    return ((part[0][c] + part[1][c]) + part[2][c]) + part[3][c];
+  };
   wide_clear(gacc, nclr, sync, 0, 1);
-  __syncthreads();
   double d = 0.0;
-  if (c < bb && *wflag == 0) {
-    const double* row = ginv + (int64_t)(c / BBP) * NQMAX * 4096;
-#pragma unroll 8
-    for (int c2 = 0; c2 < bb; ++c2) d += row[(c2 / BBP) * 4096 + ginv_index(c % BBP, c2 % BBP)] * g[c2];
+  if (*wflag == 0) {  // uniform
+    d = times(ginv, g);
+    const double r = g - times(mat, d);
+    d += times(ginv, r);
   }
-  dvec[c] = d;
-  dF[c] = (float)d;
-  if (Dout && c < bb) Dout[c] = (float)d;
+  if (h == 0) {
+    dvec[c] = d;
+    dF[c] = (float)d;
+    if (Dout && c < bb) Dout[c] = (float)d;
+  }
 }
 
 static inline unsigned grid_for(int64_t total) {
@@ -4193,7 +4238,7 @@ hipError_t launch_ustep_wide(const Ws& w, int blk, int bb, double tau, bool weig
 // joint solve; the factorization leaves it from its last U-step).
 hipError_t launch_gram_wide_raw(const Ws& w, int bb, bool weighted, hipStream_t s) {
   const WideSide a = wide_side_args(w, 1, weighted, bb);
-  hipLaunchKernelGGL(k_wide_side, dim3((unsigned)wide_side_wgs(a.nq)), dim3(NT), 0, s, a);
+  hipLaunchKernelGGL(k_wide_side<false>, dim3((unsigned)wide_side_wgs(a.nq)), dim3(NT), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_wide_clear, dim3(16), dim3(NT), 0, s, w.gaccW, wide_clear_words(bb, weighted), w.wsync);
@@ -4207,10 +4252,12 @@ hipError_t launch_scale_wide(const Ws& w, int bb, float* D_block, hipStream_t s)
   a.mode = 2;
   a.raw = w.gramVW;
   a.rel = EXTERND_SCALE_GUARD_REL;
-  hipLaunchKernelGGL(k_wide_side, dim3((unsigned)wide_side_wgs(a.nq)), dim3(NT), 0, s, a);
+  a.mat = w.ginvVW;  // the U-step's inverse has been used
+  hipLaunchKernelGGL(k_wide_side<true>, dim3((unsigned)wide_side_wgs(a.nq)), dim3(NT), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_wide_scales, dim3(1), dim3(NT), 0, s, (const double*)a.ginv, (const double*)w.gvec, bb,
+  hipLaunchKernelGGL(k_wide_scales, dim3(1), dim3(4 * BMAX), 0, s, (const double*)a.ginv, (const double*)a.mat,
+                     (const double*)w.gvec, bb,
                      (const int*)w.wflag, w.dvec, w.dF, D_block, w.gaccW, wide_clear_words(bb, false), w.wsync);
   return hipGetLastError();
 }

@@ -158,3 +158,34 @@ def test_wide_end_to_end(ext, kind, m, n, mu, tau, block, iters, weighted):
     Rr = A.astype(np.float64) - (B.astype(np.float64) * D[None, :]) @ C.astype(np.float64)
     E = 1.0 - np.sum(Rr * Rr) / np.sum(A.astype(np.float64) ** 2)
     assert abs(E - res.E) <= 1e-5
+
+
+@pytest.mark.parametrize("m,n,bb,pairs", [(900, 700, 100, [(3, 5)]), (900, 700, 100, [(6, 7), (20, 90)]),
+                                          (1100, 1030, 128, [(63, 64), (64, 65)]),
+                                          (2100, 2060, 256, [(3, 5), (10, 200), (130, 131)])])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_wide_scale_ill_conditioned(ext, m, n, bb, pairs, weighted):
+    """As test_scale_ill_conditioned: copies inside a pivot pair, inside a
+    quarter, next to each other across quarters and quarters apart (M singular,
+    solvable by the guard)."""
+    print(f"[wide] scale, copies {pairs} {m}x{n} bb={bb} w={weighted}", flush=True)
+    R = synth.small("t4_rowscale", m, n, 9).astype(np.float64)
+    h = synth.small_importance(n, 9) if weighted else None
+    w = oracle.normalized_weights(h, n)
+    U, _ = oracle.init_block(R, w, bb, 1.0)
+    V, _ = oracle.vstep(R, U, 1.0)
+    U, V = U.copy(), V.copy()
+    for a, b in pairs:
+        U[:, b], V[:, b] = U[:, a], V[:, a]
+    Q = R @ (w[:, None] * V.astype(np.float64))
+    Uf, Vf = U.astype(np.float64), V.astype(np.float64)
+    M = (Uf.T @ Uf) * (Vf.T @ (w[:, None] * Vf))
+    g = np.sum(Uf * Q, axis=0)
+    assert np.linalg.cond(M) > 1e6
+    d_ref = oracle.scale_solve(U, V, Q, w)
+    d = host(ext.step_scale(cuda(U), cuda(V), cuda(Q), h=cuda(h) if weighted else None))
+    gain = lambda x: 2.0 * (x @ g) - x @ M @ x
+    assert abs(gain(d) - gain(d_ref)) <= 1e-9 * gain(d_ref)
+    keep = np.ones(bb, dtype=bool)
+    keep[[c for p in pairs for c in p]] = False
+    np.testing.assert_allclose(d[keep], d_ref[keep], rtol=1e-6, atol=1e-9 * np.max(np.abs(d_ref)))
