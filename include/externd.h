@@ -52,10 +52,11 @@ extern "C" {
 #define EXTERND_EUNSUPPORTED -5  /* shape outside the supported range                   */
 #define EXTERND_ESYNC        -6  /* a bounded wait between the workgroups of one kernel
                                     launch ran out (the U-step's row groups and the
-                                    V-step's last row group of each column tile wait at
-                                    most 20 ms for the inverse Gram of the same launch,
-                                    and in blocks wider than 64 the workgroups that build
-                                    that inverse wait at most 20 ms for each other);
+                                    V-step's last row group of each column tile wait for
+                                    the inverse Gram of the same launch, and in blocks
+                                    wider than 64 the workgroups that build that inverse
+                                    wait for each other; at most ten seconds, so that
+                                    another stream's kernel may hold the GPU meanwhile);
                                     the factors of such a call are not to be used       */
 #define EXTERND_ESCRATCH     -7  /* the call needs more than the fixed device scratch of
                                     an allocation-free entry point                       */

@@ -513,12 +513,16 @@ __device__ __forceinline__ void load_ginv(const double* ginv, double (&a)[16]) {
 // coherent (written through); once every one of them has completed
 // (s_waitcnt, then the barrier) one thread sets the flag.  The waiting side
 // polls it with coherent loads for at most SYNC_TICKS of the 100 MHz wall
-// clock (20 ms, against a few microseconds expected); past that it raises
-// FLAG_SYNC, which the host reports as EXTERND_ESYNC, and goes on.
+// clock (ten seconds, against a few microseconds expected); past that it raises
+// FLAG_SYNC, which the host reports as EXTERND_ESYNC, and goes on.  The bound
+// only ends a wait that cannot end: nothing that is waited for waits for the
+// streaming workgroups, but its workgroups may start late, behind another
+// stream's kernel that holds a die's CUs, and then for as long as that runs
+// (a bound of 20 ms failed such calls).
 // The flag is kept in FLAG_COPIES copies on lines of their own, and workgroup
 // b polls copy b % FLAG_COPIES: hundreds of workgroups asking for one line
 // delay its store.
-constexpr unsigned long long SYNC_TICKS = 2000000ull;
+constexpr unsigned long long SYNC_TICKS = 1000000000ull;
 __device__ __forceinline__ void ginv_ready(unsigned* ready) {
   if (!ready) return;
   __builtin_amdgcn_s_waitcnt(0);
