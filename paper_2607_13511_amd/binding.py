@@ -143,7 +143,11 @@ def _dev_ptr(t) -> int:
 def _stream_ptr(torch, stream) -> int:
     if stream is None:
         # the current stream's handle without building a Stream object for it
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # (1 us of a small call), where this torch has those private functions
+        raw, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and dev is not None:
+            return raw(dev())
+        stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
 

@@ -182,3 +182,13 @@ def test_apply_noalloc_rejects_before_device_work():
     assert wsb(10, 1 << 20, 10, 8) > binding.APPLY_NOALLOC_MAX_BYTES
     assert f(d, d, d, 10, 1 << 20, 10, d, 8, d, None) == binding.ESCRATCH
     assert L.externd_strerror(binding.ESCRATCH).decode().startswith("call exceeds the fixed device scratch")
+
+
+def test_current_stream_without_private_torch_functions():
+    """The current stream's handle does not depend on torch._C's private names."""
+    from types import SimpleNamespace
+    public = SimpleNamespace(current_stream=lambda: SimpleNamespace(cuda_stream=40))
+    assert binding._stream_ptr(SimpleNamespace(_C=SimpleNamespace(), cuda=public), None) == 40
+    private = SimpleNamespace(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda d: 50 + d)
+    assert binding._stream_ptr(SimpleNamespace(_C=private, cuda=public), None) == 53
+    assert binding._stream_ptr(SimpleNamespace(_C=private, cuda=public), SimpleNamespace(cuda_stream=60)) == 60
