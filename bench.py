@@ -95,11 +95,11 @@ def kernel_source_hash() -> str:
 
 
 def vstep_row_groups(m: int, n: int) -> int:
-    """Row groups of the V-step contraction (the library's layout rule:
-    about 480 column-tile x row-group workgroups, at most 8 groups and at
-    most 512 workgroups)."""
+    """Row groups of the V-step contraction (the library's layout rule: at most
+    480 column-tile x row-group workgroups, 512 for 241 to 256 column tiles,
+    and at most 8 groups)."""
     nct, nrt = -(-n // 32), -(-m // 32)
-    return max(1, min(-(-480 // nct), 512 // nct, nrt, 8))
+    return max(1, min(-(-480 // nct), (480 if nct <= 240 else 512) // nct, nrt, 8))
 
 
 def seq_flops(m: int, n: int, k: int, iters: int) -> float:

@@ -81,14 +81,20 @@ static Layout make_layout(int64_t m, int64_t n, int64_t k) {
   L.m_pad = round_up(m, TILE);
   L.n_pad = round_up(n, TILE);
   const int64_t nct = L.n_pad / TILE, nrt = L.m_pad / TILE;
-  // V-step: about 480 column-tile x row-group workgroups, but no more than
-  // are resident at once (2 a CU): a second, partial pass takes as long as a
-  // full one.  9728 columns: 608 workgroups in two passes 31.4 us, 304 in one
-  // 29.3.  The partials' space holds the uncut number of groups (the U-step's
-  // column groups use it too).  Deflation and staging: as many row groups as
-  // keep the whole deflation grid resident in one pass, for the same reason.
+  // V-step: as many column-tile x row-group workgroups as run in one pass
+  // beside the side workgroups and the slots left empty (USTEP_FREE; the wide
+  // blocks' 96 side workgroups finish late, their launch ends on them): a
+  // second, partial pass takes as long as a full one.  V-step launch at 9728 rows,
+  // 512 against 448 workgroups of 2048 columns 26.2 -> 22.5 us, 500 against 400 of
+  // 3200 35.6 -> 26.9, 510 against 340 of 5440 52.8 -> 41.9; 9728 columns, 608
+  // against 304 31.4 -> 29.3.  241 to 256 column tiles stay at two row groups, a few
+  // workgroups past one pass: one group would leave half of the slots empty
+  // (9728 x 8192, block 64: 25.0 ms, with one group 26.5).  The partials' space
+  // holds the uncut number of groups (the U-step's column groups use it too).
+  // Deflation and staging: as many row groups as keep the whole deflation grid
+  // resident in one pass, for the same reason.
   L.gvcap = clampi((480 + nct - 1) / nct, 1, nrt < GV_MAX ? nrt : GV_MAX);
-  L.gv = clampi(512 / nct, 1, L.gvcap);
+  L.gv = clampi((nct <= USTEP_FREE / 2 ? USTEP_FREE : USTEP_SLOTS) / nct, 1, L.gvcap);
   L.gd = clampi(DEFLATE_SLOTS / nct, 1, nrt < 64 ? nrt : 64);
   ustep_split(L.m_pad, L.n_pad, L.gvcap, &L.urows, &L.ntr, &L.gu);
   L.urows_wide = clampi((L.m_pad + USTEP_FREE - 1) / USTEP_FREE, 1, TILE);

@@ -59,3 +59,12 @@ def test_sparsity_and_bpw(m, n, k):
 def test_oracle_threads():
     t, avail = _bench().oracle_threads()
     assert 1 <= t <= avail == len(os.sched_getaffinity(0))
+
+
+def test_vstep_row_groups_run_in_one_pass():
+    """Up to 240 column tiles the V-step's streaming workgroups fit beside the
+    side workgroups and the slots left empty beside them (512 - 2 x 16)."""
+    for nct in range(1, 321):
+        gv = _bench().vstep_row_groups(9728, 32 * nct)
+        assert gv == 1 or nct * gv <= (480 if nct <= 240 else 512)
+        assert gv == min(8, 304) or nct * (gv + 1) > 480 or gv == -(-480 // nct)
