@@ -1,7 +1,7 @@
 """The block steps on the GPU against the fp64 oracle at the sizes where their
 launches change: pivot blocks of the 64x64 inverse (widths around multiples
 of 16), the U-step's column groups (few rows, many columns), the V-step's row
-groups (one from 8225 columns on), a contraction with fewer K steps than
+groups (one from 8225 columns on, also in wide blocks), a contraction with fewer K steps than
 waves or a remainder of them, and wide blocks of 2, 3 and 4 quarters with a
 last quarter of 1 or 64 components.
 
@@ -33,7 +33,7 @@ pytestmark = pytest.mark.gpu
 # m, n, bb
 NARROW = [(33, 2051, 5), (37, 40, 1), (97, 4100, 16), (97, 4100, 17), (250, 700, 48), (1030, 517, 63), (700, 1500, 64),
           (70, 8225, 24), (3100, 130, 33)]
-WIDE = [(700, 130, 65), (419, 999, 128), (1100, 523, 129), (805, 1290, 193), (1025, 811, 256)]
+WIDE = [(700, 130, 65), (419, 999, 128), (1100, 523, 129), (805, 1290, 193), (1025, 811, 256), (300, 8230, 130)]
 
 
 @pytest.fixture(scope="module")
