@@ -9,19 +9,16 @@
 //
 // One vector (a matrix-vector product): integer matrix cores, with the
 // vector's digit planes in LDS (k_gemv_c, k_gemv_b) or, beyond 10240
-// entries, brought there by segments (k_gemv_long).  Beyond 65536
-// entries, and in double for a short or small side beside one past 10240
-// (long_side), k_apply_vec_c and k_apply_vec_b:
-// FMA on the vector ALUs.  The signed 2-bit field extract (v_bfe_i32)
-// of a code is the trit itself (01 -> 1, 11 -> -1, 00 -> 0).  A workgroup
-// takes VEC_RPW consecutive rows; lane l of wave w takes byte
-// p = 64 w + l + 256 i of the rows (elements 4p .. 4p+3), so the vector
-// entries a wave needs are contiguous and each loaded slice serves all
-// VEC_RPW rows from registers.  Each wave sums its lanes with a fixed
-// shuffle tree (double: wave_sum8) and the four waves are added in wave order through LDS.  For
-// one vector the matrix-core path below spends more on decoding trits and
-// staging than this path spends on arithmetic; from two vectors on it is
-// the faster one.
+// entries, brought there by segments (k_gemv_long).  Beyond 65536 entries,
+// and with double sums for a short or small side beside one past 10240
+// (long_side), k_apply_vec_c and k_apply_vec_b: FMA on the vector ALUs.  The
+// signed 2-bit field extract (v_bfe_i32) of a code is the trit itself (01 ->
+// 1, 11 -> -1, 00 -> 0).  A workgroup takes VEC_RPW consecutive rows; lane l
+// of wave w takes byte p = 64 w + l + 256 i of the rows (elements 4p ..
+// 4p+3), so the vector entries a wave needs are contiguous and each loaded
+// slice serves all VEC_RPW rows from registers.  Each wave sums its lanes
+// with a fixed shuffle tree (double: wave_sum8) and the four waves are added
+// in wave order through LDS.
 //
 // Two or more vectors: both products run on bf16 MFMA with fp32 accumulation and
 // exact operands:
@@ -136,7 +133,8 @@ struct ProdArgs {
 };
 
 // N bytes at P + o, o < total = the matrix's bytes, of any alignment, as one
-// load (global loads take any byte address).  Where fewer than N bytes are
+// load (global loads take any byte address; off a word's they run at about a
+// third of the rate).  Where fewer than N bytes are
 // left, the load starts earlier and is shifted down when it is used
 // (window_fix), zeros above.  Bytes past the row's own are the next row's:
 // they meet zero vector entries.  A matrix of fewer than N bytes is read byte
@@ -655,16 +653,15 @@ __device__ __forceinline__ v4i_g gv_load(const uint8_t* __restrict__ P, int64_t 
   return v4i_g{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
 }
 
-// The wave's share of a tile: super-steps base + [s0, s1) of row `row` (rows past
+// The wave's share of a tile: super-steps [s0, s1) of row `row` (rows past
 // the matrix read its last row; their results are discarded).
 struct GvWave {
   const uint8_t* P;
   int64_t row, total;
-  int base;  // first super-step of the segment in LDS
   int s0, s1;
 };
 __device__ __forceinline__ GvWave gv_wave(const uint8_t* __restrict__ P, int64_t rows, int64_t rb, int nss,
-                                          int64_t r0, int base = 0) {
+                                          int64_t r0) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tile = w / GV_KSPLIT, kh = w % GV_KSPLIT;
   const int half = (nss + GV_KSPLIT - 1) / GV_KSPLIT;
@@ -673,7 +670,6 @@ __device__ __forceinline__ GvWave gv_wave(const uint8_t* __restrict__ P, int64_t
   v.P = P;
   v.row = (rr < rows ? rr : rows - 1) * rb;
   v.total = rows * rb;
-  v.base = base;
   v.s0 = kh * half < nss ? kh * half : nss;
   v.s1 = (kh + 1) * half < nss ? (kh + 1) * half : nss;
   return v;
@@ -689,8 +685,7 @@ constexpr int GV_PF = 6;
 template <bool ALIGNED>
 __device__ __forceinline__ v4i_g gv_step_load(const GvWave& v, int64_t rb, int j) {
   const int g = (threadIdx.x & 63) >> 4;
-  return gv_load<ALIGNED>(v.P, v.row, rb, v.total,
-                          v.base + (v.s0 + j < v.s1 ? v.s0 + j : v.s0), g);
+  return gv_load<ALIGNED>(v.P, v.row, rb, v.total, v.s0 + j < v.s1 ? v.s0 + j : v.s0, g);
 }
 
 // The first GV_PF steps' trit loads (issued before the vector is staged, so
@@ -728,7 +723,7 @@ __device__ __forceinline__ void gv_tile(const GvWave& v, int64_t rb, v4i_g (&buf
     // no branch: a step past the wave's share (or a chunk past the row)
     // multiplies zero trits, its B operands read at a clamped address
     const int cur = v.s0 + j;
-    const bool live = cur < v.s1 && (int64_t)(v.base + cur) * 64 + 16 * g < rb;
+    const bool live = cur < v.s1 && (int64_t)cur * 64 + 16 * g < rb;
     const int jb = cur < v.s1 ? j : 0;
     v4i_g bo[4];
 #pragma unroll
@@ -736,7 +731,7 @@ __device__ __forceinline__ void gv_tile(const GvWave& v, int64_t rb, v4i_g (&buf
     if (!ALIGNED && __any(v.row + rb + 64 > v.total)) {
       // the end of the matrix: a window may have started early
       unsigned u[4] = {(unsigned)buf[j][0], (unsigned)buf[j][1], (unsigned)buf[j][2], (unsigned)buf[j][3]};
-      const int64_t o = (int64_t)(v.base + (cur < v.s1 ? cur : v.s0)) * 64 + 16 * g;
+      const int64_t o = (int64_t)(cur < v.s1 ? cur : v.s0) * 64 + 16 * g;
       window_fix<16>(v.row + (o < rb ? o : 0), v.total, u);
       buf[j] = v4i_g{(int)u[0], (int)u[1], (int)u[2], (int)u[3]};
     }
