@@ -389,8 +389,9 @@ def render_mfma(db: str, out_path: str, command: str, m: int = 9728, n: int = 25
         util = busy / (d["dur"] * 1e-9 * 2.4e9 * 1024)
         lines.append(f"| {k} | {d['n']} | {i8:.4g} | {b16:.4g} | {f64:.4g} | {f'{a:.4g}' if a else '—'} | {busy:.4g} "
                      f"| {d['dur'] / 1e3:.1f} | {100 * util:.1f}% |")
-    lines += ["", "The contractions and the deflation are bound by HBM bandwidth (a pass over the residual), not by "
-              "the matrix cores: at the measured durations their MFMA pipes are busy for the fractions shown."]
+    lines += ["", "The matrix cores bound none of these launches: at the measured durations their MFMA pipes are busy for "
+              "the fractions shown. The deflation is bound by HBM bandwidth (a pass over the residual); a contraction "
+              "launch reads the residual once and ends on its side path (Gram, inverse, targets)."]
     with open(out_path, "w") as f:
         f.write("\n".join(lines) + "\n")
     print("\n".join(lines))
