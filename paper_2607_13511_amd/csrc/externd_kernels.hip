@@ -1770,7 +1770,7 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
       else if (a.raw) a.raw[(int64_t)gi * BMAX + gj] = v;
       acc[nt][r] = gi == gj ? (real && !zero ? v + ridge : 1.0) : (zero ? 0.0 : v);
     }
-  // (the matrix is symmetric: stored as G^{-1} below)
+  // (exactly symmetric: whole 512-byte lines)
   if (JOINT)
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
@@ -1819,10 +1819,8 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
       for (int nt = 0; nt < 4; ++nt) {
         v4d y = get_tile(Pt + 128 * (4 * w + nt));
         if (JOINT) {
-          // the mean with the transpose: the rows of a later quarter take A_ki^T P
-          // where the columns take P A_kj, and where M is singular but for its
-          // guard (components alike in two quarters) 1e-6 between the two would
-          // outweigh the scales
+          // the mean with the transpose: a singular M leaves 1e-6 between them, and
+          // only the guard to tell components alike in two quarters apart
           const double* T = (const double*)(Pt + 128 * (4 * nt + w));
 #pragma unroll
           for (int r = 0; r < 4; ++r)  // row li, column lk + 4 r of tile (nt, w)
@@ -1831,11 +1829,22 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
         const double sg = (nt < nb && w < nb) ? -1.0 : 1.0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) P[nt][r] = ldexp(sg * y[r], -(sexp[16 * w + lk + 4 * r] + sexp[16 * nt + li]));
-        acc[nt] = -P[nt];
       }
-      if (nq > 1) {
-        wide_publish(pivot, P);
-        wide_arrive(a.sync + WIDE_SYNC_PIVOT + 32 * k);
+      wide_publish(pivot, P);
+      wide_arrive(a.sync + WIDE_SYNC_PIVOT + 32 * k);
+      // -P^T (see the store at the end): row li, column lk + 4 r of tile (nt, w)
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) {
+        if (JOINT) {
+          acc[nt] = -P[nt];
+          continue;
+        }
+        const double* T = (const double*)(Pt + 128 * (4 * nt + w));
+        const double sg = (nt < nb && w < nb) ? 1.0 : -1.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          acc[nt][r] = ldexp(sg * T[128 * (li >> 3) + 2 * (16 * (li & 3) + lk + 4 * r) + ((li >> 2) & 1)],
+                             -(sexp[16 * w + lk + 4 * r] + sexp[16 * nt + li]));
       }
       __syncthreads();  // Pt and sexp are reused
       continue;
@@ -1901,16 +1910,20 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
     }
     __syncthreads();  // Pt and Yt are reused
   }
-  // G^{-1} = -S; the matrix is symmetric, so element (row, col) of block (i,
-  // j) goes to the place of (col, row) of block (j, i): whole 512-byte lines
-  double* out = a.ginv + (int64_t)(j * NQMAX + i) * 4096;
+  // G^{-1} = -S, each element at its own place.  S is symmetric but for rounding,
+  // and consistent along its rows: row block k holds P^T A_kj and -P^T, the others
+  // A_ik P and A_ij - (A_ik P) A_kj.  Where components in two quarters are alike,
+  // P is as large as the ridge (the joint solve: the guard) is small, and where
+  // one row mixed P and P^T, their difference would be 1e-6 to 1e-4 of the
+  // targets and a multiple of the scales.
+  double* out = a.ginv + (int64_t)(i * NQMAX + j) * 4096;
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int gi = BBP * i + 16 * w + lk + 4 * r, gj = BBP * j + 16 * nt + li;
       const double v = zero ? ((gi >= bb || gj >= bb) && gi == gj ? 1.0 : 0.0) : -acc[nt][r];
-      out[(nt * 16 + 4 * w + r) * 64 + lane] = v;
+      out[ginv_index(16 * w + lk + 4 * r, 16 * nt + li)] = v;
     }
 }
 

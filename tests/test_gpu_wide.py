@@ -189,3 +189,46 @@ def test_wide_scale_ill_conditioned(ext, m, n, bb, pairs, weighted):
     keep = np.ones(bb, dtype=bool)
     keep[[c for p in pairs for c in p]] = False
     np.testing.assert_allclose(d[keep], d_ref[keep], rtol=1e-6, atol=1e-9 * np.max(np.abs(d_ref)))
+
+
+# pairs of components alike, in different quarters
+COPIES = [(900, 700, 100, [(6, 70), (8, 72)]), (1100, 1030, 128, [(20, 90), (21, 91), (60, 64)]),
+          (2100, 2060, 256, [(i, i + 128) for i in range(128)])]
+
+
+def solve_bound(G, X):
+    """The fp64 inverse and the product with it, 8 bb cond(G) 2^-53 of the largest
+    entry, on both sides (cond(G) is 2e6 to 2e7 here: the ridge alone tells the
+    copies apart), beside the 1e-7 of the contraction."""
+    G = G + oracle.RIDGE_REL * np.trace(G) / len(G) * np.eye(len(G))
+    return (1e-7 + 2.0 * 8.0 * len(G) * np.linalg.cond(G) * 2.0 ** -53) * np.max(np.abs(X))
+
+
+@pytest.mark.parametrize("m,n,bb,pairs", COPIES)
+def test_wide_vstep_copies(ext, m, n, bb, pairs):
+    print(f"[wide] vstep, copies {m}x{n} bb={bb}", flush=True)
+    R = synth.small("t4_rowscale", m, n, 9)
+    U, _ = oracle.init_block(R.astype(np.float64), np.ones(n), bb, 1.0)
+    for a, b in pairs:
+        U[:, b] = U[:, a]
+    _, Y_ref = oracle.vstep(R.astype(np.float64), U, 1.0)
+    _, Y = ext.step_vstep(cuda(R), cuda(U), 1.0)
+    Uf = U.astype(np.float64)
+    assert np.max(np.abs(host(Y) - Y_ref)) <= solve_bound(Uf.T @ Uf, Y_ref)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("m,n,bb,pairs", COPIES)
+def test_wide_ustep_copies(ext, m, n, bb, pairs, weighted):
+    print(f"[wide] ustep, copies {m}x{n} bb={bb} w={weighted}", flush=True)
+    R = synth.small("t4_rowscale", m, n, 9)
+    h = synth.small_importance(n, 9) if weighted else None
+    w = oracle.normalized_weights(h, n)
+    U, _ = oracle.init_block(R.astype(np.float64), w, bb, 1.0)
+    V, _ = oracle.vstep(R.astype(np.float64), U, 1.0)
+    for a, b in pairs:
+        V[:, b] = V[:, a]
+    _, _, Z_ref = oracle.ustep(R.astype(np.float64), V, w, 1.0)
+    _, _, Z = ext.step_ustep(cuda(R), cuda(V), 1.0, h=cuda(h) if weighted else None)
+    Vf = V.astype(np.float64)
+    assert np.max(np.abs(host(Z) - Z_ref)) <= solve_bound(Vf.T @ (w[:, None] * Vf), Z_ref)
