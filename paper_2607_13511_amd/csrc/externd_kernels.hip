@@ -1558,8 +1558,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // workgroups (quarter pair x K slice) add integer Gram blocks with integer
 // atomics, and nq x nq sweep workgroups, each holding one 64 x 64 fp64 block
 // in registers, run the blocked sweep A -> -A^{-1}, one step per quarter:
-//   B_kk = -P, B_kj = P A_kj, B_ik = A_ik P, B_ij = A_ij - (A_ik P) A_kj,
-// P = A_kk^{-1}.  The blocks of row k (the swept matrix is symmetric, so
+//   B_kk = -P^T, B_kj = P^T A_kj, B_ik = A_ik P, B_ij = A_ij - (A_ik P) A_kj,
+// P = A_kk^{-1} (P^T differs by rounding only; see the store of G^{-1}).  The blocks of row k (the swept matrix is symmetric, so
 // A_ik = A_ki^T) and P travel through memory: written through, then counted
 // or flagged, then read with plain loads (each place is written once per
 // launch and read only after its flag, and a launch starts with clean
