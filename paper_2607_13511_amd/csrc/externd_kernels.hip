@@ -518,11 +518,12 @@ __device__ __forceinline__ void load_ginv(const double* ginv, double (&a)[16]) {
 // only ends a wait that cannot end: nothing that is waited for waits for the
 // streaming workgroups, but its workgroups may start late, behind another
 // stream's kernel that holds a die's CUs, and then for as long as that runs
-// (a bound of 20 ms failed such calls).
+// (a bound of 20 ms failed such calls).  Once FLAG_SYNC is up the call is lost
+// and its later launches wait no longer than SYNC_LOST_TICKS.
 // The flag is kept in FLAG_COPIES copies on lines of their own, and workgroup
 // b polls copy b % FLAG_COPIES: hundreds of workgroups asking for one line
 // delay its store.
-constexpr unsigned long long SYNC_TICKS = 1000000000ull;
+constexpr unsigned long long SYNC_TICKS = 1000000000ull, SYNC_LOST_TICKS = 2000000ull;
 __device__ __forceinline__ void ginv_ready(unsigned* ready) {
   if (!ready) return;
   __builtin_amdgcn_s_waitcnt(0);
@@ -533,7 +534,8 @@ __device__ __forceinline__ void await_flag(unsigned* ready, int* flags) {
   ready += FLAG_STRIDE * (blockIdx.x % FLAG_COPIES);
   const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
   while (load_coherent(ready) == 0u) {
-    if (__builtin_amdgcn_s_memrealtime() - t0 > SYNC_TICKS) {
+    const unsigned long long t = __builtin_amdgcn_s_memrealtime() - t0;
+    if (t > SYNC_TICKS || (t > SYNC_LOST_TICKS && load_coherent(flags + FLAG_SYNC) != 0)) {
       store_coherent(flags + FLAG_SYNC, 1);
       return;
     }
@@ -1611,9 +1613,11 @@ __host__ __device__ __forceinline__ int wide_gram_wgs(int nq) { return nq * (nq 
 __host__ __device__ __forceinline__ int wide_side_wgs(int nq) { return wide_gram_wgs(nq) + nq * nq; }
 
 // Waits (thread 0, then the workgroup) until *p reaches n; bounded as
-// await_flag.
+// await_flag.  FIRST: the launch's first wait, none in a lost call (the check
+// ends long before the Gram that is waited for).
+template <bool FIRST = false>
 __device__ __forceinline__ void wide_await(const unsigned* p, unsigned n, int* flags) {
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0 && (!FIRST || load_coherent(flags + FLAG_SYNC) == 0)) {
     const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
     while (load_coherent(p) < n) {
       if (__builtin_amdgcn_s_memrealtime() - t0 > SYNC_TICKS) {
@@ -1723,7 +1727,7 @@ __device__ __forceinline__ void wide_side(const WideSide& a, int b, char* smem) 
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   const int li = lane & 15, lk = lane >> 4;
   const int bb = a.bb;
-  wide_await(a.sync + WIDE_SYNC_GRAM, (unsigned)ngram, a.flags);
+  wide_await<true>(a.sync + WIDE_SYNC_GRAM, (unsigned)ngram, a.flags);
   const double unit = a.mode == 1 ? a.hwmax[1] : 1.0;
   auto gram = [&](int p, int e) {
     return a.mode == 1 ? (double)load_coherent((const long long*)a.gacc + (int64_t)p * 4096 + e) * unit
