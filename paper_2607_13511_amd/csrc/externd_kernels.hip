@@ -3975,51 +3975,60 @@ __global__ void k_set_scales(const double* __restrict__ d, int bb, double* dvec,
 // blocks (k_wide_side) and g_c = diag(U^T Q)_c (the per-split partial sums in
 // split order), refined once, d += M^{-1} (g - M d): the rounding of the inverse
 // of a nearly singular M (components alike) is 1e-7 of the block's energy
-// decrease, after it 1e-14.  Zero trace: d = 0.  d into dvec, dF (fp32) and D (the
-// block's output).  One workgroup of 4 x BMAX threads: row c = tid % BMAX of the
-// products, quarter tid / BMAX of their columns in order, the quarters added in
-// order.  Bound by the latency of the columns' loads: with a row a thread 18 us
-// for one product, now 27 for the three.  Also clears the side path's Gram
-// blocks and arrival words.
-__global__ __launch_bounds__(4 * BMAX) void k_wide_scales(const double* __restrict__ ginv,
-                                                          const double* __restrict__ mat,
-                                                          const double* __restrict__ gvec, int bb,
-                                                          const int* __restrict__ wflag, double* dvec, float* dF,
-                                                          float* Dout, int* gacc, int nclr, unsigned* sync) {
-  __shared__ double x[BMAX], part[NQMAX][BMAX];
-  static_assert(BMAX == NQMAX * BBP, "one column quarter per thread group");
-  const int c = threadIdx.x % BMAX, h = __builtin_amdgcn_readfirstlane(threadIdx.x / BMAX);
-  const bool live = h * BBP < bb && c < bb;
-  double g = 0.0;
-  if (c < bb)
+// decrease, after it 1e-11.  Zero trace: d = 0.  Three launches of 16 workgroups,
+// 16 rows each: STEP 0, A = M^{-1}: d0 = A g; 1, A = M: r = g - A d0; 2, A =
+// M^{-1}: d = d0 + A r into dvec, dF (fp32) and D (the block's output), and the
+// side path's Gram blocks and arrival words cleared.  Bound by latency: 14.4 us
+// for the three, one workgroup for all products 26.5 us (512 KB each through
+// one CU), and for one product without refinement 18.3.
+// tmp: d0 and r, BMAX doubles each.
+constexpr int WSCALE_WGS = BMAX / 16;
+template <int STEP>
+__global__ __launch_bounds__(NT) void k_wide_scales(const double* __restrict__ A, double* tmp,
+                                                    const double* __restrict__ gvec, int bb,
+                                                    const int* __restrict__ wflag, double* dvec, float* dF, float* Dout,
+                                                    int* gacc, int nclr, unsigned* sync) {
+  static_assert(BMAX == NT && NQMAX * BBP == BMAX, "one entry of x per thread");
+  __shared__ double x[BMAX], gs[BMAX], part[NT / 64][16];
+  const int c = threadIdx.x, lane = lane_id(), w = wave_id();
+  const int rg = (int)blockIdx.x, q = rg / 4, nq = (bb + BBP - 1) / BBP;  // rows 16 rg .. of quarter q
+  // this workgroup's rows of A: chunk i of the wave is 4 columns x 16 rows
+  double av[16];
+  if (q < nq)  // uniform
 #pragma unroll
-    for (int k = 0; k < TERN_SPLIT_MAX; ++k) g += gvec[c * TERN_SPLIT_MAX + k];
-  // row c of A x (x zero past bb), in every thread of the row
-  auto times = [&](const double* __restrict__ A, double v) {
-    __syncthreads();
-    if (h == 0) x[c] = v;
-    __syncthreads();
-    double s = 0.0;
-    if (live) {
-      const double* row = A + (int64_t)((c / BBP) * NQMAX + h) * 4096;
-#pragma unroll 32
-      for (int e = 0; e < BBP; ++e) s += row[ginv_index(c % BBP, e)] * x[BBP * h + e];
+    for (int i = 0; i < 16; ++i) {
+      const int q2 = i / 4 < nq ? i / 4 : 0;
+      av[i] = A[((int64_t)q * NQMAX + q2) * 4096 + ((rg % 4) * 16 + 4 * (i % 4) + w) * 64 + lane];
     }
-    part[h][c] = s;
-    __syncthreads();
-    return ((part[0][c] + part[1][c]) + part[2][c]) + part[3][c];
-  };
-  wide_clear(gacc, nclr, sync, 0, 1);
-  double d = 0.0;
-  if (*wflag == 0) {  // uniform
-    d = times(ginv, g);
-    const double r = g - times(mat, d);
-    d += times(ginv, r);
+  if (STEP < 2) {
+    double g = 0.0;
+    if (c < bb)
+#pragma unroll
+      for (int k = 0; k < TERN_SPLIT_MAX; ++k) g += gvec[c * TERN_SPLIT_MAX + k];
+    gs[c] = g;
   }
-  if (h == 0) {
-    dvec[c] = d;
-    dF[c] = (float)d;
-    if (Dout && c < bb) Dout[c] = (float)d;
+  x[c] = STEP == 0 ? gs[c] : tmp[(STEP == 1 ? 0 : BMAX) + c];
+  if (STEP == 2) wide_clear(gacc, nclr, sync, rg, WSCALE_WGS);
+  __syncthreads();
+  double s = 0.0;
+  if (q < nq)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (i / 4 < nq) s += av[i] * x[BBP * (i / 4) + 4 * (4 * (i % 4) + w) + (lane >> 4)];
+  s += __shfl_xor(s, 16, 64);
+  s += __shfl_xor(s, 32, 64);
+  if (lane < 16) part[w][lane] = s;
+  __syncthreads();
+  if (threadIdx.x >= 16) return;
+  const int row = 16 * rg + c;
+  const double v = ((part[0][c] + part[1][c]) + part[2][c]) + part[3][c];
+  if (STEP == 0) tmp[row] = v;
+  if (STEP == 1) tmp[BMAX + row] = gs[row] - v;
+  if (STEP == 2) {
+    const double d = row < bb && *wflag == 0 ? tmp[row] + v : 0.0;
+    dvec[row] = d;
+    dF[row] = (float)d;
+    if (Dout && row < bb) Dout[row] = (float)d;
   }
 }
 
@@ -4275,11 +4284,21 @@ hipError_t launch_scale_wide(const Ws& w, int bb, float* D_block, hipStream_t s)
   a.rel = EXTERND_SCALE_GUARD_REL;
   a.mat = w.ginvVW;  // the U-step's inverse has been used
   hipLaunchKernelGGL(k_wide_side<true>, dim3((unsigned)wide_side_wgs(a.nq)), dim3(NT), 0, s, a);
-  const hipError_t e = hipGetLastError();
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_wide_scales, dim3(1), dim3(4 * BMAX), 0, s, (const double*)a.ginv, (const double*)a.mat,
-                     (const double*)w.gvec, bb,
-                     (const int*)w.wflag, w.dvec, w.dF, D_block, w.gaccW, wide_clear_words(bb, false), w.wsync);
+  double* tmp = w.wpanel;  // the side path has used it
+  const double* ginv = a.ginv;
+  const int nclr = wide_clear_words(bb, false);
+  hipLaunchKernelGGL(k_wide_scales<0>, dim3(WSCALE_WGS), dim3(NT), 0, s, ginv, tmp, (const double*)w.gvec, bb,
+                     (const int*)w.wflag, w.dvec, w.dF, D_block, w.gaccW, nclr, w.wsync);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_wide_scales<1>, dim3(WSCALE_WGS), dim3(NT), 0, s, (const double*)a.mat, tmp,
+                     (const double*)w.gvec, bb, (const int*)w.wflag, w.dvec, w.dF, D_block, w.gaccW, nclr, w.wsync);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_wide_scales<2>, dim3(WSCALE_WGS), dim3(NT), 0, s, ginv, tmp, (const double*)w.gvec, bb,
+                     (const int*)w.wflag, w.dvec, w.dF, D_block, w.gaccW, nclr, w.wsync);
   return hipGetLastError();
 }
 
